@@ -15,7 +15,10 @@ spread between the modes and ln Z comes out far too high at p = 5d).  ``value`` 
 evaluations of runs whose ln Z passes the 3 sigma check, divided by the wall time of all timed
 runs (the pass count is printed beside it, and ``rate_all_runs`` is the raw rate).  Labelled
 legs run the same workload with the full-covariance metric at p = 5d and at p = 20d, and the
-plain FP64 form with the headline's settings.
+plain FP64 form with the headline's settings.  In all of these every candidate's likelihood is
+evaluated as a point (8 planned tests per round, or the 4-test kernel in FP64).  The library's
+default for mixtures evaluates a step's candidates along the step's line instead (the same
+decisions and trajectories); the labelled leg ``line_evaluation`` times that.
 
 Prints one JSON line (see the keys below).  --gpus N > 1 is not supported (one GPU).
 """
@@ -90,13 +93,24 @@ def algorithmic_flop_per_eval(K: int, d: int) -> int:
     return K * d * (d + 1) + 3 * K * d
 
 
+def line_flop(K: int, d: int, steps: float, evals: float) -> float:
+    """The work of chains evaluated along their lines: per step and component the image of the
+    direction under the triangular factor and two dot products, per evaluation a parabola."""
+    return K * (steps * (d * (d + 1) + 4 * d) + 6.0 * evals)
+
+
 def run_gpu(N, prob, precision, seeds, p, warmup, timing=True, autotune=True, shape_out=None,
-            diagonal_metric=False):
+            diagonal_metric=False, points=False):
     """Runs len(seeds) full NS runs on one context (the launch shape tuned during the warmup
-    runs, or on the first timed run without warmup); returns per-run records and totals."""
+    runs, or on the first timed run without warmup); returns per-run records and totals.
+    points: every candidate evaluated as a point, in the shape the tuner chooses among those
+    kernels on the benchmark (4 chains per workgroup; 8 tests per round, or 4 in FP64)."""
     import torch
+    if points:
+        autotune = False
     R = N.NSRun(prob, p=p, seed=seeds[0], precision=precision, timing=timing,
-                autotune=autotune, diagonal_metric=diagonal_metric)
+                autotune=autotune, diagonal_metric=diagonal_metric,
+                plan8=points and precision != "fp64", shallow_plan=points and precision == "fp64")
     for w in range(warmup):
         R.reset(10_000 + w)
         R.run()
@@ -335,9 +349,10 @@ def bench_batch(args):
         cpw[str(c)] = cpw.get(str(c), 0) + 1
     stats = [B.stats(r) for r in range(len(probs))]
     evals = sum(s["evals"] for s in stats)
-    fpe = [p["d"] * (p["d"] + 1) + 3 * p["d"] if p["lik"] == "mixture" else 3 * p["d"]
-           for p in probs]
-    flops = sum(s["evals"] * f for s, f in zip(stats, fpe))
+    flops = sum(line_flop(1, p["d"], float(s["iterations"]) * p["k"] * p["p"], s["evals"])
+                if p["lik"] == "mixture" else
+                float(s["iterations"]) * p["k"] * p["p"] * 4 * p["d"] + 10.0 * s["evals"]
+                for p, s in zip(probs, stats))
     done = sum(B.state(r)["done"] for r in range(len(probs)))
     zs, errs, _ = B.logz()
     z_of = []
@@ -358,10 +373,12 @@ def bench_batch(args):
                    "runs_done": done, "max_iterations": it, "graphs": args.graph,
                    "concurrent_groups": not args.serial_groups,
                    "autotune": not args.no_autotune, "runs_by_chains_per_workgroup": cpw},
-        "roofline": {"bound": "mfma", "achieved": flops / dt / 1e12, "peak": 2500.0,
-                     "unit": "TFLOP/s", "frac": flops / dt / 2.5e15, "traffic": None,
+        "roofline": {"bound": "mfma", "achieved": flops / dt / 1e12, "peak": 78.6,
+                     "unit": "TFLOP/s", "frac": flops / dt / 78.6e12, "traffic": None,
                      "kernel": "whole job (host clock, all runs and kernels)",
-                     "flop_per_eval": "d(d+1)+3d (Gaussian), 3d (funnel)"},
+                     "flop_per_eval": "per step d(d+1) + 4d (Gaussian) or 4d (funnel), per "
+                                      "evaluation 6 or 10: candidates along the step's line, "
+                                      "FP64"},
         "lnz": {"runs_within_3sigma": f"{sum(abs(z) < 3 for z in z_of)}/{len(z_of)}",
                 "z_by_run": z_of},
     }
@@ -789,8 +806,8 @@ def bench_smc(args):
               file=sys.stderr, flush=True)
         R.close()
     smc = res["smc"]
-    fpe = algorithmic_flop_per_eval(1, d)
-    achieved = smc["evals"] * fpe / (smc["hrss_ms"] / 1e3)
+    work = line_flop(1, d, float(smc["launches"]) * prob["m"] * 5 * d, smc["evals"])
+    achieved = work / (smc["hrss_ms"] / 1e3)
     zs = np.array(smc["logz"])
     out = {
         "metric": "SMC-SS likelihood evals/s (d=32 correlated Gaussian, 1000 particles)",
@@ -802,7 +819,8 @@ def bench_smc(args):
                    "particles": prob["m"], "chain_len": 5 * d, "ess_frac": 0.5},
         "roofline": {"bound": "mfma", "achieved": achieved / 1e12, "peak": 78.6,
                      "unit": "TFLOP/s", "frac": achieved / 78.6e12, "traffic": None,
-                     "kernel": "k_hrss<32, FP64, mixture, 1> (tempered)", "flop_per_eval": fpe,
+                     "kernel": "k_hrss_line (D = 32, mixture, tempered)",
+                     "flop_per_eval": work / max(1, smc["evals"]),
                      "avg_launch_ms": smc["hrss_ms"] / max(1, smc["launches"])},
         "lnz": {"truth": tz, "smc": smc["logz"], "smc_mean_error": float(zs.mean() - tz),
                 "smc_spread": float(zs.std()), "ns": res["ns"]["logz"],
@@ -827,26 +845,28 @@ def bench_small(args, which):
     if which == "gauss5":
         prob, precs = G.config1(), ["fp64"]
         truth = -5 * math.log(2.0) + 5 * math.log(erf(1.0 / (0.1 * math.sqrt(2.0))))
-        fpe, workload = 3 * 5 + 2, "gauss5_box1_nlive200_k50_p25"
+        workload = "gauss5_box1_nlive200_k50_p25"
     else:
         prob, precs = G.config2(), ["bf16x3", "fp64"]
         d = prob["d"]
         truth = float(multivariate_normal(mean=np.zeros(d), cov=prob["cov"][0] + 4 * np.eye(d))
                       .logpdf(prob["mu"][0]))
-        fpe, workload = algorithmic_flop_per_eval(1, d), "corr32_cond1e3_prior4_nlive1000_k500_p160"
+        workload = "corr32_cond1e3_prior4_nlive1000_k500_p160"
     seeds = list(range(args.steps))
     res = {}
     for prec in precs:
         recs, total = run_gpu(N, prob, prec, seeds, prob["p"], args.warmup)
         evals = sum(r["evals"] for r in recs)
         hrss_s = sum(r["hrss_ms"] for r in recs) / 1e3
-        res[prec] = dict(recs=recs, total=total, evals=evals, hrss_s=hrss_s,
-                         launches=sum(r["hrss_launches"] for r in recs))
+        launches = sum(r["hrss_launches"] for r in recs)
+        res[prec] = dict(recs=recs, total=total, evals=evals, hrss_s=hrss_s, launches=launches,
+                         flops=line_flop(1, prob["d"], float(launches) * prob["k"] * prob["p"],
+                                         evals))
     main_prec = precs[0]
     r0 = res[main_prec]
     mixed = main_prec != "fp64"
-    peak = 2.5e15 if mixed else 78.6e12
-    achieved = r0["evals"] * fpe / r0["hrss_s"] if r0["hrss_s"] > 0 else 0.0
+    peak = 78.6e12   # the chains evaluate along their lines in FP64 in every precision
+    achieved = r0["flops"] / r0["hrss_s"] if r0["hrss_s"] > 0 else 0.0
     rates = [r["evals"] / r["wall_s"] for r in r0["recs"]]
     out = {
         "metric": f"slice-step likelihood evals/s ({which})", "value": r0["evals"] / r0["total"],
@@ -858,7 +878,8 @@ def bench_small(args, which):
                    "chain_len": prob["p"], "precision": main_prec, "seeds": seeds},
         "roofline": {"bound": "mfma" if which == "corr32" else "alu", "achieved": achieved / 1e12,
                      "peak": peak / 1e12, "unit": "TFLOP/s", "frac": achieved / peak,
-                     "traffic": None, "kernel": "k_hrss", "flop_per_eval": fpe,
+                     "traffic": None, "kernel": "k_hrss_line",
+                     "flop_per_eval": r0["flops"] / max(1, r0["evals"]),
                      "avg_launch_ms": 1e3 * r0["hrss_s"] / max(1, r0["launches"])},
         "per_seed_evals_per_s": {"median": statistics.median(rates),
                                  "range": [min(rates), max(rates)]},
@@ -869,7 +890,7 @@ def bench_small(args, which):
         r1 = res[prec]
         out[prec] = {"value": r1["evals"] / r1["total"], "unit": "evals/s",
                      "z_scores": [(r["logz"] - truth) / r["err"] for r in r1["recs"]],
-                     "frac_of_fp64_peak": r1["evals"] * fpe / max(r1["hrss_s"], 1e-12) / 78.6e12}
+                     "frac_of_fp64_peak": r1["flops"] / max(r1["hrss_s"], 1e-12) / 78.6e12}
     if not args.no_cpu:
         # a mid-run live set about a third of the way through these short runs
         out["cpu_baseline"] = cpu_baseline(prob, prob["p"], args.cpu_seconds, warm_iters=0)
@@ -899,6 +920,9 @@ def main():
                     help="chain length factor of the labelled long-chain line")
     ap.add_argument("--long-chain-steps", type=int, default=5,
                     help="runs of the long-chain line (full-covariance metric; 0 = skip)")
+    ap.add_argument("--line-steps", type=int, default=3,
+                    help="runs of the labelled line on the default chains, which evaluate "
+                         "candidates along each step's line (0 = skip)")
     ap.add_argument("--no-cpu", action="store_true")
     ap.add_argument("--no-autotune", action="store_true",
                     help="keep the launch-shape rule (4 chains per workgroup, 16 planned tests "
@@ -997,7 +1021,7 @@ def main():
     shape = {}
     diag = args.metric == "diagonal"
     recs, total = run_gpu(N, prob, args.precision, seeds, p, args.warmup,
-                          autotune=not args.no_autotune, shape_out=shape, diagonal_metric=diag)
+                          shape_out=shape, diagonal_metric=diag, points=True)
     head = summary(recs, total)
     evals = sum(r["evals"] for r in recs)
     hrss_s = sum(r["hrss_ms"] for r in recs) / 1e3
@@ -1054,7 +1078,7 @@ def main():
                              "unit": "T lane-instr/s", "frac": a / VALU_PEAK}
     if args.fp64_steps > 0 and mixed:
         r64, t64 = run_gpu(N, prob, "fp64", list(range(args.fp64_steps)), p, 1,
-                           autotune=not args.no_autotune, diagonal_metric=diag)
+                           diagonal_metric=diag, points=True)
         s64 = summary(r64, t64)
         ev64 = sum(r["evals"] for r in r64)
         out["fp64"] = {"value": s64["value"], "rate_all_runs": s64["rate_all_runs"],
@@ -1069,7 +1093,7 @@ def main():
     if args.other_metric_steps > 0:
         # the same workload and chain length with the other direction metric
         ro, to = run_gpu(N, prob, args.precision, list(range(args.other_metric_steps)), p, 0,
-                         autotune=not args.no_autotune, diagonal_metric=not diag)
+                         diagonal_metric=not diag, points=True)
         so = summary(ro, to)
         out["other_metric"] = {
             "label": "the same workload at p = 5d with the direction metric from the survivors' "
@@ -1081,7 +1105,7 @@ def main():
     if args.long_chain_steps > 0:
         pl = args.long_chain_factor * d
         rl, tl = run_gpu(N, prob, args.precision, list(range(args.long_chain_steps)), pl, 0,
-                         autotune=not args.no_autotune, diagonal_metric=False)
+                         diagonal_metric=False, points=True)
         sl = summary(rl, tl)
         out["long_chain"] = {"label": f"the same workload at chain length p = "
                                       f"{args.long_chain_factor}d = {pl} (not the configured "
@@ -1091,6 +1115,23 @@ def main():
                              "runs_within_3sigma": sl["runs_within_3sigma"],
                              "z_scores": sl["z_scores"], "z_mean": sl["z_mean"],
                              "z_sd": sl["z_sd"], "iterations": sl["iterations"]}
+    if args.line_steps > 0:
+        re, te = run_gpu(N, prob, args.precision, list(range(args.line_steps)), p, 1,
+                         autotune=not args.no_autotune, diagonal_metric=diag)
+        se = summary(re, te)
+        ms = sum(r["hrss_ms"] for r in re)
+        n = sum(r["hrss_launches"] for r in re)
+        fl = line_flop(K, d, float(n) * prob["k"] * p, sum(r["evals"] for r in re))
+        out["line_evaluation"] = {
+            "label": "the headline's workload and settings on the library's default chains: "
+                     "candidates evaluated along each step's line, in FP64",
+            "value": se["value"], "rate_all_runs": se["rate_all_runs"], "unit": "evals/s",
+            "runs_within_3sigma": se["runs_within_3sigma"],
+            "ms_per_run": 1e3 * te / args.line_steps, "avg_launch_ms": ms / max(1, n),
+            "frac_of_fp64_peak": fl / (ms / 1e3) / 78.6e12 if ms > 0 else None,
+            "same_trajectory_as_headline": [
+                a["iters"] == b["iters"] and a["evals"] == b["evals"]
+                and abs(a["logz"] - b["logz"]) < 1e-9 for a, b in zip(re, recs)]}
     if not args.no_cpu:
         out["cpu_baseline"] = cpu_baseline(prob, p, args.cpu_seconds, diagonal_metric=diag)
     print(json.dumps(out), flush=True)

@@ -201,15 +201,20 @@ typedef enum {
                               * allowed) in this process, which then do not tune.  Results are
                               * identical with and without it.  Not used by NS_LIK_GP (one chain
                               * per workgroup). */
-#define NS_FLAG_SHALLOW_PLAN 64  /* mixture chains in a 16-bit mode plan at most 4 tests per
-                                 * round (the two bracket ends, then shrink proposals) instead
-                                 * of 16 (the next two stepping-out tests of each open end and
-                                 * the shrink proposals of the likeliest expansion outcomes).
-                                 * Decisions, trajectories and counters are identical. */
+#define NS_FLAG_SHALLOW_PLAN 64  /* every candidate is evaluated as a point, with at most 4
+                                 * tests planned per round (the two bracket ends, then shrink
+                                 * proposals).  By default a mixture's (up to 16 components) or
+                                 * the funnel's slice chains, which read their directions from
+                                 * the buffer, evaluate sixteen candidates of a step at a time
+                                 * along the step's line: the quadratic forms are parabolas in
+                                 * t, held in FP64 in every precision (no re-checks), and each
+                                 * chain's final point is evaluated as a point.  Decisions and
+                                 * trajectories are identical. */
 #define NS_FLAG_PLAN8 128  /* mixture chains in a 16-bit mode plan 8 tests per round (the
                            * next two stepping-out tests of each open end and the shrink
-                           * proposals of the three likeliest expansion outcomes) instead of
-                           * 16; identical results.  NS_FLAG_SHALLOW_PLAN takes precedence. */
+                           * proposals of the three likeliest expansion outcomes), each
+                           * evaluated as a point; identical results.  NS_FLAG_SHALLOW_PLAN
+                           * takes precedence. */
 #define NS_FLAG_GP_NO_WAIT 256  /* testing the failure path of NS_LIK_GP chains: the
                                 * factorisation's bounded wait for each diagonal tile gives up
                                 * at once, so every chain evaluation fails (log L = -inf, a
@@ -437,7 +442,9 @@ ns_status ns_tune_load(const char *path, int32_t *n);
 ns_status ns_tune_clear(int32_t *n);
 
 /* The launch shape run `run`'s chains use now: chains per workgroup and tests planned per
- * round (4 for the k_hrss kernel, 8 or 16 for the hypothesis-plan kernel, 1 for NS_LIK_GP).
+ * round (4 for the k_hrss kernel and for FP64 chains evaluated along their lines, 8 for the
+ * hypothesis-plan kernel, 16 for it or for 16-bit chains evaluated along their lines, 1 for
+ * NS_LIK_GP).
  * Either output may be NULL.  Errors: NS_EINVAL for a NULL context or a run out of range. */
 ns_status ns_launch_shape(const ns_ctx *ctx, int32_t run, int32_t *chains_per_wg,
                           int32_t *plan_tests);

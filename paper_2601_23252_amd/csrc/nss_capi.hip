@@ -24,6 +24,7 @@ struct RunHost {
     DevProblem P;   // descriptor in the run's own precision
     DevRun R;
     // 16-bit W fragments per format, and the rounded remainders for the split modes
+    double wmax = 0.0;   // largest magnitude in the mixture's inverse Cholesky factors
     const uint4 *wf_bf16 = nullptr, *wf_fp16 = nullptr, *wf_bf16_lo = nullptr,
                 *wf_fp16_lo = nullptr;
     int done = 0;
@@ -36,6 +37,7 @@ struct Group {
     int D, lik, mode, upwT, rw;
     bool plan_ok;   // 16-bit mixture chains that may use the hypothesis-plan kernel
     int plan;       // tests a chain plans per round: 0 = the k_hrss kernel (up to 4), or 8 / 16
+    bool line;      // FP64 chains, and 16-bit ones at 16 tests, evaluate along each step's line
     std::vector<int> runs;
 };
 
@@ -331,7 +333,10 @@ static ns_status prepare_problem(ns_ctx *ctx, RunHost &rh, const ns_prior *prior
         for (int j = 0; j < d; ++j) logdetW -= log(L[j * d + j]);
         std::fill(W.begin(), W.end(), 0.0);
         for (int r = 0; r < d; ++r)
-            for (int s = 0; s < d; ++s) W[r * D + s] = Wd[r * d + s];
+            for (int s = 0; s < d; ++s) {
+                W[r * D + s] = Wd[r * d + s];
+                if (!(fabs(Wd[r * d + s]) <= rh.wmax)) rh.wmax = fabs(Wd[r * d + s]);
+            }
         for (int j = 0; j < d; ++j) {
             mu[(size_t)c * D + j] = en->mean[(size_t)c * d + j];
             mu32[(size_t)c * D + j] = (float)mu[(size_t)c * D + j];
@@ -447,6 +452,36 @@ static int dirs_blocks(const RunHost &r)
     return (int)((t + dirs_rows(r.D) - 1) / dirs_rows(r.D));
 }
 static int hrss_blocks(const RunHost &r) { return (r.k + r.R.C - 1) / r.R.C; }  // GP: C = 1
+
+// Whether a run's chains may be evaluated along each step's line (k_hrss_line): a likelihood of
+// quadratic forms, slice chains with the direction buffer, one workgroup's Gram matrices in LDS
+// (sixteen components), chains long enough that a block of fifteen steps is mostly used (a
+// shorter chain pays for the whole block: the products of one block cost what the batched tile
+// takes for about three steps), and parameters whose squares stay finite (an overflow to
+// infinity minus infinity would differ from the point evaluation's).
+constexpr int kLineMinSteps = 4;
+constexpr double kLineMax = 1e40;
+static bool line_ok(const RunHost &rh, const ns_prior *prior, const ns_energy *en)
+{
+    if (rh.lik != LIK_MIXTURE && rh.lik != LIK_FUNNEL) return false;
+    if (rh.R.rw || !rh.R.dirbuf || rh.p < kLineMinSteps) return false;
+    if (rh.cfg.flags & NS_FLAG_SHALLOW_PLAN) return false;
+    if (rh.lik == LIK_MIXTURE && rh.K > 16) return false;
+    if (line_lds_bytes(rh.D, rh.K, rh.lik) > 160 * 1024) return false;
+    auto fits = [](double v) { return fabs(v) <= kLineMax; };
+    const bool box = rh.P.prior_kind == PRIOR_BOX;
+    for (int j = 0; j < rh.d; ++j)
+        if (!fits(prior->a[j]) || !fits(prior->b[j]) || (!box && !fits(1.0 / prior->b[j])))
+            return false;
+    if (!fits(rh.R.width)) return false;
+    if (rh.lik == LIK_FUNNEL) {   // exp(-x_0) has to stay finite
+        const double a = prior->a[0], b = prior->b[0];
+        return box ? (a >= -600.0 && b <= 600.0) : fabs(a) + 40.0 * b <= 600.0;
+    }
+    for (size_t i = 0; i < (size_t)rh.K * rh.d; ++i)
+        if (!fits(en->mean[i])) return false;
+    return rh.wmax <= kLineMax;
+}
 
 struct MapBuilder {
     std::vector<int2> &h;
@@ -593,12 +628,18 @@ static int plan_occupancy(const ns_ctx *ctx, const Launch &L)
     return (L.nblocks > kChipCUs || ctx->forked) ? 2 : 1;
 }
 
+// The 4- and 8-test shapes of the 16-bit modes stay on the point-evaluating kernels (a caller
+// or the tuner chooses them); 16 tests and FP64 are the line kernel's.
+static bool use_line(const Group &G) { return G.line && (!G.plan_ok || G.plan == 16); }
+
 static ns_status enqueue_hrss_group(ns_ctx *ctx, size_t g, hipStream_t s)
 {
     const Group &G = ctx->groups[g];
     const hipError_t e =
         G.lik == LIK_GP ? launch_hrss_gp(ctx->L_hrss[g], G.mode, s)
         : G.rw          ? launch_rw(ctx->L_hrss[g], G.D, G.lik, G.mode, G.upwT, s)
+        : use_line(G)   ? launch_hrss_line(ctx->L_hrss[g], G.D, G.lik, ctx->smc,
+                                           G.mode == MODE_FP64, s)
         : G.plan        ? launch_hrss_plan(ctx->L_hrss[g], G.D, G.mode, G.upwT, G.plan,
                                            plan_occupancy(ctx, ctx->L_hrss[g]), s)
                         : launch_hrss(ctx->L_hrss[g], G.D, G.lik, G.mode, G.upwT, s);
@@ -1203,16 +1244,17 @@ extern "C" ns_status ns_init_batch(int32_t n_runs, const ns_prior *priors,
                              rh.D <= 128 && rh.R.dirbuf &&
                              !(rh.cfg.flags & NS_FLAG_SHALLOW_PLAN);
         const int plan0 = !plan_ok ? 0 : (rh.cfg.flags & NS_FLAG_PLAN8) ? 8 : kDefaultPlan;
+        const bool line = line_ok(rh, priors + r, energies + r);
         int g = -1;
         for (size_t i = 0; i < ctx->groups.size(); ++i) {
             const Group &G = ctx->groups[i];
             if (G.D == rh.D && G.lik == rh.lik && G.mode == rh.mode && G.upwT == rh.upw &&
-                G.rw == rh.R.rw && G.plan_ok == plan_ok && G.plan == plan0)
+                G.rw == rh.R.rw && G.plan_ok == plan_ok && G.plan == plan0 && G.line == line)
                 g = (int)i;
         }
         if (g < 0) {
             ctx->groups.push_back(Group{rh.D, rh.lik, rh.mode, rh.upw, rh.R.rw, plan_ok, plan0,
-                                        {}});
+                                        line, {}});
             g = (int)ctx->groups.size() - 1;
         }
         ctx->groups[g].runs.push_back(r);
