@@ -37,7 +37,8 @@ struct Group {
     int D, lik, mode, upwT, rw;
     bool plan_ok;   // 16-bit mixture chains that may use the hypothesis-plan kernel
     int plan;       // tests a chain plans per round: 0 = the k_hrss kernel (up to 4), or 8 / 16
-    bool line;      // FP64 chains, and 16-bit ones at 16 tests, evaluate along each step's line
+    int line;       // FP64 chains, and 16-bit ones at 16 tests, evaluate along each step's line:
+                    // 0 = no, 1 = box priors, 2 = Gaussian priors
     std::vector<int> runs;
 };
 
@@ -467,9 +468,9 @@ static bool line_ok(const RunHost &rh, const ns_prior *prior, const ns_energy *e
     if (rh.R.rw || !rh.R.dirbuf || rh.p < kLineMinSteps) return false;
     if (rh.cfg.flags & NS_FLAG_SHALLOW_PLAN) return false;
     if (rh.lik == LIK_MIXTURE && rh.K > 16) return false;
-    if (line_lds_bytes(rh.D, rh.K, rh.lik) > 160 * 1024) return false;
-    auto fits = [](double v) { return fabs(v) <= kLineMax; };
     const bool box = rh.P.prior_kind == PRIOR_BOX;
+    if (line_lds_bytes(rh.D, rh.K, rh.lik, box) > 160 * 1024) return false;
+    auto fits = [](double v) { return fabs(v) <= kLineMax; };
     for (int j = 0; j < rh.d; ++j)
         if (!fits(prior->a[j]) || !fits(prior->b[j]) || (!box && !fits(1.0 / prior->b[j])))
             return false;
@@ -618,7 +619,7 @@ static ns_status enqueue_pre(ns_ctx *ctx)
 }
 
 // The chains of group g.
-// Workgroups per CU the hypothesis-plan kernel is compiled for: two when the launch has more
+// Workgroups per CU the hypothesis-plan and line kernels are compiled for: two when the launch has more
 // workgroups than the chip has CUs, or runs beside other groups' chains on side streams (two
 // resident workgroups then hide each other's latency, at the cost of spilled registers), else
 // one.
@@ -639,7 +640,8 @@ static ns_status enqueue_hrss_group(ns_ctx *ctx, size_t g, hipStream_t s)
         G.lik == LIK_GP ? launch_hrss_gp(ctx->L_hrss[g], G.mode, s)
         : G.rw          ? launch_rw(ctx->L_hrss[g], G.D, G.lik, G.mode, G.upwT, s)
         : use_line(G)   ? launch_hrss_line(ctx->L_hrss[g], G.D, G.lik, ctx->smc,
-                                           G.mode == MODE_FP64, s)
+                                           G.line == 1, G.mode == MODE_FP64,
+                                           plan_occupancy(ctx, ctx->L_hrss[g]), s)
         : G.plan        ? launch_hrss_plan(ctx->L_hrss[g], G.D, G.mode, G.upwT, G.plan,
                                            plan_occupancy(ctx, ctx->L_hrss[g]), s)
                         : launch_hrss(ctx->L_hrss[g], G.D, G.lik, G.mode, G.upwT, s);
@@ -1244,7 +1246,9 @@ extern "C" ns_status ns_init_batch(int32_t n_runs, const ns_prior *priors,
                              rh.D <= 128 && rh.R.dirbuf &&
                              !(rh.cfg.flags & NS_FLAG_SHALLOW_PLAN);
         const int plan0 = !plan_ok ? 0 : (rh.cfg.flags & NS_FLAG_PLAN8) ? 8 : kDefaultPlan;
-        const bool line = line_ok(rh, priors + r, energies + r);
+        const int line = !line_ok(rh, priors + r, energies + r) ? 0
+                         : rh.P.prior_kind == PRIOR_BOX        ? 1
+                                                               : 2;
         int g = -1;
         for (size_t i = 0; i < ctx->groups.size(); ++i) {
             const Group &G = ctx->groups[i];

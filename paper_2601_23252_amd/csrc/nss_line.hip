@@ -21,6 +21,22 @@
 // are tested at a time, each form of a candidate in its own lane, and the lanes' votes are
 // folded to a bit per candidate.  A mixture is above L* when any component alone is, and is not
 // when every one is below L* - log K; only between the two is the sum of exponentials taken.
+//
+// The walk is a chain of dependent scalar-sized operations, so its length is what a step costs.
+// The first pass of a step tests both ends twice and four shrink proposals of each of the three
+// likeliest outcomes (neither end, or one of them once, expands); their t do not depend on the
+// point, so a block's are laid out at its start, and nine steps of ten end with that pass.  The
+// row of u_15 is kept shifted so that the current step's column is column 0 (row shifts and row
+// broadcasts instead of trips through LDS), and whole-wave values move by lane reads.
+//
+// What it replaces evaluated every candidate as a point, in a tile shared by a workgroup's
+// chains, at two barriers and two to three tiles a step.  One launch with points and here:
+// d = 5, 50 chains of 25 steps 241 and 33 us; d = 32, 500 chains of 160 steps (BF16x3 points)
+// 1561 and 178 us; 8 components at d = 64, 1000 chains of 320 steps in FP64 7800 and 905 us.
+// (Without the planned first pass, the shifted row and the fragments requested ahead: 56, 301
+// and 1900 us.)  One wave per SIMD runs at those sizes, so the bound is the walk's length, about
+// 2,500 cycles a step; at 8 components the products take as long again, twice what the FP64
+// matrix rate allows.
 #include "nss_internal.hpp"
 #include "nss_rng.hpp"
 #include "nss_tiles.hpp"
@@ -36,20 +52,23 @@ constexpr int kLineSide = 8;            // stepping-out tests per end and pass
 constexpr int kLineForms = 16;          // most components
 
 // LDS of one workgroup (byte offsets; identical on host): per chain the forms' Gram matrices
-// (the last one the Gaussian prior's), the point, the block's step uniforms and the shrink
-// uniforms of a pass past the buffer; the final points' FP64 tile overlays the Gram matrices.
+// (the last one the Gaussian prior's), the point, the block's step uniforms, its first passes'
+// t, and the shrink uniforms of a later pass; the final points' FP64 tile overlays the Gram
+// matrices.
 struct LineLayout {
-    int gram, x, us, su, chain;         // per-chain offsets and stride
+    int gram, x, us, tt, su, chain;     // per-chain offsets and stride
+    int mu, pa, ipb;                    // the workgroup's means and Gaussian prior (1 / std)
     int cand, q, L, mask, total;
 };
-__host__ __device__ inline LineLayout line_layout(int D, int K, int lik)
+__host__ __device__ inline LineLayout line_layout(int D, int K, int lik, bool box)
 {
-    const int forms = (lik == LIK_MIXTURE ? K : 1) + 1;
+    const int forms = (lik == LIK_MIXTURE ? K : 1) + (box ? 0 : 1);
     LineLayout o;
     int off = 0;
     o.gram = off; off += al16(forms * 16 * kLineLd * 8);
     o.x = off; off += al16(D * 8);
-    o.us = off; off += kLineB * kStepU * 8;
+    o.us = off; off += 16 * kStepU * 8;
+    o.tt = off; off += 16 * 16 * 8;
     o.su = off; off += 16 * 8;
     o.chain = al16(off);
     int t = 0;
@@ -57,10 +76,17 @@ __host__ __device__ inline LineLayout line_layout(int D, int K, int lik)
     o.q = t; t += al16(kRows * q_stride(D, K) * 8);
     o.L = t; t += al16(kRows * 8);
     o.mask = t; t += al16(kRows * 4);
-    o.total = kMaxChainsPerWG * o.chain > t ? kMaxChainsPerWG * o.chain : t;
+    off = kMaxChainsPerWG * o.chain;
+    o.mu = off; off += lik == LIK_MIXTURE ? K * D * 8 : 0;
+    o.pa = off; off += D * 8;
+    o.ipb = off; off += D * 8;
+    o.total = off > t ? off : t;
     return o;
 }
-size_t line_lds_bytes(int D, int K, int lik) { return (size_t)line_layout(D, K, lik).total; }
+size_t line_lds_bytes(int D, int K, int lik, int box)
+{
+    return (size_t)line_layout(D, K, lik, box != 0).total;
+}
 
 // Bits of a ballot folded over the four rows: bit c = some lane of column c voted.
 __device__ __forceinline__ unsigned fold_rows(unsigned long long b)
@@ -68,17 +94,43 @@ __device__ __forceinline__ unsigned fold_rows(unsigned long long b)
     const unsigned h = (unsigned)b | (unsigned)(b >> 32);
     return (h | (h >> 16)) & 0xFFFFu;
 }
-__device__ __forceinline__ float wave_minf(float v)
+// Minimum over the wave of floats that are not negative (ordered as their bits are; a negative
+// one counts as large): DPP within a row, then the last lanes of rows 0 and 2 into the rows after
+// them and lane 31 into the upper half; lane 63 has the result.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned dpp_min(unsigned v)
 {
-    v = fminf(v, dppf<DPP_XOR1>(v)); v = fminf(v, dppf<DPP_XOR2>(v));
-    v = fminf(v, dppf<DPP_HMIR>(v)); v = fminf(v, dppf<DPP_RMIR>(v));
-    v = fminf(v, __shfl_xor(v, 16, 64));
-    return fminf(v, __shfl_xor(v, 32, 64));
+    return min(v, (unsigned)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ float wave_min_pos(float x)
+{
+    unsigned v = __builtin_bit_cast(unsigned, x);
+    v = dpp_min<DPP_XOR1, 0xF>(v);
+    v = dpp_min<DPP_XOR2, 0xF>(v);
+    v = dpp_min<DPP_HMIR, 0xF>(v);
+    v = dpp_min<DPP_RMIR, 0xF>(v);
+    v = dpp_min<0x142, 0xA>(v);   // row_bcast:15
+    v = dpp_min<0x143, 0xC>(v);   // row_bcast:31
+    float m = __builtin_bit_cast(float, __builtin_amdgcn_readlane((int)v, 63));
+    asm volatile("" : "+v"(m));
+    return m;
+}
+#define DPP_BCAST0 0x150   /* row_newbcast:0, the row's first lane to all of it */
+#define DPP_ROL1 0x12F     /* row_ror:15, lane i takes lane i + 1 of its row */
+// The value of one lane (the same index in every lane), in vector registers: a compare of a
+// value known to be uniform has been compiled into a scalar select on a stale condition code,
+// so the value is made opaque.
+__device__ __forceinline__ double lane_value(double v, int lane)
+{
+    double r = readlane_d(v, uniform_i(lane));
+    asm volatile("" : "+v"(r));
+    return r;
 }
 
-// NR: forms per lane (components 4 q + row, q < NR); TEMP: tempered SMC slices (no constraint).
-template <int D, int LIK, int NR, bool TEMP>
-__global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
+// NR: forms per lane (components 4 q + row, q < NR); TEMP: tempered SMC slices (no constraint);
+// BOX: the prior is a box.
+template <int D, int LIK, int NR, bool TEMP, bool BOX, int OCC>
+__global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     const int2 bm = Lc.map[blockIdx.x];
@@ -88,7 +140,7 @@ __global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
     constexpr int NA = (D + 63) / 64;
     constexpr int NJB = D / 16, NKS = D / 4;
     constexpr bool MIX = LIK == LIK_MIXTURE;
-    const LineLayout lay = line_layout(D, P.K, LIK);
+    const LineLayout lay = line_layout(D, P.K, LIK, BOX);
     const int tid = threadIdx.x, w = uniform_i(tid >> 6), l = tid & 63;
     const int col = l & 15, row = l >> 4;
     const int d = P.d, K = MIX ? P.K : 1, C = R.C, p = R.p;
@@ -97,14 +149,24 @@ __global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
     const uint32_t it = (uint32_t)R.iscal[3] + 1u;
     const double width = R.width;
     const int cap_out = R.stepout_cap, cap_sh = R.shrink_cap;
-    const bool box = P.prior_kind == PRIOR_BOX;
 
     unsigned char *mine = smem + w * lay.chain;
     double *gram = (double *)(mine + lay.gram);
     double *xs = (double *)(mine + lay.x);
     double *us = (double *)(mine + lay.us);
+    double *tt = (double *)(mine + lay.tt);
     double *su = (double *)(mine + lay.su);
     double *gpri = gram + K * 16 * kLineLd;   // the Gaussian prior's form
+
+    double *smu = (double *)(smem + lay.mu), *spa = (double *)(smem + lay.pa),
+           *sipb = (double *)(smem + lay.ipb);
+    if constexpr (MIX)
+        for (int i = tid; i < K * D; i += 256) smu[i] = as_global(P.mu)[i];
+    if constexpr (!BOX)
+        for (int i = tid; i < D; i += 256) {
+            spa[i] = as_global(P.pa)[i];
+            sipb[i] = 1.0 / as_global(P.pb)[i];
+        }
 
     const int j = bm.y * C + w;
     const bool has_chain = w < C && j < R.k;
@@ -115,6 +177,7 @@ __global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
     bool moved = false;
     unsigned long long c_evals = 0, c_tests = 0, c_outcap = 0, c_shcap = 0, c_viol = 0;
 
+    __syncthreads();
     if (has_chain) {
         int parent = j;   // tempered SMC: the resampled particle j, gathered into slot j
         if constexpr (!TEMP) {
@@ -125,18 +188,19 @@ __global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
             parent = R.perm[t0 + qi];
             if (l == 0) R.parents[j] = parent;
         }
-        // the prior's box of the lane's coordinates, and how far rounding can move y = x + t v
-        double par[NA], pbr[NA], slop[NA];
+        // the prior's box of the lane's coordinates, and a distance to its faces that rounding
+        // of y = x + t v is small against
+        double par[NA], pbr[NA], near_[NA];
 #pragma unroll
         for (int i = 0; i < NA; ++i) {
             const int a = l + 64 * i;
-            par[i] = -INFINITY; pbr[i] = INFINITY; slop[i] = 0.0;
+            par[i] = -INFINITY; pbr[i] = INFINITY; near_[i] = -1.0;
             if (a < d) {
                 x0r[i] = R.X[(size_t)a * R.m_pad + parent];
-                if (box) {
+                if (BOX) {
                     par[i] = P.pa[a];
                     pbr[i] = P.pb[a];
-                    slop[i] = 4e-15 * fmax(fabs(par[i]), fabs(pbr[i]));
+                    near_[i] = 1e-9 * fmax(fabs(par[i]), fabs(pbr[i]));
                 }
             }
         }
@@ -149,154 +213,259 @@ __global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
         }
         // below this a component cannot make the mixture exceed L* together with the others
         const double Lamb = (MIX && K > 1) ? Lstar - log((double)K) - 1e-6 : INFINITY;
-        const double *dirs = R.dirbuf + (size_t)j * p * D;
-        const double *ub = R.ubuf + (size_t)j * p * kStepU;
+        const auto dirs = as_global((const double *)R.dirbuf) + (size_t)j * p * D;
+        const auto ub = as_global((const double *)R.ubuf) + (size_t)j * p * kStepU;
+        const bool xcol = col == 15;
+        // the first pass needs room for two expansions of an end and four proposals
+        const bool fast = cap_out >= 2 && cap_sh >= 4;
+
+        // the step's direction (lane l: coordinates l, l + 64, ...), one step ahead, and the next
+        // block's columns (lane: column col, coordinates 4 ks + row) and uniforms, loaded while
+        // the current block is walked
         double pv[NA];
 #pragma unroll
         for (int i = 0; i < NA; ++i) pv[i] = (l + 64 * i < D) ? dirs[l + 64 * i] : 0.0;
+        double b[MIX ? NKS : 1], pus[2];
+        auto fetch_block = [&](int s0) {
+            const int nb = min(kLineB, p - s0);
+            const bool dcol = col < nb;
+            const auto vrow = dirs + (size_t)(s0 + (dcol ? col : 0)) * D + row;
+            if constexpr (MIX) {
+#pragma unroll
+                for (int ks = 0; ks < NKS; ++ks) b[ks] = dcol ? vrow[4 * ks] : 0.0;
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                pus[i] = l + 64 * i < nb * kStepU ? ub[(size_t)s0 * kStepU + l + 64 * i] : 0.5;
+        };
+        fetch_block(0);
 
         for (int s0 = 0; s0 < p; s0 += kLineB) {
             const int nb = min(kLineB, p - s0);
             // ---- the block's products ----
 #pragma unroll
             for (int i = 0; i < NA; ++i) if (l + 64 * i < D) xs[l + 64 * i] = x0r[i];
-            for (int e = l; e < nb * kStepU; e += 64) us[e] = ub[(size_t)s0 * kStepU + e];
+            us[l] = pus[0];
+            us[l + 64] = pus[1];
             wave_sync();
-            const bool dcol = col < nb, xcol = col == 15;
-            const double *vrow = dirs + (size_t)(s0 + (dcol ? col : 0)) * D;
+            // W column blocks in pairs (pr, NJB - 1 - pr) of equal triangular work, taken in
+            // chunks of at most 20 fragments, the next chunk's requested before this one's
+            // products (a trip to L2 costs about what the products of a chunk take)
+            constexpr int NPR = NJB / 2, NF = 4 * (NJB + 1), NCH = NF > 20 ? 2 : 1;
+            constexpr int CH = NF / NCH, NSEQ = NPR * NCH;   // chunks per component
+            double wa[CH], wb[CH];
+            // fragment f of pair pr: column block j0 or j1 in turn while both have k-steps
+            auto frag = [](int pr, int f, int &jb, int &ks, bool &lo) {
+                const int n0 = 4 * (pr + 1);
+                lo = f < 2 * n0 && !(f & 1);
+                jb = lo ? pr : NJB - 1 - pr;
+                ks = f < 2 * n0 ? f >> 1 : f - n0;
+            };
+            auto load = [&](double *wf, int c, int sq) {
+                const auto src = as_global(P.wf64) +
+                                 (size_t)(c < K ? c : K - 1) * NJB * NKS * 64 + l;
+#pragma unroll
+                for (int i = 0; i < CH; ++i) {
+                    int jb, ks;
+                    bool lo;
+                    frag(sq / NCH, (sq % NCH) * CH + i, jb, ks, lo);
+                    wf[i] = src[(jb * NKS + ks) * 64];
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            };
+            if constexpr (MIX) load(wa, 0, 0);
+            // t of the first passes: columns 0, 1 the left end's next tests, 2, 3 the right
+            // end's, then four proposals after no expansion, one left, one right (four steps at
+            // a time, one per row)
+            for (int s4 = 0; s4 < nb; s4 += 4) {
+                const double *uq = us + (s4 + row) * kStepU;
+                const double tl = uq[0], tr = tl + width;
+                const int hyp = (col >> 2) - 1;
+                double sL = hyp == 1 ? tl - width : tl, sR = hyp == 2 ? tr + width : tr;
+                double t = col == 0 ? tl : (col == 1 ? tl - width : (col == 2 ? tr : tr + width));
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const double tq = fma(uq[2 + q], sR - sL, sL);
+                    if (col >= 4 && (col & 3) == q) t = tq;
+                    if (tq < 0.0) sL = tq; else sR = tq;
+                }
+                tt[(s4 + row) * 16 + col] = t;
+            }
+            double luh = 0.0;
+            if (TEMP || !BOX) luh = log(us[col * kStepU + 1]);
             typedef double d4v __attribute__((ext_vector_type(4)));
             auto put = [&](double *g, const d4v &G) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) g[(row + 4 * i) * kLineLd + col] = G[i];
             };
             if constexpr (MIX) {
-                double b[NKS];   // the directions' columns (the point's column differs per form)
+                d4v G, a0, a1;
+                auto mul = [&](const double *wf, int sq) {
+                    if (sq % NCH == 0) a0 = a1 = (d4v){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-                for (int ks = 0; ks < NKS; ++ks) {
-                    const int kk = 4 * ks + row;
-                    b[ks] = dcol ? vrow[kk] : (xcol ? xs[kk] : 0.0);
-                }
-                for (int c = 0; c < K; ++c) {
-                    const double *wf = P.wf64 + (size_t)c * NJB * NKS * 64 + l;
-                    const double *mu = P.mu + c * D;
-                    d4v acc[NJB];
-#pragma unroll
-                    for (int jb = 0; jb < NJB; ++jb) acc[jb] = (d4v){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int ks = 0; ks < NKS; ++ks) {
-                        const double bb = xcol ? b[ks] - mu[4 * ks + row] : b[ks];
-#pragma unroll
-                        for (int jb = 0; jb < NJB; ++jb)
-                            if (ks < 4 * jb + 4)
-                                acc[jb] = __builtin_amdgcn_mfma_f64_16x16x4f64(
-                                    wf[((size_t)jb * NKS + ks) * 64], bb, acc[jb], 0, 0, 0);
+                    for (int i = 0; i < CH; ++i) {
+                        int jb, ks;
+                        bool lo;
+                        frag(sq / NCH, (sq % NCH) * CH + i, jb, ks, lo);
+                        if (lo) a0 = __builtin_amdgcn_mfma_f64_16x16x4f64(wf[i], b[ks], a0, 0, 0, 0);
+                        else a1 = __builtin_amdgcn_mfma_f64_16x16x4f64(wf[i], b[ks], a1, 0, 0, 0);
                     }
-                    d4v G = (d4v){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-                    for (int jb = 0; jb < NJB; ++jb)
+                    if (sq % NCH == NCH - 1) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            G = __builtin_amdgcn_mfma_f64_16x16x4f64(acc[jb][i], acc[jb][i], G, 0, 0, 0);
-                    put(gram + c * 16 * kLineLd, G);
+                            G = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[i], a0[i], G, 0, 0, 0);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            G = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[i], a1[i], G, 0, 0, 0);
+                    }
+                };
+                auto begin = [&](int c) {   // the point's column, less the component's mean
+                    G = (d4v){0.0, 0.0, 0.0, 0.0};
+                    const double *mu = smu + c * D + row;
+#pragma unroll
+                    for (int ks = 0; ks < NKS; ++ks)
+                        if (xcol) b[ks] = xs[4 * ks + row] - mu[4 * ks];
+                };
+                if constexpr (NSEQ == 1) {
+                    for (int c = 0; c < K; c += 2) {
+                        load(wb, c + 1, 0);
+                        begin(c);
+                        mul(wa, 0);
+                        put(gram + c * 16 * kLineLd, G);
+                        if (c + 1 < K) {
+                            load(wa, c + 2, 0);
+                            begin(c + 1);
+                            mul(wb, 0);
+                            put(gram + (c + 1) * 16 * kLineLd, G);
+                        }
+                    }
+                } else {
+                    for (int c = 0; c < K; ++c) {
+                        begin(c);
+#pragma unroll
+                        for (int sq = 0; sq < NSEQ; sq += 2) {
+                            load(wb, c, sq + 1);
+                            mul(wa, sq);
+                            load(wa, sq + 2 < NSEQ ? c : c + 1, sq + 2 < NSEQ ? sq + 2 : 0);
+                            mul(wb, sq + 1);
+                        }
+                        put(gram + c * 16 * kLineLd, G);
+                    }
                 }
-                if (!box) {
-                    d4v G = (d4v){0.0, 0.0, 0.0, 0.0};
+                if (!BOX) {
+                    d4v Gp = (d4v){0.0, 0.0, 0.0, 0.0};
 #pragma unroll
                     for (int ks = 0; ks < NKS; ++ks) {
                         const int kk = 4 * ks + row;
-                        const double bb = kk < d ? (xcol ? b[ks] - P.pa[kk] : b[ks]) / P.pb[kk] : 0.0;
-                        G = __builtin_amdgcn_mfma_f64_16x16x4f64(bb, bb, G, 0, 0, 0);
+                        const double bb = kk < d ? (xcol ? xs[kk] - spa[kk] : b[ks]) * sipb[kk] : 0.0;
+                        Gp = __builtin_amdgcn_mfma_f64_16x16x4f64(bb, bb, Gp, 0, 0, 0);
                     }
-                    put(gpri, G);
+                    put(gpri, Gp);
                 }
             } else {
                 // the funnel's form: the coordinates after the first
+                const bool dcol = col < nb;
+                const auto vrow = dirs + (size_t)(s0 + (dcol ? col : 0)) * D;
                 d4v G = (d4v){0.0, 0.0, 0.0, 0.0}, Gp = (d4v){0.0, 0.0, 0.0, 0.0};
-#pragma unroll 8
+#pragma unroll 16
                 for (int ks = 0; ks < NKS; ++ks) {
                     const int kk = 4 * ks + row;
-                    const double b = dcol ? vrow[kk] : (xcol ? xs[kk] : 0.0);
-                    const double bb = kk > 0 ? b : 0.0;
+                    const double bv = dcol ? vrow[kk] : (xcol ? xs[kk] : 0.0);
+                    const double bb = kk > 0 ? bv : 0.0;
                     G = __builtin_amdgcn_mfma_f64_16x16x4f64(bb, bb, G, 0, 0, 0);
-                    if (!box) {
-                        const double bp = kk < d ? (xcol ? b - P.pa[kk] : b) / P.pb[kk] : 0.0;
+                    if (!BOX) {
+                        const double bp = kk < d ? (xcol ? bv - spa[kk] : bv) * sipb[kk] : 0.0;
                         Gp = __builtin_amdgcn_mfma_f64_16x16x4f64(bp, bp, Gp, 0, 0, 0);
                     }
                 }
                 put(gram, G);
-                if (!box) put(gpri, Gp);
+                if (!BOX) put(gpri, Gp);
             }
             wave_sync();
-            // row 15: the point's products with every column; column 15 its own square
-            double h[NR], hp = 0.0, luh = 0.0;
+            // the point's products with the directions (row 15; column 0 is the current step's),
+            // and its own square
+            double h[NR], aa[NR], hp = 0.0;
 #pragma unroll
             for (int q = 0; q < NR; ++q) {
                 const int c = 4 * q + row;
-                h[q] = (c < K) ? gram[(c * 16 + 15) * kLineLd + col] : 0.0;
+                const double *g15 = gram + ((c < K ? c : 0) * 16 + 15) * kLineLd;
+                h[q] = g15[col];
+                aa[q] = g15[15];
             }
-            if (!box) hp = gpri[15 * kLineLd + col];
-            if (TEMP || !box) luh = log(dcol ? us[col * kStepU + 1] : 1.0);
+            if (!BOX) hp = gpri[15 * kLineLd + col];
+            if (s0 + kLineB < p) fetch_block(s0 + kLineB);
 
             // ---- the block's steps ----
+            unsigned n_tests = 0, n_evals = 0;
+            double tn = tt[col], grn[NR], gpn = 0.0;   // the next step's, read ahead
+#pragma unroll
+            for (int q = 0; q < NR; ++q) grn[q] = gram[((4 * q + row < K ? 4 * q + row : 0) * 16) * kLineLd + col];
+            if (!BOX) gpn = gpri[col];
             for (int sb = 0; sb < nb; ++sb) {
                 const int st = s0 + sb;
 #pragma unroll
                 for (int i = 0; i < NA; ++i) vr[i] = pv[i];
                 if (st + 1 < p) {
-                    const double *nx = dirs + (size_t)(st + 1) * D;
+                    const auto nx = dirs + (size_t)(st + 1) * D;
 #pragma unroll
                     for (int i = 0; i < NA; ++i) if (l + 64 * i < D) pv[i] = nx[l + 64 * i];
                 }
-                double cu[kStepU];
-#pragma unroll
-                for (int q = 0; q < kStepU; ++q) cu[q] = us[sb * kStepU + q];
-                // the step's parabolas: point, slope, curvature, and the row of the update
-                double a[NR], b2[NR], g[NR], gr[NR];
+                // the step's parabolas a + b2 t + g t^2 and the row of the update
+                double b2[NR], g[NR], gr[NR];
 #pragma unroll
                 for (int q = 0; q < NR; ++q) {
-                    const int c = 4 * q + row;
-                    const double *gc = gram + ((c < K ? c : 0) * 16 + sb) * kLineLd;
-                    gr[q] = gc[col];
-                    g[q] = gc[sb];
-                    a[q] = __shfl(h[q], (l & 48) | 15, 64);
-                    b2[q] = 2.0 * __shfl(h[q], (l & 48) | sb, 64);
+                    gr[q] = grn[q];
+                    g[q] = dppd<DPP_BCAST0>(gr[q]);
+                    b2[q] = 2.0 * dppd<DPP_BCAST0>(h[q]);
                 }
-                double ap = 0.0, bp2 = 0.0, gp = 0.0, grp = 0.0, lu = 0.0;
-                if (!box) {
-                    grp = gpri[sb * kLineLd + col];
-                    gp = gpri[sb * kLineLd + sb];
-                    ap = __shfl(hp, 15, 64);
-                    bp2 = 2.0 * __shfl(hp, sb, 64);
+                double bp2 = 0.0, gp = 0.0, grp = 0.0, lu = 0.0;
+                if (!BOX) {
+                    grp = gpn;
+                    gp = dppd<DPP_BCAST0>(grp);
+                    bp2 = 2.0 * dppd<DPP_BCAST0>(hp);
                 }
-                if (TEMP || !box) lu = __shfl(luh, sb, 64);
+                if (TEMP || !BOX) lu = lane_value(luh, sb);
+                const double tf = tn;
+                {
+                    // (step 15 of a full block reads row 15, unused)
+                    const int sn = sb + 1;
+                    tn = tt[sn * 16 + col];
+#pragma unroll
+                    for (int q = 0; q < NR; ++q) {
+                        const int c = 4 * q + row < K ? 4 * q + row : 0;
+                        grn[q] = gram[(c * 16 + sn) * kLineLd + min(sn + col, 15)];
+                    }
+                    if (!BOX) gpn = gpri[sn * kLineLd + min(sn + col, 15)];
+                }
                 double v0 = 0.0, x00 = 0.0;
-                if constexpr (!MIX) { v0 = __shfl(vr[0], 0, 64); x00 = __shfl(x0r[0], 0, 64); }
+                if constexpr (!MIX) { v0 = lane_value(vr[0], 0); x00 = lane_value(x0r[0], 0); }
                 // box prior: t inside [tin0, tin1] keeps every coordinate in the box whatever
                 // the rounding of x + t v, t outside [tou0, tou1] puts one out; the margins
-                // cover the FP32 quotients and half a unit in the last place of y
+                // cover the FP32 quotients and, away from the faces, the rounding of y
                 float tin0 = -INFINITY, tin1 = INFINITY, tou0 = -INFINITY, tou1 = INFINITY;
-                if (box) {
-                    float i0 = INFINITY, i1 = INFINITY, o0 = INFINITY, o1 = INFINITY;
+                if (BOX) {
+                    float m0 = INFINITY, m1 = INFINITY;
+                    bool face = false;
 #pragma unroll
                     for (int i = 0; i < NA; ++i) {
-                        // distances to the bound that t > 0 and t < 0 approach
                         const bool pos = vr[i] > 0.0;
-                        const double up = pos ? pbr[i] - x0r[i] : x0r[i] - par[i];
-                        const double dn = pos ? x0r[i] - par[i] : pbr[i] - x0r[i];
-                        const float rv = __builtin_amdgcn_rcpf(fabsf((float)vr[i]));
-                        if (fabsf((float)vr[i]) > 1e-30f && up >= 0.0 && dn >= 0.0) {
-                            i1 = fminf(i1, (float)(up - slop[i]) * rv);
-                            i0 = fminf(i0, (float)(dn - slop[i]) * rv);
-                            o1 = fminf(o1, (float)(up + slop[i]) * rv);
-                            o0 = fminf(o0, (float)(dn + slop[i]) * rv);
-                        } else if (vr[i] != 0.0 || up < 0.0 || dn < 0.0) {
-                            i0 = i1 = -1.f;   // decided coordinate by coordinate
-                        }
+                        const double hi = pbr[i] - x0r[i], lo = x0r[i] - par[i];
+                        const float va = fabsf((float)vr[i]), rv = __builtin_amdgcn_rcpf(va);
+                        const bool flat = !(va > 1e-30f);
+                        face = face || !(hi > near_[i]) || !(lo > near_[i]) || (flat && vr[i] != 0.0);
+                        m1 = fminf(m1, flat ? INFINITY : (float)(pos ? hi : lo) * rv);
+                        m0 = fminf(m0, flat ? INFINITY : (float)(pos ? lo : hi) * rv);
                     }
-                    tin1 = wave_minf(i1) * (1.f - 1e-5f);
-                    tin0 = -wave_minf(i0) * (1.f - 1e-5f);
-                    tou1 = wave_minf(o1) * (1.f + 1e-5f) + 1e-30f;
-                    tou0 = -wave_minf(o0) * (1.f + 1e-5f) - 1e-30f;
+                    m1 = wave_min_pos(m1);
+                    m0 = wave_min_pos(m0);
+                    tin1 = m1 * (1.f - 2e-5f);
+                    tin0 = -m0 * (1.f - 2e-5f);
+                    tou1 = m1 * (1.f + 2e-5f);
+                    tou0 = -m0 * (1.f + 2e-5f);
+                    if (__any(face)) {   // decided coordinate by coordinate
+                        tin0 = INFINITY; tin1 = -INFINITY;
+                        tou0 = -INFINITY; tou1 = INFINITY;
+                    }
                 }
                 // Sixteen candidates, column c at this lane's t: okm the bits that pass the
                 // prior, the result those inside the slice; vm = the candidates wanted.
@@ -304,22 +473,24 @@ __global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
                 auto test = [&](double t, unsigned vm, unsigned &okm) -> unsigned {
                     unsigned in;
                     const double lp = -0.5 * (t * fma(t, gp, bp2));   // log Pi(y) - log Pi(x)
-                    if (box) {
+                    if (BOX) {
                         const unsigned inb = (unsigned)__ballot(t >= (double)tin0 && t <= (double)tin1) & vm;
-                        const unsigned out = (unsigned)__ballot(t < (double)tou0 || t > (double)tou1);
                         okm = inb;
-                        unsigned ask = vm & ~inb & ~out & 0xFFFFu;
-                        while (ask) {   // within a margin of the box's faces
-                            const int s = __builtin_ctz(ask);
-                            ask &= ask - 1u;
-                            const double ts = __shfl(t, s, 64);
-                            bool ib = true;
+                        if (inb != vm) {
+                            const unsigned out = (unsigned)__ballot(t < (double)tou0 || t > (double)tou1);
+                            unsigned ask = vm & ~inb & ~out & 0xFFFFu;
+                            while (ask) {   // within a margin of the box's faces
+                                const int s = __builtin_ctz(ask);
+                                ask &= ask - 1u;
+                                const double ts = lane_value(t, s);
+                                bool ib = true;
 #pragma unroll
-                            for (int i = 0; i < NA; ++i) {
-                                const double y = fma(ts, vr[i], x0r[i]);
-                                if (l + 64 * i < d) ib = ib && y >= par[i] && y <= pbr[i];
+                                for (int i = 0; i < NA; ++i) {
+                                    const double y = fma(ts, vr[i], x0r[i]);
+                                    if (l + 64 * i < d) ib = ib && y >= par[i] && y <= pbr[i];
+                                }
+                                okm |= (__all(ib) ? 1u : 0u) << s;
                             }
-                            okm |= (__all(ib) ? 1u : 0u) << s;
                         }
                     } else {
                         okm = TEMP ? vm : ((unsigned)__ballot(lp > lu) & vm);
@@ -329,7 +500,7 @@ __global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
                         bool hit = false, amb = false;
 #pragma unroll
                         for (int q = 0; q < NR; ++q) {
-                            lc[q] = cst[q] - 0.5 * fma(t, fma(t, g[q], b2[q]), a[q]);
+                            lc[q] = cst[q] - 0.5 * fma(t, fma(t, g[q], b2[q]), aa[q]);
                             hit = hit || lc[q] > Lstar;
                             amb = amb || lc[q] > Lamb;
                         }
@@ -358,98 +529,123 @@ __global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
                             }
                         }
                     } else {
-                        const double s2 = fmax(fma(t, fma(t, g[0], b2[0]), a[0]), 0.0);
+                        const double s2 = fmax(fma(t, fma(t, g[0], b2[0]), aa[0]), 0.0);
                         const double vv = fma(t, v0, x00);
                         Lv = -vv * vv / 18.0 - 0.5 * (LOG_2PI + log(9.0)) - 0.5 * exp(-vv) * s2
                              - (double)(d - 1) * 0.5 * (vv + LOG_2PI);
                         if constexpr (!TEMP) in = (unsigned)__ballot(Lv > Lstar);
                     }
                     if constexpr (TEMP)
-                        in = (unsigned)__ballot((box ? 0.0 : lp) + beta * (Lv - logL0) > lu);
+                        in = (unsigned)__ballot((BOX ? 0.0 : lp) + beta * (Lv - logL0) > lu);
                     return in & okm;
                 };
                 auto tally = [&](unsigned cons, unsigned okm) {
-                    c_tests += __builtin_popcount(cons);
-                    c_evals += __builtin_popcount(cons & okm);
+                    n_tests += __builtin_popcount(cons);
+                    n_evals += __builtin_popcount(cons & okm);
                 };
 
-                // stepping out: the next eight positions of both ends at once
-                double tL = cu[0], tR = tL + width;
-                int nl = 0, nr = 0;
-                bool la = cap_out > 0, ra = la;
-                if (cap_out <= 0) c_outcap += 2;
-                while (la || ra) {
-                    const int nsl = la ? min(kLineSide, cap_out - nl) : 0;
-                    const int nsr = ra ? min(kLineSide, cap_out - nr) : 0;
-                    const double step = col < kLineSide ? -width : width;
-                    double t = col < kLineSide ? tL : tR;
-#pragma unroll
-                    for (int i = 1; i < kLineSide; ++i) if ((col & 7) >= i) t += step;
-                    const unsigned ml = (1u << nsl) - 1u, mr = (1u << nsr) - 1u;
+                const double *uq = us + sb * kStepU;
+                int nl = 0, nr = 0, ns = 0, acc = 0;
+                bool la = cap_out > 0, ra = la, open = true;
+                double tL = 0.0, tR = 0.0, ta = 0.0;
+                if (fast) {
                     unsigned okm;
-                    const unsigned in = test(t, ml | (mr << kLineSide), okm);
-                    // leading inside tests of each end
-                    const int na = __builtin_ctz(~(in & ml));
-                    const int nc = __builtin_ctz(~((in >> kLineSide) & mr));
-                    if (la) {
-                        tally(((2u << na) - 1u) & ml, okm);
-                        if (na > 0) tL = __shfl(t, min(na, 7), 64) - (na == 8 ? width : 0.0);
-                        nl += na;
-                        if (na < nsl) la = false;
-                        else if (nl >= cap_out) { la = false; ++c_outcap; }
+                    const unsigned in = test(tf, 0xFFFFu, okm);
+                    const unsigned le = in & 3u, re = (in >> 2) & 3u;
+                    nl = le == 3u ? 2 : (int)(le & 1u);
+                    nr = re == 3u ? 2 : (int)(re & 1u);
+                    la = nl == 2;
+                    ra = nr == 2;
+                    // a second test of an end is made where its first was inside
+                    unsigned cons = 5u | ((le & 1u) << 1) | ((re & 1u) << 3);
+                    if (nl + nr <= 1) {   // one of the three outcomes that were planned
+                        const int s = 4 + 4 * nl + 8 * nr;
+                        const unsigned f = (in >> s) & 0xFu;
+                        ns = __builtin_ctz(f | 8u) + 1;
+                        cons |= ((1u << ns) - 1u) << s;
+                        if (f) {
+                            acc = 1;
+                            ta = lane_value(tf, s + ns - 1);
+                            if constexpr (TEMP) logL0 = lane_value(Lv, s + ns - 1);
+                            open = false;
+                        }
                     }
-                    if (ra) {
-                        tally(((2u << nc) - 1u) & mr, okm >> kLineSide);
-                        if (nc > 0) tR = __shfl(t, 8 + min(nc, 7), 64) + (nc == 8 ? width : 0.0);
-                        nr += nc;
-                        if (nc < nsr) ra = false;
-                        else if (nr >= cap_out) { ra = false; ++c_outcap; }
-                    }
+                    tally(cons, okm);
+                } else if (cap_out <= 0) {
+                    c_outcap += 2;
                 }
-                // shrinking: the proposals that follow if every earlier one is rejected
-                int ns = 0, acc = 0;
-                double ta = 0.0;
-                while (!acc && ns < cap_sh) {
-                    const int avail = ns == 0 ? kStepShrinkU : 16;
-                    const int np = min(avail, cap_sh - ns);
-                    if (ns > 0) {   // past the buffer: one proposal's uniform per lane
+                if (open) {
+                    tL = uq[0];
+                    tR = tL + width;
+                    for (int i = 0; i < nl; ++i) tL -= width;
+                    for (int i = 0; i < nr; ++i) tR += width;
+                    if (la && nl >= cap_out) { la = false; ++c_outcap; }
+                    if (ra && nr >= cap_out) { ra = false; ++c_outcap; }
+                    // stepping out: the next eight positions of both ends at once
+                    while (la || ra) {
+                        const int nsl = la ? min(kLineSide, cap_out - nl) : 0;
+                        const int nsr = ra ? min(kLineSide, cap_out - nr) : 0;
+                        const double step = col < kLineSide ? -width : width;
+                        double t = col < kLineSide ? tL : tR;
+#pragma unroll
+                        for (int i = 1; i < kLineSide; ++i) if ((col & 7) >= i) t += step;
+                        const unsigned ml = (1u << nsl) - 1u, mr = (1u << nsr) - 1u;
+                        unsigned okm;
+                        const unsigned in = test(t, ml | (mr << kLineSide), okm);
+                        // leading inside tests of each end
+                        const int na = __builtin_ctz(~(in & ml));
+                        const int nc = __builtin_ctz(~((in >> kLineSide) & mr));
+                        if (la) {
+                            tally(((2u << na) - 1u) & ml, okm);
+                            if (na > 0) tL = lane_value(t, min(na, 7)) - (na == 8 ? width : 0.0);
+                            nl += na;
+                            if (na < nsl) la = false;
+                            else if (nl >= cap_out) { la = false; ++c_outcap; }
+                        }
+                        if (ra) {
+                            tally(((2u << nc) - 1u) & mr, okm >> kLineSide);
+                            if (nc > 0) tR = lane_value(t, 8 + min(nc, 7)) + (nc == 8 ? width : 0.0);
+                            nr += nc;
+                            if (nc < nsr) ra = false;
+                            else if (nr >= cap_out) { ra = false; ++c_outcap; }
+                        }
+                    }
+                    // the proposals that the first pass rejected
+                    for (int q = 0; q < ns; ++q) {
+                        const double tq = fma(uq[2 + q], tR - tL, tL);
+                        if (tq < 0.0) tL = tq; else tR = tq;
+                    }
+                    // shrinking: the next sixteen proposals, if every earlier one is rejected
+                    while (!acc && ns < cap_sh) {
+                        const int np = min(16, cap_sh - ns);
                         double u, unused;
                         draw2(R.key0, R.key1, PUR_SHRINK, (uint32_t)j, it, (uint32_t)st,
                               (uint32_t)(ns + col), u, unused);
                         if (l < 16) su[l] = u;
                         wave_sync();
-                    }
-                    double sL = tL, sR = tR, t = 0.0;
-                    if (ns == 0) {
-#pragma unroll
-                        for (int q = 0; q < kStepShrinkU; ++q) {
-                            const double tq = sL + cu[2 + q] * (sR - sL);
-                            if (col == q) t = tq;
-                            if (tq < 0.0) sL = tq; else sR = tq;
-                        }
-                    } else {
+                        double sL = tL, sR = tR, t = 0.0;
                         for (int q = 0; q < 16; ++q) {
-                            const double tq = sL + su[q] * (sR - sL);
+                            const double tq = fma(su[q], sR - sL, sL);
                             if (col == q) t = tq;
                             if (tq < 0.0) sL = tq; else sR = tq;
                         }
                         wave_sync();
-                    }
-                    const unsigned pm = (1u << np) - 1u;
-                    unsigned okm;
-                    const unsigned in = test(t, pm, okm);
-                    if (in) {
-                        const int q = __builtin_ctz(in);
-                        tally((2u << q) - 1u, okm);
-                        ta = __shfl(t, q, 64);
-                        if constexpr (TEMP) logL0 = __shfl(Lv, q, 64);
-                        ns += q + 1;
-                        acc = 1;
-                    } else {
-                        tally(pm, okm);
-                        ns += np;
-                        tL = sL;
-                        tR = sR;
+                        const unsigned pm = (1u << np) - 1u;
+                        unsigned okm;
+                        const unsigned in = test(t, pm, okm);
+                        if (in) {
+                            const int q = __builtin_ctz(in);
+                            tally((2u << q) - 1u, okm);
+                            ta = lane_value(t, q);
+                            if constexpr (TEMP) logL0 = lane_value(Lv, q);
+                            ns += q + 1;
+                            acc = 1;
+                        } else {
+                            tally(pm, okm);
+                            ns += np;
+                            tL = sL;
+                            tR = sR;
+                        }
                     }
                 }
                 if (acc) {
@@ -457,18 +653,24 @@ __global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
 #pragma unroll
                     for (int i = 0; i < NA; ++i) x0r[i] = fma(ta, vr[i], x0r[i]);
 #pragma unroll
-                    for (int q = 0; q < NR; ++q)
-                        h[q] = fma(ta, xcol ? fma(ta, g[q], b2[q]) : gr[q], h[q]);
-                    if (!box) hp = fma(ta, xcol ? fma(ta, gp, bp2) : grp, hp);
+                    for (int q = 0; q < NR; ++q) {
+                        aa[q] = fma(ta, fma(ta, g[q], b2[q]), aa[q]);
+                        h[q] = fma(ta, gr[q], h[q]);
+                    }
+                    if (!BOX) hp = fma(ta, grp, hp);
                 } else {
                     ++c_shcap;
                 }
+#pragma unroll
+                for (int q = 0; q < NR; ++q) h[q] = dppd<DPP_ROL1>(h[q]);
+                if (!BOX) hp = dppd<DPP_ROL1>(hp);
                 if (R.trace && l == 0) {
                     int *tr = R.trace + ((size_t)j * p + st) * 4;
                     tr[0] = nl; tr[1] = nr; tr[2] = ns; tr[3] = acc;
                 }
-                (void)ap;
             }
+            c_tests += n_tests;
+            c_evals += n_evals;
             wave_sync();   // the block's LDS is rewritten
         }
     }
@@ -513,11 +715,14 @@ __global__ __launch_bounds__(256, 2) void k_hrss_line(Launch Lc, int fp64)
     }
 }
 
-template <int D, int LIK, int NR>
-static hipError_t line_t(const Launch &L, int smc, int fp64, hipStream_t s)
+template <int D, int LIK, int NR, int OCC>
+static hipError_t line_o(const Launch &L, int smc, int box, int fp64, hipStream_t s)
 {
-    const size_t lds = line_lds_bytes(D, L.max_K, LIK);
-    auto f = smc ? k_hrss_line<D, LIK, NR, true> : k_hrss_line<D, LIK, NR, false>;
+    const size_t lds = line_lds_bytes(D, L.max_K, LIK, box);
+    auto f = smc ? (box ? k_hrss_line<D, LIK, NR, true, true, OCC>
+                        : k_hrss_line<D, LIK, NR, true, false, OCC>)
+                 : (box ? k_hrss_line<D, LIK, NR, false, true, OCC>
+                        : k_hrss_line<D, LIK, NR, false, false, OCC>);
     hipError_t e = hipFuncSetAttribute((const void *)f,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -525,25 +730,38 @@ static hipError_t line_t(const Launch &L, int smc, int fp64, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int D>
-static hipError_t line_d(const Launch &L, int lik, int smc, int fp64, hipStream_t s)
+// Workgroups per CU of the register allocation: a mixture's W fragments in flight do not fit 256
+// registers at D = 64 and 128, and a launch that leaves one workgroup per CU loses nothing by
+// taking more.
+template <int D, int LIK, int NR>
+static hipError_t line_t(const Launch &L, int smc, int box, int fp64, int occ, hipStream_t s)
 {
-    if (lik == LIK_FUNNEL) return line_t<D, LIK_FUNNEL, 1>(L, smc, fp64, s);
+    if constexpr (LIK == LIK_MIXTURE && D >= 64)
+        if (occ == 1) return line_o<D, LIK, NR, 1>(L, smc, box, fp64, s);
+    return line_o<D, LIK, NR, 2>(L, smc, box, fp64, s);
+}
+
+template <int D>
+static hipError_t line_d(const Launch &L, int lik, int smc, int box, int fp64, int occ,
+                         hipStream_t s)
+{
+    if (lik == LIK_FUNNEL) return line_t<D, LIK_FUNNEL, 1>(L, smc, box, fp64, occ, s);
     if constexpr (D <= 128) {
-        if (L.max_K <= 4) return line_t<D, LIK_MIXTURE, 1>(L, smc, fp64, s);
-        if (L.max_K <= 8) return line_t<D, LIK_MIXTURE, 2>(L, smc, fp64, s);
-        if (L.max_K <= kLineForms) return line_t<D, LIK_MIXTURE, 4>(L, smc, fp64, s);
+        if (L.max_K <= 4) return line_t<D, LIK_MIXTURE, 1>(L, smc, box, fp64, occ, s);
+        if (L.max_K <= 8) return line_t<D, LIK_MIXTURE, 2>(L, smc, box, fp64, occ, s);
+        if (L.max_K <= kLineForms) return line_t<D, LIK_MIXTURE, 4>(L, smc, box, fp64, occ, s);
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_hrss_line(const Launch &L, int D, int lik, int smc, int fp64, hipStream_t s)
+hipError_t launch_hrss_line(const Launch &L, int D, int lik, int smc, int box, int fp64, int occ,
+                            hipStream_t s)
 {
     if (L.nblocks <= 0) return hipSuccess;
-    if (D == 32) return line_d<32>(L, lik, smc, fp64, s);
-    if (D == 64) return line_d<64>(L, lik, smc, fp64, s);
-    if (D == 128) return line_d<128>(L, lik, smc, fp64, s);
-    if (D == 320) return line_d<320>(L, lik, smc, fp64, s);
+    if (D == 32) return line_d<32>(L, lik, smc, box, fp64, occ, s);
+    if (D == 64) return line_d<64>(L, lik, smc, box, fp64, occ, s);
+    if (D == 128) return line_d<128>(L, lik, smc, box, fp64, occ, s);
+    if (D == 320) return line_d<320>(L, lik, smc, box, fp64, occ, s);
     return hipErrorInvalidValue;
 }
 

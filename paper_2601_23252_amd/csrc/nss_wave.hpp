@@ -11,6 +11,17 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
+// A pointer read from a descriptor in memory is a generic one to the compiler, and a load through
+// it a flat load, which counts as an LDS access too: every wait for LDS then waits for it.  This
+// names it as global memory.
+template <typename T>
+using global_ptr = T __attribute__((address_space(1))) *;
+template <typename T>
+__device__ __forceinline__ global_ptr<T> as_global(T *p)
+{
+    return (global_ptr<T>)p;
+}
+
 #define LOG_2PI 1.8378770664093454836
 
 // ------------------------------------------------------------------------------------------
