@@ -203,12 +203,13 @@ typedef enum {
                               * per workgroup). */
 #define NS_FLAG_SHALLOW_PLAN 64  /* every candidate is evaluated as a point, with at most 4
                                  * tests planned per round (the two bracket ends, then shrink
-                                 * proposals).  By default a mixture's (up to 16 components) or
-                                 * the funnel's slice chains, which read their directions from
-                                 * the buffer, evaluate sixteen candidates of a step at a time
-                                 * along the step's line: the quadratic forms are parabolas in
-                                 * t, held in FP64 in every precision (no re-checks), and each
-                                 * chain's final point is evaluated as a point.  Decisions and
+                                 * proposals).  By default the slice chains of a mixture (up to
+                                 * 16 components), the funnel or the Gaussian-Rastrigin
+                                 * likelihood that read their directions from the buffer
+                                 * evaluate sixteen candidates of a step at a time along the
+                                 * step's line: quadratic forms are parabolas in t, held in
+                                 * FP64 in every precision (no re-checks), and each chain's
+                                 * final point is evaluated as a point.  Decisions and
                                  * trajectories are identical. */
 #define NS_FLAG_PLAN8 128  /* mixture chains in a 16-bit mode plan 8 tests per round (the
                            * next two stepping-out tests of each open end and the shrink

@@ -454,8 +454,8 @@ static int dirs_blocks(const RunHost &r)
 }
 static int hrss_blocks(const RunHost &r) { return (r.k + r.R.C - 1) / r.R.C; }  // GP: C = 1
 
-// Whether a run's chains may be evaluated along each step's line (k_hrss_line): a likelihood of
-// quadratic forms, slice chains with the direction buffer, one workgroup's Gram matrices in LDS
+// Whether a run's chains may be evaluated along each step's line (k_hrss_line): any likelihood but
+// the GP's, slice chains with the direction buffer, one workgroup's Gram matrices in LDS
 // (sixteen components), chains long enough that a block of fifteen steps is mostly used (a
 // shorter chain pays for the whole block: the products of one block cost what the batched tile
 // takes for about three steps), and parameters whose squares stay finite (an overflow to
@@ -464,7 +464,7 @@ constexpr int kLineMinSteps = 4;
 constexpr double kLineMax = 1e40;
 static bool line_ok(const RunHost &rh, const ns_prior *prior, const ns_energy *en)
 {
-    if (rh.lik != LIK_MIXTURE && rh.lik != LIK_FUNNEL) return false;
+    if (rh.lik == LIK_GP) return false;
     if (rh.R.rw || !rh.R.dirbuf || rh.p < kLineMinSteps) return false;
     if (rh.cfg.flags & NS_FLAG_SHALLOW_PLAN) return false;
     if (rh.lik == LIK_MIXTURE && rh.K > 16) return false;
@@ -479,6 +479,7 @@ static bool line_ok(const RunHost &rh, const ns_prior *prior, const ns_energy *e
         const double a = prior->a[0], b = prior->b[0];
         return box ? (a >= -600.0 && b <= 600.0) : fabs(a) + 40.0 * b <= 600.0;
     }
+    if (rh.lik == LIK_RG) return true;
     for (size_t i = 0; i < (size_t)rh.K * rh.d; ++i)
         if (!fits(en->mean[i])) return false;
     return rh.wmax <= kLineMax;

@@ -1,5 +1,5 @@
-// gfx950 HRSS chains whose likelihood is a function of quadratic forms (Gaussian mixtures,
-// Neal's funnel), evaluated along each step's line.
+// gfx950 HRSS chains evaluated along each step's line: likelihoods of quadratic forms (Gaussian
+// mixtures, Neal's funnel), and the Gaussian-Rastrigin likelihood's sum over coordinates.
 //
 // A step's candidates all lie on x + t v, and a form |W (x + t v - mu)|^2 is on that line the
 // parabola a + 2 b t + g t^2 with a = |W (x - mu)|^2, b = W (x - mu) . W v, g = |W v|^2.  The
@@ -29,6 +29,13 @@
 // row of u_15 is kept shifted so that the current step's column is column 0 (row shifts and row
 // broadcasts instead of trips through LDS), and whole-wave values move by lane reads.
 //
+// The Gaussian-Rastrigin likelihood has no parabola: a candidate's four lanes sum |y|^2 and
+// cos(2 pi y) over a quarter of the coordinates each, y = x + t v from LDS, with no barrier and no
+// reduction over the wave.  cos(2 pi y) is sin(2 pi s), s = 1/4 - |y - rint(y)|, by its Taylor
+// polynomial of degree 21 (truncation 1.3e-18 on |s| <= 1/4).  At d = 100, 500 chains of 2500
+// steps: 25.4 ms a launch with points and 7.4 here; a pass takes 3,000 cycles of FP64 arithmetic,
+// eight polynomials side by side for their latency (two: 8.6 ms).
+//
 // What it replaces evaluated every candidate as a point, in a tile shared by a workgroup's
 // chains, at two barriers and two to three tiles a step.  One launch with points and here:
 // d = 5, 50 chains of 25 steps 241 and 33 us; d = 32, 500 chains of 160 steps (BF16x3 points)
@@ -43,6 +50,7 @@
 #include "nss_wave.hpp"
 
 #include <math.h>
+#include <type_traits>
 
 namespace nss {
 
@@ -56,17 +64,18 @@ constexpr int kLineForms = 16;          // most components
 // t, and the shrink uniforms of a later pass; the final points' FP64 tile overlays the Gram
 // matrices.
 struct LineLayout {
-    int gram, x, us, tt, su, chain;     // per-chain offsets and stride
+    int gram, x, v, us, tt, su, chain;  // per-chain offsets and stride (v: Gaussian-Rastrigin)
     int mu, pa, ipb;                    // the workgroup's means and Gaussian prior (1 / std)
     int cand, q, L, mask, total;
 };
 __host__ __device__ inline LineLayout line_layout(int D, int K, int lik, bool box)
 {
-    const int forms = (lik == LIK_MIXTURE ? K : 1) + (box ? 0 : 1);
+    const int forms = (lik == LIK_MIXTURE ? K : lik == LIK_RG ? 0 : 1) + (box ? 0 : 1);
     LineLayout o;
     int off = 0;
     o.gram = off; off += al16(forms * 16 * kLineLd * 8);
     o.x = off; off += al16(D * 8);
+    o.v = off; off += lik == LIK_RG ? al16(D * 8) : 0;
     o.us = off; off += 16 * kStepU * 8;
     o.tt = off; off += 16 * 16 * 8;
     o.su = off; off += 16 * 8;
@@ -127,6 +136,32 @@ __device__ __forceinline__ double lane_value(double v, int lane)
     return r;
 }
 
+// sum of cos(2 pi y[i]) (see above; y - rint(y) and, from 1/8 up, 1/4 minus it are exact): the
+// polynomials of U values side by side, for the length of their chains
+template <int U>
+__device__ __forceinline__ double cos_2pi(const double (&y)[U])
+{
+    constexpr double kC[11] = {0.0011309237482517963, -0.012031585942120627, 0.10422916220813984,
+                                -0.7181223017785006, 3.819952584848282, -15.09464257682299,
+                                42.058693944897655, -76.70585975306139, 81.60524927607506,
+                                -41.34170224039976, 6.283185307179586};
+    double s[U], z[U], p[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i) {
+        s[i] = 0.25 - fabs(y[i] - rint(y[i]));
+        z[i] = s[i] * s[i];
+        p[i] = kC[0];
+    }
+#pragma unroll
+    for (int k = 1; k < 11; ++k)
+#pragma unroll
+        for (int i = 0; i < U; ++i) p[i] = fma(p[i], z[i], kC[k]);
+    double c = 0.0;
+#pragma unroll
+    for (int i = 0; i < U; ++i) c = fma(p[i], s[i], c);
+    return c;
+}
+
 // NR: forms per lane (components 4 q + row, q < NR); TEMP: tempered SMC slices (no constraint);
 // BOX: the prior is a box.
 template <int D, int LIK, int NR, bool TEMP, bool BOX, int OCC>
@@ -139,11 +174,11 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
     if (R.iscal[0] || R.iscal[2] <= 0) return;
     constexpr int NA = (D + 63) / 64;
     constexpr int NJB = D / 16, NKS = D / 4;
-    constexpr bool MIX = LIK == LIK_MIXTURE;
+    constexpr bool MIX = LIK == LIK_MIXTURE, RG = LIK == LIK_RG;
     const LineLayout lay = line_layout(D, P.K, LIK, BOX);
     const int tid = threadIdx.x, w = uniform_i(tid >> 6), l = tid & 63;
     const int col = l & 15, row = l >> 4;
-    const int d = P.d, K = MIX ? P.K : 1, C = R.C, p = R.p;
+    const int d = P.d, K = MIX ? P.K : (RG ? 0 : 1), C = R.C, p = R.p;
     const double Lstar = R.scal[0], beta = Lstar;   // tempered: the inverse temperature
     const int t0 = R.iscal[1], nsurv = R.iscal[2];
     const uint32_t it = (uint32_t)R.iscal[3] + 1u;
@@ -153,6 +188,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
     unsigned char *mine = smem + w * lay.chain;
     double *gram = (double *)(mine + lay.gram);
     double *xs = (double *)(mine + lay.x);
+    double *vs = (double *)(mine + lay.v);
     double *us = (double *)(mine + lay.us);
     double *tt = (double *)(mine + lay.tt);
     double *su = (double *)(mine + lay.su);
@@ -212,7 +248,9 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             cst[q] = MIX ? (c < K ? P.cst[c] : -INFINITY) : 0.0;
         }
         // below this a component cannot make the mixture exceed L* together with the others
-        const double Lamb = (MIX && K > 1) ? Lstar - log((double)K) - 1e-6 : INFINITY;
+        const double Lamb = MIX && K > 1 ? Lstar - log((double)K) - 1e-6
+                            : RG         ? Lstar - log(2.0) - 1e-6
+                                         : INFINITY;
         const auto dirs = as_global((const double *)R.dirbuf) + (size_t)j * p * D;
         const auto ub = as_global((const double *)R.ubuf) + (size_t)j * p * kStepU;
         const bool xcol = col == 15;
@@ -362,8 +400,8 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                     }
                     put(gpri, Gp);
                 }
-            } else {
-                // the funnel's form: the coordinates after the first
+            } else if (!RG || !BOX) {
+                // the funnel's form: the coordinates after the first (and the Gaussian prior's)
                 const bool dcol = col < nb;
                 const auto vrow = dirs + (size_t)(s0 + (dcol ? col : 0)) * D;
                 d4v G = (d4v){0.0, 0.0, 0.0, 0.0}, Gp = (d4v){0.0, 0.0, 0.0, 0.0};
@@ -372,13 +410,13 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                     const int kk = 4 * ks + row;
                     const double bv = dcol ? vrow[kk] : (xcol ? xs[kk] : 0.0);
                     const double bb = kk > 0 ? bv : 0.0;
-                    G = __builtin_amdgcn_mfma_f64_16x16x4f64(bb, bb, G, 0, 0, 0);
+                    if (!RG) G = __builtin_amdgcn_mfma_f64_16x16x4f64(bb, bb, G, 0, 0, 0);
                     if (!BOX) {
                         const double bp = kk < d ? (xcol ? bv - spa[kk] : bv) * sipb[kk] : 0.0;
                         Gp = __builtin_amdgcn_mfma_f64_16x16x4f64(bp, bp, Gp, 0, 0, 0);
                     }
                 }
-                put(gram, G);
+                if (!RG) put(gram, G);
                 if (!BOX) put(gpri, Gp);
             }
             wave_sync();
@@ -389,8 +427,8 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             for (int q = 0; q < NR; ++q) {
                 const int c = 4 * q + row;
                 const double *g15 = gram + ((c < K ? c : 0) * 16 + 15) * kLineLd;
-                h[q] = g15[col];
-                aa[q] = g15[15];
+                h[q] = RG ? 0.0 : g15[col];
+                aa[q] = RG ? 0.0 : g15[15];
             }
             if (!BOX) hp = gpri[15 * kLineLd + col];
             if (s0 + kLineB < p) fetch_block(s0 + kLineB);
@@ -399,7 +437,8 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             unsigned n_tests = 0, n_evals = 0;
             double tn = tt[col], grn[NR], gpn = 0.0;   // the next step's, read ahead
 #pragma unroll
-            for (int q = 0; q < NR; ++q) grn[q] = gram[((4 * q + row < K ? 4 * q + row : 0) * 16) * kLineLd + col];
+            for (int q = 0; q < NR; ++q)
+                grn[q] = RG ? 0.0 : gram[((4 * q + row < K ? 4 * q + row : 0) * 16) * kLineLd + col];
             if (!BOX) gpn = gpri[col];
             for (int sb = 0; sb < nb; ++sb) {
                 const int st = s0 + sb;
@@ -433,12 +472,21 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
 #pragma unroll
                     for (int q = 0; q < NR; ++q) {
                         const int c = 4 * q + row < K ? 4 * q + row : 0;
-                        grn[q] = gram[(c * 16 + sn) * kLineLd + min(sn + col, 15)];
+                        if (!RG) grn[q] = gram[(c * 16 + sn) * kLineLd + min(sn + col, 15)];
                     }
                     if (!BOX) gpn = gpri[sn * kLineLd + min(sn + col, 15)];
                 }
                 double v0 = 0.0, x00 = 0.0;
-                if constexpr (!MIX) { v0 = lane_value(vr[0], 0); x00 = lane_value(x0r[0], 0); }
+                if constexpr (LIK == LIK_FUNNEL) {
+                    v0 = lane_value(vr[0], 0);
+                    x00 = lane_value(x0r[0], 0);
+                }
+                if constexpr (RG) {   // the point and the direction, for the coordinate sums
+#pragma unroll
+                    for (int i = 0; i < NA; ++i)
+                        if (l + 64 * i < D) { xs[l + 64 * i] = x0r[i]; vs[l + 64 * i] = vr[i]; }
+                    wave_sync();
+                }
                 // box prior: t inside [tin0, tin1] keeps every coordinate in the box whatever
                 // the rounding of x + t v, t outside [tou0, tou1] puts one out; the margins
                 // cover the FP32 quotients and, away from the faces, the rounding of y
@@ -527,6 +575,52 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                                 se += __shfl_xor(se, 32, 64);
                                 in |= (unsigned)__ballot(se > 1.0) & doubt;
                             }
+                        }
+                    } else if constexpr (RG) {
+                        double s2 = 0.0, sc = 0.0;
+                        // the lane's coordinates 8 i + 2 row, + 1: four i at a time, then one
+                        auto add = [&](int a, auto n) {
+                            constexpr int U = 2 * decltype(n)::value;
+                            double y[U];
+#pragma unroll
+                            for (int i = 0; i < U / 2; ++i) {
+                                const double2 x2 = *(const double2 *)(xs + a + 8 * i);
+                                const double2 v2 = *(const double2 *)(vs + a + 8 * i);
+                                y[2 * i] = fma(t, v2.x, x2.x);
+                                y[2 * i + 1] = fma(t, v2.y, x2.y);
+                            }
+                            double q0 = 0.0, q1 = 0.0;
+#pragma unroll
+                            for (int i = 0; i < U / 2; ++i) {
+                                q0 = fma(y[2 * i], y[2 * i], q0);
+                                q1 = fma(y[2 * i + 1], y[2 * i + 1], q1);
+                            }
+                            s2 += q0 + q1;
+                            sc += cos_2pi<U>(y);
+                        };
+                        int a = 2 * row;
+                        for (; a + 25 < d; a += 32) add(a, std::integral_constant<int, 4>{});
+                        for (; a + 1 < d; a += 8) add(a, std::integral_constant<int, 1>{});
+                        if (a < d) {
+                            const double y[1] = {fma(t, vs[a], xs[a])};
+                            s2 = fma(y[0], y[0], s2);
+                            sc += cos_2pi<1>(y);
+                        }
+                        s2 += __shfl_xor(s2, 16, 64);
+                        sc += __shfl_xor(sc, 16, 64);
+                        s2 += __shfl_xor(s2, 32, 64);
+                        sc += __shfl_xor(sc, 32, 64);
+                        const double tf = P.rg_la - 0.5 * s2;
+                        const double tg = P.rg_l1a - P.rg_amp * d + P.rg_amp * sc;
+                        const double mx = fmax(tf, tg);
+                        if constexpr (TEMP) {
+                            Lv = mx + log(exp(tf - mx) + exp(tg - mx));
+                        } else {
+                            in = (unsigned)__ballot(mx > Lstar) & 0xFFFFu;
+                            const unsigned doubt = (unsigned)__ballot(mx > Lamb) & ~in & okm;
+                            if (doubt)
+                                in |= (unsigned)__ballot(exp(tf - Lstar) + exp(tg - Lstar) > 1.0) &
+                                      doubt;
                         }
                     } else {
                         const double s2 = fmax(fma(t, fma(t, g[0], b2[0]), aa[0]), 0.0);
@@ -746,6 +840,7 @@ static hipError_t line_d(const Launch &L, int lik, int smc, int box, int fp64, i
                          hipStream_t s)
 {
     if (lik == LIK_FUNNEL) return line_t<D, LIK_FUNNEL, 1>(L, smc, box, fp64, occ, s);
+    if (lik == LIK_RG) return line_t<D, LIK_RG, 1>(L, smc, box, fp64, occ, s);
     if constexpr (D <= 128) {
         if (L.max_K <= 4) return line_t<D, LIK_MIXTURE, 1>(L, smc, box, fp64, occ, s);
         if (L.max_K <= 8) return line_t<D, LIK_MIXTURE, 2>(L, smc, box, fp64, occ, s);

@@ -82,12 +82,20 @@ def test_funnel(N, d):
     _same(N, G.funnel(d, m=100, k=41, p=20))
 
 
-@pytest.mark.parametrize("target", ["gauss", "mixture", "funnel"])
+@pytest.mark.parametrize("d", [1, 2, 7, 8, 9, 64, 100, 129, 320])
+@pytest.mark.parametrize("alpha", [0.0, 0.5, 1.0])
+def test_rastrigin(N, d, alpha):
+    from paper_2601_23252_amd import problems as G
+    _same(N, G.rastrigin_gauss(d, alpha, m=100, k=41, p=20))
+
+
+@pytest.mark.parametrize("target", ["gauss", "mixture", "funnel", "rastrigin"])
 def test_tempered(N, target):
     from paper_2601_23252_amd import problems as G
     prob = {"gauss": lambda: G.config2(2, d=20, m=120, k=60),
             "mixture": lambda: G.mixture_problem(6, 24, 5, m=120, k=60),
-            "funnel": lambda: G.funnel(9, m=120, k=60)}[target]()
+            "funnel": lambda: G.funnel(9, m=120, k=60),
+            "rastrigin": lambda: G.rastrigin_gauss(6, 0.5, m=120, k=60, p=20)}[target]()
     a = N.NSRun(prob, seed=4, outer="smc", p=20)
     b = N.NSRun(prob, seed=4, outer="smc", p=20, shallow_plan=True)
     for _ in range(5):
