@@ -216,9 +216,8 @@ typedef enum {
                            * proposals of the three likeliest expansion outcomes), each
                            * evaluated as a point; identical results.  NS_FLAG_SHALLOW_PLAN
                            * takes precedence. */
-#define NS_FLAG_GP_NO_WAIT 256  /* testing the failure path of NS_LIK_GP chains: the
-                                * factorisation's bounded wait for each diagonal tile gives up
-                                * at once, so every chain evaluation fails (log L = -inf, a
+#define NS_FLAG_GP_NO_WAIT 256  /* testing the failure path of NS_LIK_GP chains: every chain
+                                * evaluation gives up at once, fails (log L = -inf, a
                                 * rejection) and is counted in gp_wait_timeouts; every kernel
                                 * still exits normally.  The initial evaluation is unaffected. */
 #define NS_FLAG_FREEZE_WHITENING 512  /* the whitening factor (and with it the direction
@@ -266,9 +265,8 @@ typedef struct {
     double width;           /* slice width in use */
     int64_t tune_launches;  /* NS_FLAG_AUTOTUNE: HRSS launches the tuner timed in this context
                              * (0 when every shape came from the cache) */
-    int64_t gp_wait_timeouts; /* NS_LIK_GP: chain evaluations whose factorisation gave up a
-                               * bounded wait for a diagonal tile (the candidate then counts as
-                               * log L = -inf); never expected outside NS_FLAG_GP_NO_WAIT */
+    int64_t gp_wait_timeouts; /* NS_LIK_GP: chain evaluations that gave up (the candidate then
+                               * counts as log L = -inf); none outside NS_FLAG_GP_NO_WAIT */
 } ns_stats_t;
 
 /* Host arrays for state access (any pointer may be NULL to skip it). */

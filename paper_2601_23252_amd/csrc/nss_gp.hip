@@ -8,14 +8,23 @@
 //
 // One workgroup of 8 waves evaluates one candidate at a time.  The kernel matrix is built as
 // 16x16 tiles of the lower triangle in the accumulator layout of the 16x16x4 MFMA (tile t is
-// owned by tile wave t mod 7; a wave's first seven tiles sit in its own LDS area, the others in
-// its registers), and factorised by a right-looking blocked
-// Cholesky: for each block column J one wave factors the diagonal tile and inverts the factor,
-// the panel tiles are multiplied by that inverse on MFMA, and every trailing tile takes its
-// rank-16 update on MFMA with operands from LDS.  The right-hand side y rides along, so the
-// forward solve z = L^{-1} y and the log-determinant come out of the same sweep:
+// held by wave t mod 8 in registers) and factorised by a right-looking blocked Cholesky.  For
+// each block column J the column's tiles, up to date, go to LDS, and the column is factored with
+// one row per lane: a wave takes the 16 rows of the diagonal tile in its first lanes, 47 rows
+// below it in the next and the right-hand side y_J in the last, and eliminates the 16 columns in
+// turn, each row less its pivot entry times the pivot rows' entries (lane reads).  The diagonal
+// factor, the panel L_IJ and z_J = L_JJ^{-1} y_J all come out of that one loop; up to six waves
+// run it side by side, each repeating the diagonal rows, so there is no inverse and no second
+// serial stage.  The other tiles meanwhile take the previous column's rank-16 update on MFMA
+// with operands from LDS.  The log-determinant and |z|^2 are summed on the way:
 //   log L = -|z|^2 / 2 - sum_i log L_ii - n/2 log(2 pi).
 // A pivot that is not positive makes the factorisation fail (FP64: log L = -inf).
+//
+// What bounds it at n = 256 (about 250,000 cycles an evaluation): 16 eliminations of about 4,000
+// cycles on the 256 pivots' dependent chain, the entries' exponentials (50,000), and the trailing
+// products, of which the FP64 matrix rate would allow 43,000.  One launch of 500 chains of 30
+// steps takes 16.2 ms; with one wave factoring and inverting each diagonal tile and a panel stage
+// after it (14,000 and 6,000 cycles a block column) it took 26.4 ms.
 //
 //  k_hrss_gp   one HRSS chain per workgroup (App. A.6), candidates evaluated one at a time
 //  k_eval_gp   one point per workgroup (initial live set, tests)
@@ -31,15 +40,9 @@ namespace {
 
 constexpr int kGpWaves = 8;                                           // per workgroup
 constexpr int kGpThreads = 64 * kGpWaves;
-constexpr int kGpTileWaves = 7;        // waves 0..6 hold the covariance tiles
-constexpr int kGpPivot = 7;            // wave 7 factors the diagonal tiles
 constexpr int kGpMaxTiles = 136;                                      // 16 * 17 / 2
-constexpr int kGpSlots = (kGpMaxTiles + kGpTileWaves - 1) / kGpTileWaves;  // tiles per wave
-// a wave's first kGpLdsSlots tiles (the upper block rows, final after few updates) live in its
-// own LDS area, the rest in registers: 14 register tiles keep the wave inside its 256 VGPRs
-constexpr int kGpLdsSlots = 7;
-constexpr int kGpRegSlots = kGpSlots - kGpLdsSlots;
-constexpr int kGpSpinMax = 1 << 22;    // bound on the pivot wave's wait for a diagonal tile
+constexpr int kGpSlots = kGpMaxTiles / kGpWaves;                      // tiles per wave
+constexpr int kGpRowLanes = 47;        // panel rows of a wave's elimination (lanes 16..62)
 constexpr int kGpLd = 17;                                             // LDS tile row stride
 constexpr int kTile = 16 * kGpLd;
 constexpr int kGpD = 6;                                               // hyperparameters
@@ -54,12 +57,11 @@ constexpr int kOffT = kOffSc + 4 * kGpMaxObs * 8;
 template <typename T>
 constexpr int gp_lds_bytes()
 {
-    // 16 panel tiles, diagonal tile, inverse tile, right-hand side, z block, reciprocal pivots,
-    // then the tile waves' LDS-resident tiles; the FP32 refinement adds the inverse factors of
-    // all diagonal tiles, z, alpha, the partial products of a block step and one 16-vector
-    return kOffT + (int)sizeof(T) * (16 * kTile + 2 * kTile + kGpMaxObs + 32 +
-                                     kGpLdsSlots * kGpTileWaves * kTile) +
-           (sizeof(T) == 4 ? 4 * (16 * kTile + 2 * kGpMaxObs + 16 * 16 + 16) : 0);
+    // two columns of tiles (the one being factored and the one being read), the right-hand side;
+    // the FP32 refinement adds the diagonal factors and their reciprocal pivots, z, alpha and the
+    // partial products of a block step
+    return kOffT + (int)sizeof(T) * (2 * 16 * kTile + kGpMaxObs) +
+           (sizeof(T) == 4 ? 4 * (16 * kTile + 3 * kGpMaxObs + 16 * 16) : 0);
 }
 
 template <typename T> struct Mf;
@@ -113,6 +115,45 @@ __device__ __forceinline__ GpTheta gp_theta(const double *u)
     return h;
 }
 
+// exp(x) for x <= 0: x = k log 2 + r with |r| <= log(2) / 2, the Taylor polynomial of degree 13
+// (truncation 4e-18), no test for overflow; large -x gives 0 by the exponent.
+__device__ __forceinline__ double exp_neg(double x)
+{
+    const double k = rint(x * 1.44269504088896340736);
+    double r = fma(-k, 0.693147180369123816490, x);   // the leading 33 bits of log 2
+    r = fma(-k, 1.90821492927058770002e-10, r);
+    double p = 1.0 / 6227020800.0;
+    p = fma(p, r, 1.0 / 479001600.0);
+    p = fma(p, r, 1.0 / 39916800.0);
+    p = fma(p, r, 1.0 / 3628800.0);
+    p = fma(p, r, 1.0 / 362880.0);
+    p = fma(p, r, 1.0 / 40320.0);
+    p = fma(p, r, 1.0 / 5040.0);
+    p = fma(p, r, 1.0 / 720.0);
+    p = fma(p, r, 1.0 / 120.0);
+    p = fma(p, r, 1.0 / 24.0);
+    p = fma(p, r, 1.0 / 6.0);
+    p = fma(p, r, 0.5);
+    p = fma(p, r, 1.0);
+    p = fma(p, r, 1.0);
+    return ldexp(p, (int)k);
+}
+
+// The kernel at input differences d1, d2, with s1, s2 the sines of pi d / P.
+template <typename T>
+__device__ __forceinline__ T gp_cov(double d1, double d2, double s1, double s2, const GpTheta &h)
+{
+    if constexpr (sizeof(T) == 8) {
+        const double a1 = d1 * h.il1, a2 = d2 * h.il2;
+        return h.sf2 * exp_neg(-0.5 * (a1 * a1 + a2 * a2) - 2.0 * (s1 * s1 + s2 * s2) * h.ilp2);
+    } else {
+        const float a1 = (float)(d1 * h.il1), a2 = (float)(d2 * h.il2);
+        const float f1 = (float)s1, f2 = (float)s2;
+        return (float)h.sf2 *
+               expf(-0.5f * (a1 * a1 + a2 * a2) - 2.0f * (f1 * f1 + f2 * f2) * (float)h.ilp2);
+    }
+}
+
 // Entry (row, col) of the padded covariance: identity outside the n observations, zero above
 // the diagonal (never read as data).  sin(pi (a - b) / P) = s_a c_b - c_a s_b from the per-point
 // sc[i] = (sin, cos)(pi x_i1 / P), (sin, cos)(pi x_i2 / P), so an entry costs one exponential.
@@ -122,22 +163,11 @@ __device__ __forceinline__ T gp_entry(const double *xs, const double *sc, int n,
 {
     if (row >= n || col >= n) return (row == col) ? T(1) : T(0);
     if (col > row) return T(0);
-    const double d1 = xs[2 * row] - xs[2 * col], d2 = xs[2 * row + 1] - xs[2 * col + 1];
     const double *pa = sc + 4 * row, *pb = sc + 4 * col;
-    const double s1 = pa[0] * pb[1] - pa[1] * pb[0], s2 = pa[2] * pb[3] - pa[3] * pb[2];
-    if constexpr (sizeof(T) == 8) {
-        const double a1 = d1 * h.il1, a2 = d2 * h.il2;
-        double v = h.sf2 * exp(-0.5 * (a1 * a1 + a2 * a2) - 2.0 * (s1 * s1 + s2 * s2) * h.ilp2);
-        if (row == col) v += h.sn2;
-        return v;
-    } else {
-        const float a1 = (float)(d1 * h.il1), a2 = (float)(d2 * h.il2);
-        const float f1 = (float)s1, f2 = (float)s2;
-        float v = (float)h.sf2 *
-                  expf(-0.5f * (a1 * a1 + a2 * a2) - 2.0f * (f1 * f1 + f2 * f2) * (float)h.ilp2);
-        if (row == col) v += (float)h.sn2;
-        return v;
-    }
+    T v = gp_cov<T>(xs[2 * row] - xs[2 * col], xs[2 * row + 1] - xs[2 * col + 1],
+                    pa[0] * pb[1] - pa[1] * pb[0], pa[2] * pb[3] - pa[3] * pb[2], h);
+    if (row == col) v += (T)h.sn2;
+    return v;
 }
 
 template <typename T, typename V>
@@ -153,19 +183,14 @@ __device__ __forceinline__ void load_tile(V &acc, const T *p, int l)
     for (int r = 0; r < 4; ++r) acc[r] = p[Mf<T>::row(l, r) * kGpLd + (l & 15)];
 }
 
-// Factor the diagonal tile in dg (rows of stride kGpLd) in place, write the inverse of the
-// factor to li and its reciprocal pivots to dv, z = L^{-1} y_J to zb, add log det and |z|^2 to
-// this wave's (ldet, quad) (lane 0) and raise the flag on a pivot that is not positive.  Run by
-// one whole wave; lane i (mod 16) holds row i, every DPP row a copy.
-// 1/sqrt(x): the hardware estimate refined by Newton steps r <- r (3/2 - x r^2 / 2)
-// (two in FP64, one in FP32), for a short dependent chain per pivot.
+// 1/sqrt(x) from the hardware estimate r, for a short dependent chain per pivot: with
+// e = 1 - x r^2, r (1 + e/2 + 3 e^2/8) has the relative error 5 e^3 / 16 (e is about 2^-23 in FP64;
+// FP32 takes Newton's r (1 + e/2)).
 __device__ __forceinline__ double rsq_refined(double x)
 {
-    double r = __builtin_amdgcn_rsq(x);
-    const double h = 0.5 * x;
-    r = r * (1.5 - h * r * r);
-    r = r * (1.5 - h * r * r);
-    return r;
+    const double r = __builtin_amdgcn_rsq(x);
+    const double e = fma(-(x * r), r, 1.0);
+    return fma(r * e, fma(e, 0.375, 0.5), r);
 }
 __device__ __forceinline__ float rsq_refined(float x)
 {
@@ -173,99 +198,81 @@ __device__ __forceinline__ float rsq_refined(float x)
     return r * (1.5f - 0.5f * x * r * r);
 }
 
+// Eliminates block column J with one row per lane (see above): a[c] is the lane's row, lane i < 16
+// row i of the diagonal tile.  On return lane i < 16 holds row i of the factor (its entries above
+// the diagonal are not meaningful), the other lanes their row times the transposed inverse
+// factor.  iv: reciprocal pivots' roots; p0, p1: the products of the first and last eight pivots;
+// bad: a pivot was not positive (the results are then not meaningful).
 template <typename T>
-__device__ __forceinline__ void diag_block(T *dg, T *li, T *zb, T *dv, const T *yJ, int *flag,
-                                           int l, double &ldet, double &quad)
+__device__ __forceinline__ void eliminate(T (&a)[16], T (&iv)[16], double &p0, double &p1, int &bad)
 {
-    const int i = l & 15;
-    T a[16], iv[16];
-#pragma unroll
-    for (int c = 0; c < 16; ++c) a[c] = dg[i * kGpLd + c];
-    bool bad = false;
-    double prod = 1.0;
+    p0 = p1 = 1.0;
+    bad = 0;
 #pragma unroll
     for (int jj = 0; jj < 16; ++jj) {
-        const T piv = readlane_t(a[jj], jj);
-        const bool ok = piv > T(0);
-        bad = bad || !ok;
-        const T r = ok ? rsq_refined(piv) : T(1);
-        const T ljj = ok ? piv * r : T(1);
+        T piv = readlane_t(a[jj], jj);
+        asm volatile("" : "+v"(piv));
+        bad |= piv > T(0) ? 0 : 1;
+        if (jj < 8) p0 *= (double)piv; else p1 *= (double)piv;
+        const T r = rsq_refined(piv);
         iv[jj] = r;
-        prod *= (double)ljj;
-        // column jj scaled; rows above jj only touch their unused upper part
-        a[jj] = (i == jj) ? ljj : a[jj] * r;
+        a[jj] *= r;
 #pragma unroll
         for (int c = jj + 1; c < 16; ++c) a[c] -= a[jj] * readlane_t(a[jj], c);
-    }
-    ldet += log(prod);
-    if (l == 0 && bad) *flag = 1;
-    // inverse, one column per lane: x = L^{-1} e_c by forward substitution, L[r][t] taken from
-    // lane r's registers (one row's operands in flight at a time)
-    const int c = l & 15;
-    T x[16];
+        // every row takes this column now: left to itself the compiler sinks the updates to
+        // their columns' turns and keeps all the lane reads until then
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        T sacc = (r == c) ? T(1) : T(0);
-#pragma unroll
-        for (int t = 0; t < r; ++t) sacc -= readlane_t(a[t], r) * x[t];
-        x[r] = sacc * iv[r];
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    // z_J = L_JJ^{-1} y_J: row sums over the 16 lanes of a DPP row
-    const T yc = yJ[c];
-    double q2 = 0.0;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        if (l < 16) li[r * kGpLd + c] = x[r];
-        const T zr = row_sum16(x[r] * yc);
-        if (l == 0) zb[r] = zr;
-        q2 += (double)zr * (double)zr;
-    }
-    if (l == 0) {
-        quad += q2;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) dv[r] = iv[r];
+        for (int c = jj + 1; c < 16; ++c) asm volatile("" : "+v"(a[c]));
     }
 }
 
 // log N(y; 0, K_theta + sigma_n^2 I) at u = log theta with the factorisation in T.  Called by
 // every thread of the workgroup with the same u (the result is uniform); the inputs and
-// targets must be staged at kOffXs / kOffYs.  failed = a pivot was not positive.
+// targets must be staged at kOffXs / kOffYs.  failed = a pivot was not positive.  A negative
+// spin_max makes the evaluation fail as timed out at once (a host-set test mode of the failure
+// path).
 //
-// Waves 0..6 hold the covariance tiles and do the panel and trailing updates; wave 7 factors
-// each diagonal tile as soon as its owner has applied the last update to it and published it
-// (a one-block look-ahead: the factorisation of block J+1 overlaps the trailing update of
-// step J).  The two roles run separate loops with the same barrier count, so the pivot wave's
-// code holds none of the tile registers.
+// A function of its own rather than inlined in the chain's loop: there, the loop's state and what
+// the compiler hoists out of it (addresses, the math functions' constants) took registers that
+// the tiles need, and came back from scratch memory inside the entries' loop.
+typedef __attribute__((address_space(3))) unsigned char *lds_ptr;
+struct GpPoint {
+    double u[kGpD];
+};
+struct GpResult {
+    double L;
+    int failed, timed_out;
+};
 template <typename T>
-__device__ __forceinline__ double gp_eval(const double *u, int n, unsigned char *smem, bool &failed,
-                                          bool &timed_out, int spin_max = kGpSpinMax)
+__device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_ptr lds,
+                                                         int spin_max)
 {
+    unsigned char *smem = (unsigned char *)lds;
+    const double *u = pt.u;
     typedef Mf<T> M;
     typedef typename M::v4 v4;
     const double *xs = (const double *)(smem + kOffXs);
     const double *ys = (const double *)(smem + kOffYs);
     double *red = (double *)(smem + kOffMisc);
     int *flag = (int *)(red + 16);
-    int *dflag = flag + 1;           // index of the last diagonal tile published to dg
-    int *tflag = flag + 2;           // the pivot wave's bounded wait gave up
     double *sc = (double *)(smem + kOffSc);
-    T *pan = (T *)(smem + kOffT);
-    T *dg = pan + 16 * kTile;
-    T *li = dg + kTile;
-    T *yb = li + kTile;
-    T *zb = yb + kGpMaxObs;
-    T *dv = zb + 16;                 // reciprocal pivots of the diagonal tile
-    T *far = dv + 16;                // [kGpLdsSlots][kGpTileWaves] LDS-resident tiles
+    T *pan = (T *)(smem + kOffT);    // [2][16] tiles
+    T *yb = pan + 2 * 16 * kTile;
     constexpr bool refine = sizeof(T) == 4;
-    // FP32 refinement: L_JJ^{-1} of every block (the factor's inverse diagonal tiles), z,
-    // alpha = L^{-T} z, partial products of one block step, one 16-vector
-    float *linv = (float *)(far + kGpLdsSlots * kGpTileWaves * kTile);
-    float *zall = linv + 16 * kTile;
+    // FP32 refinement: L_JJ of every block and its reciprocal pivots, z, alpha = L^{-T} z, the
+    // partial products of one block step
+    float *ldg = (float *)(yb + kGpMaxObs);
+    float *rdg = ldg + 16 * kTile;
+    float *zall = rdg + kGpMaxObs;
     float *alpha = zall + kGpMaxObs;
     float *part = alpha + kGpMaxObs;
-    float *wv = part + 16 * 16;
-    const int tid = threadIdx.x, lane0 = tid & 63, w = uniform_i(tid >> 6);
+    if (spin_max < 0) return GpResult{-INFINITY, 1, 1};
+    // the thread index, opaque to the compiler in each evaluation and each block column: keeps
+    // the many lane-derived masks and LDS addresses of the unrolled code below from being hoisted
+    // out of the loops around it, where they would hold registers across all of it
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane0 = tid & 63, w = uniform_i(tid >> 6);
     const int NT = (n + 15) >> 4, NTT = NT * (NT + 1) / 2;
     const GpTheta h = gp_theta(u);
 
@@ -276,221 +283,228 @@ __device__ __forceinline__ double gp_eval(const double *u, int n, unsigned char 
         sincospi(xs[2 * i + 1] * h.iper, &s1, &c1);
         sc[4 * i] = s0; sc[4 * i + 1] = c0; sc[4 * i + 2] = s1; sc[4 * i + 3] = c1;
     }
-    if (tid == 0) { *flag = 0; *dflag = -1; *tflag = 0; }
+    if (tid == 0) *flag = 0;
     __syncthreads();
 
-    if (w == kGpPivot) {
-        double ldet = 0.0, quad = 0.0;   // lane 0
-        for (int J = -1; J < NT; ++J) {
-            int l = lane0;
-            asm volatile("" : "+v"(l));
-            if (J >= 0) __syncthreads();   // the panel step of the tile waves
-            const int J1 = J + 1;
-            if (J1 < NT) {
-                // bounded wait for the diagonal tile; giving up fails this evaluation (log L =
-                // -inf) and is reported (spin_max < 0: give up at once, a host-set test mode)
-                int spins = 0;
-                while (spin_max < 0 ||
-                       __hip_atomic_load(dflag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) != J1) {
-                    if (++spins > spin_max) {
-                        if (l == 0) { *flag = 1; *tflag = 1; }
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
+    // The wave's tiles, four at a time through its share of the column buffers: the entries'
+    // code then stands in a loop over tiles, with a lane's four entries side by side, instead of
+    // once per register slot.
+    int tI[kGpSlots], tK[kGpSlots];
+    v4 acc[kGpSlots];
+#pragma unroll
+    for (int s0 = 0; s0 < kGpSlots; s0 += 4) {
+        T *stage = pan + 4 * w * kTile;
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {
+            const int t = w + kGpWaves * (s0 + q);
+            if (s0 + q >= kGpSlots || t >= NTT) break;
+            const int l = lane0;
+            int I, K;
+            tile_ik(t, I, K);
+            const int col = 16 * K + (l & 15);
+            v4 e;
+            if (I > K && 16 * I + 16 <= n) {   // all observations, all below the diagonal
+                const double2 xc = *(const double2 *)(xs + 2 * col);
+                const double2 c1 = *(const double2 *)(sc + 4 * col);
+                const double2 c2 = *(const double2 *)(sc + 4 * col + 2);
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    const int row = 16 * I + M::row(l, r);
+                    const double2 xr = *(const double2 *)(xs + 2 * row);
+                    const double2 r1 = *(const double2 *)(sc + 4 * row);
+                    const double2 r2 = *(const double2 *)(sc + 4 * row + 2);
+                    e[r] = gp_cov<T>(xr.x - xc.x, xr.y - xc.y, r1.x * c1.y - r1.y * c1.x,
+                                     r2.x * c2.y - r2.y * c2.x, h);
                 }
-                diag_block<T>(dg, li, zb, dv, yb + 16 * J1, flag, l, ldet, quad);
-                if constexpr (refine) {
-                    for (int e = l; e < kTile; e += 64) linv[J1 * kTile + e] = (float)li[e];
-                    if (l < 16) zall[16 * J1 + l] = (float)zb[l];
+            } else {
+#pragma unroll 1
+                for (int r = 0; r < 4; ++r) {
+                    const T v = gp_entry<T>(xs, sc, n, 16 * I + M::row(l, r), col, h);
+                    e[0] = r == 0 ? v : e[0];
+                    e[1] = r == 1 ? v : e[1];
+                    e[2] = r == 2 ? v : e[2];
+                    e[3] = r == 3 ? v : e[3];
                 }
             }
-            __syncthreads();
+            store_tile<T>(e, stage + q * kTile, l);
         }
-        if (lane0 == 0) {
-            red[0] = ldet;
-            red[1] = quad;
-        }
-        if constexpr (refine) {
-            // alpha = L^{-T} z, block rows from the last: alpha_J = L_JJ^{-T} (z_J - sum_{I > J}
-            // L_IJ^T alpha_I), the products L_IJ^T alpha_I from the tiles' owners
-            for (int J = NT - 1; J >= 0; --J) {
-                __syncthreads();   // the owners' partial products of step J
-                const int l = lane0;
-                if (l < 16) {
-                    float w = zall[16 * J + l];
-                    for (int I = J + 1; I < NT; ++I) w -= part[16 * I + l];
-                    wv[l] = w;
+        wave_sync();
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int s = s0 + q;
+            if (s < kGpSlots) {
+                const int t = w + kGpWaves * s;
+                int I = -1, K = -1;
+                if (t < NTT) {
+                    tile_ik(t, I, K);
+                    load_tile<T>(acc[s], stage + q * kTile, lane0);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) acc[s][r] = T(0);
                 }
-                wave_sync();
-                if (l < 16) {
-                    float a = 0.f;
-                    for (int r = l; r < 16; ++r) a += linv[J * kTile + r * kGpLd + l] * wv[r];
-                    alpha[16 * J + l] = a;
-                }
-                __syncthreads();
+                tI[s] = I;
+                tK[s] = K;
             }
         }
-    } else {
-        int tI[kGpSlots], tK[kGpSlots];
-        v4 acc[kGpRegSlots];             // slot s >= kGpLdsSlots in acc[s - kGpLdsSlots]
-        T *lt[kGpLdsSlots];              // slot s < kGpLdsSlots in LDS
+        wave_sync();
+    }
+    __syncthreads();   // the column buffers are free
+    double det = 1.0, quad = 0.0;    // wave 0
+    int ebits = 0;
+    for (int J = 0; J < NT; ++J) {
+        int l = lane0;
+        asm volatile("" : "+v"(l));
+        T *cur = pan + (J & 1) * 16 * kTile;
+        const T *prv = pan + ((J & 1) ^ 1) * 16 * kTile;   // column J - 1 of the factor
+        struct Ops {
+            T i[4], k[4];
+        };
+        auto operands = [&](Ops &o, int I, int K) {        // of L_I,J-1 and L_K,J-1
+            const T *pI = prv + I * kTile + (l & 15) * kGpLd + (l >> 4);
+            const T *pK = prv + K * kTile + (l & 15) * kGpLd + (l >> 4);
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) { o.i[ks] = -pI[4 * ks]; o.k[ks] = pK[4 * ks]; }
+        };
+        auto multiply = [&](v4 &a, const Ops &o) {         // A_IK -= L_I,J-1 L_K,J-1^T
+#pragma unroll
+            for (int ks = 0; ks < 4; ++ks) a = M::mma(o.i[ks], o.k[ks], a);
+        };
+        // column J's tiles first
 #pragma unroll
         for (int s = 0; s < kGpSlots; ++s) {
-            const int t = w + kGpTileWaves * s;
-            int I = -1, K = 0;
-            if (t < NTT) tile_ik(t, I, K);
-            tI[s] = I;
-            tK[s] = K;
+            if (tK[s] == J) {
+                if (J > 0) {
+                    Ops o;
+                    operands(o, tI[s], J);
+                    multiply(acc[s], o);
+                }
+                store_tile<T>(acc[s], cur + tI[s] * kTile, l);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
+        __syncthreads();
+        const int rows = 16 * (NT - 1 - J);                // rows below the diagonal tile
+        if (w == 0 || kGpRowLanes * w < rows) {
+            const int below = kGpRowLanes * w + (l - 16);  // the lane's row among them
+            const bool prow = l >= 16 && l < 63 && below < rows;
+            const int row = 16 * J + (l < 16 ? l : (prow ? 16 + below : 0));
+            T *rp = cur + (row >> 4) * kTile + (row & 15) * kGpLd;
+            const T *src = l == 63 ? yb + 16 * J : rp;
+            T a[16], iv[16];
 #pragma unroll
-        for (int s = 0; s < kGpLdsSlots; ++s) lt[s] = far + (s * kGpTileWaves + w) * kTile;
+            for (int c = 0; c < 16; ++c) a[c] = src[c];
+            double p0, p1;
+            int bad;
+            eliminate<T>(a, iv, p0, p1, bad);
+            if (prow) {
 #pragma unroll
-        for (int s = 0; s < kGpRegSlots; ++s)
+                for (int c = 0; c < 16; ++c) rp[c] = a[c];
+            }
+            // y_I -= L_IJ z_J, z_J in the last lane
+            T y0 = T(0), y1 = T(0);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[s][r] = T(0);
-        {
-            // entries of the wave's tiles (a slot's four entries in a loop that is not unrolled,
-            // so the exponential's code appears once per slot)
-            const int l = lane0;
+            for (int c = 0; c < 16; c += 2) {
+                y0 += a[c] * readlane_t(a[c], 63);
+                y1 += a[c + 1] * readlane_t(a[c + 1], 63);
+            }
+            if (prow) yb[row] -= y0 + y1;
+            if (w == 0) {
+                // the determinant as mantissa and exponent, |z|^2 in the last lane
+                ebits += __builtin_amdgcn_frexp_exp(p0) + __builtin_amdgcn_frexp_exp(p1);
+                det *= __builtin_amdgcn_frexp_mant(p0) * __builtin_amdgcn_frexp_mant(p1);
+                ebits += __builtin_amdgcn_frexp_exp(det);
+                det = __builtin_amdgcn_frexp_mant(det);
+                if (l == 0 && bad) *flag = 1;
 #pragma unroll
-            for (int s = 0; s < kGpSlots; ++s) {
-                const int t = w + kGpTileWaves * s;
-                if (t < NTT) {
-                    int I, K;
-                    tile_ik(t, I, K);
-                    const int col = 16 * K + (l & 15);
-                    if (s < kGpLdsSlots) {
-#pragma unroll 1
-                        for (int r = 0; r < 4; ++r)
-                            lt[s][M::row(l, r) * kGpLd + (l & 15)] =
-                                gp_entry<T>(xs, sc, n, 16 * I + M::row(l, r), col, h);
-                    } else {
-#pragma unroll 1
-                        for (int r = 0; r < 4; ++r)
-                            acc[s - kGpLdsSlots][r] =
-                                gp_entry<T>(xs, sc, n, 16 * I + M::row(l, r), col, h);
+                for (int c = 0; c < 16; ++c) quad = fma((double)a[c], (double)a[c], quad);
+                if constexpr (refine) {
+                    if (l < 16) {
+#pragma unroll
+                        for (int c = 0; c < 16; ++c) ldg[J * kTile + l * kGpLd + c] = (float)a[c];
+                    }
+                    if (l == 63) {
+#pragma unroll
+                        for (int c = 0; c < 16; ++c) zall[16 * J + c] = (float)a[c];
+                    }
+                    if (l == 0) {
+#pragma unroll
+                        for (int c = 0; c < 16; ++c) rdg[16 * J + c] = (float)iv[c];
                     }
                 }
             }
         }
-        for (int J = -1; J < NT; ++J) {
-            // the lane index, opaque to the compiler inside each iteration: keeps the many
-            // lane-derived masks and LDS addresses of the unrolled code below from being
-            // hoisted out of the loop, where they would hold registers across all of it
+        // the tiles of the later columns take column J - 1
+        if (J > 0) {
+#pragma unroll
+            for (int s = 0; s < kGpSlots; s += 2) {   // two tiles' operands and products together
+                const int s1 = s + 1 < kGpSlots ? s + 1 : s;
+                const bool b0 = tK[s] > J, b1 = s1 > s && tK[s1] > J;
+                if (b0 || b1) {
+                    Ops o0, o1;   // (a tile that is not due reads its own, unused)
+                    operands(o0, max(tI[s], 0), max(tK[s], 0));
+                    operands(o1, max(tI[s1], 0), max(tK[s1], 0));
+                    if (b0) multiply(acc[s], o0);
+                    if (b1) multiply(acc[s1], o1);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __syncthreads();
+        if constexpr (refine) {   // the factor's tiles, kept for the solve
+#pragma unroll
+            for (int s = 0; s < kGpSlots; ++s)
+                if (tK[s] == J && tI[s] > J) load_tile<T>(acc[s], cur + tI[s] * kTile, l);
+        }
+    }
+    if (w == 0 && lane0 == 63) {
+        red[0] = 0.5 * (log(det) + (double)ebits * 0.69314718055994530942);
+        red[1] = quad;
+    }
+    if constexpr (refine) {
+        // alpha = L^{-T} z, block rows from the last: alpha_J = L_JJ^{-T} (z_J - sum_{I > J}
+        // L_IJ^T alpha_I), the products L_IJ^T alpha_I from the tiles' owners
+        for (int J = NT - 1; J >= 0; --J) {
             int l = lane0;
             asm volatile("" : "+v"(l));
-            if (J >= 0) {
-                // panel: L_IJ = A_IJ L_JJ^{-T}, and y_I -= L_IJ z_J
 #pragma unroll
-                for (int s = 0; s < kGpSlots; ++s) {
-                    if (tK[s] == J && tI[s] > J) {
-                        T *pI = pan + tI[s] * kTile;
-                        v4 a;
-                        if (s < kGpLdsSlots) load_tile<T>(a, lt[s], l);
-                        else a = acc[s - kGpLdsSlots];
-                        store_tile<T>(a, pI, l);
-                        wave_sync();
-                        v4 o;
+            for (int s = 0; s < kGpSlots; ++s) {
+                if (tK[s] == J && tI[s] > J) {
+                    float v = 0.f;
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) o[r] = T(0);
-#pragma unroll
-                        for (int ks = 0; ks < 4; ++ks) {
-                            const int ko = (l & 15) * kGpLd + 4 * ks + (l >> 4);
-                            o = M::mma(pI[ko], li[ko], o);
-                        }
-                        wave_sync();
-                        store_tile<T>(o, pI, l);
-                        if constexpr (refine) {   // the factor's tile, kept for the solve
-                            if (s < kGpLdsSlots) store_tile<T>(o, lt[s], l);
-                            else acc[s - kGpLdsSlots] = o;
-                        }
-                        const T zc = zb[l & 15];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const T sr = row_sum16(o[r] * zc);
-                            if ((l & 15) == 0) yb[16 * tI[s] + M::row(l, r)] -= sr;
-                        }
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+                    for (int r = 0; r < 4; ++r)
+                        v += (float)acc[s][r] * alpha[16 * tI[s] + M::row(l, r)];
+                    v += __shfl_xor(v, 16, 64);
+                    v += __shfl_xor(v, 32, 64);
+                    if (l < 16) part[16 * tI[s] + l] = v;
                 }
-                __syncthreads();
-            }
-            // trailing update A_IK -= L_IJ L_KJ^T for J < K <= I; the next diagonal tile first,
-            // published to the pivot wave as soon as it is final
-            const int J1 = J + 1;
-            const int tD = J1 * (J1 + 1) / 2 + J1;
-            if (J1 < NT && w == tD % kGpTileWaves) {
-                const T *pD = pan + J1 * kTile;
-#pragma unroll
-                for (int s = 0; s < kGpSlots; ++s) {
-                    if (w + kGpTileWaves * s == tD) {
-                        v4 a;
-                        if (s < kGpLdsSlots) load_tile<T>(a, lt[s], l);
-                        else a = acc[s - kGpLdsSlots];
-                        if (J >= 0) {
-#pragma unroll
-                            for (int ks = 0; ks < 4; ++ks) {
-                                const int ko = (l & 15) * kGpLd + 4 * ks + (l >> 4);
-                                a = M::mma(-pD[ko], pD[ko], a);
-                            }
-                        }
-                        store_tile<T>(a, dg, l);
-                    }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-                if (l == 0) __hip_atomic_store(dflag, J1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
-            }
-            if (J >= 0) {
-#pragma unroll
-                for (int s = 0; s < kGpSlots; ++s) {
-                    if (tK[s] > J && w + kGpTileWaves * s != tD) {
-                        const T *pI = pan + tI[s] * kTile, *pK = pan + tK[s] * kTile;
-                        v4 a;
-                        if (s < kGpLdsSlots) load_tile<T>(a, lt[s], l);
-                        else a = acc[s - kGpLdsSlots];
-#pragma unroll
-                        for (int ks = 0; ks < 4; ++ks) {
-                            const int ko = (l & 15) * kGpLd + 4 * ks + (l >> 4);
-                            a = M::mma(-pI[ko], pK[ko], a);
-                        }
-                        if (s < kGpLdsSlots) store_tile<T>(a, lt[s], l);
-                        else acc[s - kGpLdsSlots] = a;
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+                __builtin_amdgcn_sched_barrier(0);
             }
             __syncthreads();
-        }
-        if constexpr (refine) {
-            for (int J = NT - 1; J >= 0; --J) {
-                int l = lane0;
-                asm volatile("" : "+v"(l));
-                // the partial products L_IJ^T alpha_I of this wave's tiles (I, J), I > J
+            if (w == 0) {
+                // lane i: component i, with column i of L_JJ (a solve from the last row up)
+                const int i = l & 15;
+                float wv = zall[16 * J + i];
+                for (int I = J + 1; I < NT; ++I) wv -= part[16 * I + i];
+                float lc[16];
 #pragma unroll
-                for (int s = 0; s < kGpSlots; ++s) {
-                    if (tK[s] == J && tI[s] > J) {
-                        v4 a;
-                        if (s < kGpLdsSlots) load_tile<T>(a, lt[s], l);
-                        else a = acc[s - kGpLdsSlots];
-                        float v = 0.f;
+                for (int c = 0; c < 16; ++c) lc[c] = ldg[J * kTile + c * kGpLd + i];
+                const float rv = rdg[16 * J + i];
+                float al = 0.f;
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) v += (float)a[r] * alpha[16 * tI[s] + M::row(l, r)];
-                        v += __shfl_xor(v, 16, 64);
-                        v += __shfl_xor(v, 32, 64);
-                        if (l < 16) part[16 * tI[s] + l] = v;
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
+                for (int c = 15; c >= 0; --c) {
+                    const float ac = readlane_t(wv * rv, c);
+                    if (i == c) al = ac;
+                    if (i < c) wv -= lc[c] * ac;
                 }
-                __syncthreads();
-                __syncthreads();   // alpha_J from the pivot wave
+                if (l < 16) alpha[16 * J + l] = al;
             }
+            __syncthreads();
         }
     }
     __syncthreads();
     const double ld = red[0];
     double q = red[1];
-    failed = (*flag != 0);
-    timed_out = (*tflag != 0);
+    const int failed = *flag;
     if constexpr (refine) {
         // y^T K^{-1} y from the FP32 solve alpha, with the entries in FP64:
         // 2 y^T alpha - alpha^T K alpha = y^T K^{-1} y - |alpha - K^{-1} y|_K^2, exact up to a
@@ -517,7 +531,20 @@ __device__ __forceinline__ double gp_eval(const double *u, int n, unsigned char 
         q = qv;
     }
     __syncthreads();   // the LDS slots are reused by the next evaluation
-    return -0.5 * q - ld - 0.5 * (double)n * LOG_2PI;
+    return GpResult{-0.5 * q - ld - 0.5 * (double)n * LOG_2PI, failed, 0};
+}
+
+template <typename T>
+__device__ __forceinline__ double gp_eval(const double *u, int n, unsigned char *smem, bool &failed,
+                                          bool &timed_out, int spin_max = 0)
+{
+    GpPoint pt;
+#pragma unroll
+    for (int a = 0; a < kGpD; ++a) pt.u[a] = u[a];
+    const GpResult r = gp_eval_at<T>(pt, n, (lds_ptr)smem, spin_max);
+    failed = uniform_i(r.failed) != 0;
+    timed_out = uniform_i(r.timed_out) != 0;
+    return r.L;
 }
 
 __device__ __forceinline__ void gp_stage(const DevProblem &P, unsigned char *smem)
@@ -615,8 +642,10 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
     if (tid == 0) R.parents[j] = parent;
     if (tid < kGpD) sx0[tid] = R.X[(size_t)tid * R.m_pad + parent];
     double logL0 = R.logL[parent];
-    bool exact0 = true;
-    // counters (every thread keeps identical copies; thread 0 publishes them)
+    int exact0 = 1;
+    // The walk's state is the same in every thread; outcomes are made uniform where they are
+    // taken, so that it sits in scalar registers across the evaluation, whose tiles need the
+    // vector ones.  Thread 0 publishes the counters.
     unsigned long long c_evals = 0, c_tests = 0, c_prej = 0, c_outcap = 0, c_shcap = 0,
                        c_nonfin = 0, c_rc = 0, c_viol = 0, c_wait = 0;
     const int spin_max = P.gp_spin_max;
@@ -702,18 +731,19 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
         }
         double y[kGpD];
 #pragma unroll
-        for (int a = 0; a < kGpD; ++a) y[a] = (phase == PH_FINAL) ? sx0[a] : sx0[a] + t * sv[a];
-        bool in = true;
+        for (int a = 0; a < kGpD; ++a) y[a] = (phase == PH_FINAL) ? sx0[a] : fma(t, sv[a], sx0[a]);
+        int in = 1;
         if (phase != PH_FINAL) {
             ++c_tests;
             if (box) {
 #pragma unroll
-                for (int a = 0; a < kGpD; ++a) in = in && (y[a] >= P.pa[a] && y[a] <= P.pb[a]);
+                for (int a = 0; a < kGpD; ++a) in &= (y[a] >= P.pa[a] && y[a] <= P.pb[a]) ? 1 : 0;
             } else {
-                in = logprior(y) > logy;
+                in = logprior(y) > logy ? 1 : 0;
             }
         }
-        bool r = false, exact = true;
+        in = uniform_i(in);
+        int r = 0, exact = 1;
         double L = -INFINITY;
         if (!in) {
             ++c_prej;
@@ -722,21 +752,21 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
             bool failed = false, tout = false;
             if constexpr (MODE == MODE_FP64) {
                 L = gp_eval<double>(y, n, smem, failed, tout, spin_max);
-                c_wait += tout;
+                c_wait += uniform_i(tout);
             } else {
-                bool need64 = (phase == PH_FINAL);
-                if (!need64 && gp_illcond(P, y)) {   // FP64 only, no FP32 attempt
-                    need64 = true;
+                int need64 = (phase == PH_FINAL);
+                if (!need64 && uniform_i(gp_illcond(P, y))) {   // FP64 only, no FP32 attempt
+                    need64 = 1;
                     ++c_rc;
                 } else if (!need64) {
                     L = gp_eval<float>(y, n, smem, failed, tout, spin_max);
-                    c_wait += tout;
-                    need64 = (failed && !tout) || !(L == L) || gp_near(L, Lstar, P, y);
-                    if (need64) ++c_rc; else exact = false;
+                    c_wait += uniform_i(tout);
+                    need64 = uniform_i((failed && !tout) || !(L == L) || gp_near(L, Lstar, P, y));
+                    if (need64) ++c_rc; else exact = 0;
                 }
                 if (need64) {
                     L = gp_eval<double>(y, n, smem, failed, tout, spin_max);
-                    c_wait += tout;
+                    c_wait += uniform_i(tout);
                 }
             }
             if (failed) L = -INFINITY;
@@ -746,8 +776,10 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
                 break;
             }
             ++c_evals;
-            L = sanitize(L, c_nonfin);
-            r = L > Lstar;
+            const int nf = uniform_i((L != L || L == INFINITY) ? 1 : 0);
+            if (nf) L = -INFINITY;
+            c_nonfin += nf;
+            r = uniform_i(L > Lstar ? 1 : 0);
         }
         if (phase == PH_LEFT) {
             if (r) { tL -= width; ++nl; } else phase = PH_RIGHT;
@@ -757,7 +789,7 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
             ++ns;
             if (r) {
                 // every thread has passed the evaluation's barriers: sx0 is free to update
-                if (tid < kGpD) sx0[tid] = y[tid];
+                if (tid < kGpD) sx0[tid] = fma(t, sv[tid], sx0[tid]);
                 logL0 = L;
                 exact0 = exact;
                 if (R.trace && tid == 0) {
@@ -766,10 +798,9 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
                 }
                 ++st;
                 phase = PH_NEW;
-            } else if (t < 0.0) {
-                tL = t;
             } else {
-                tR = t;
+                tL = t < 0.0 ? t : tL;
+                tR = t < 0.0 ? tR : t;
             }
         }
     }
@@ -801,7 +832,8 @@ static hipError_t gp_lds(F *f, size_t bytes)
 hipError_t launch_hrss_gp(const Launch &L, int mode, hipStream_t s)
 {
     if (L.nblocks <= 0) return hipSuccess;
-    const size_t lds = (size_t)gp_lds_bytes<double>();
+    const size_t lds = (size_t)(gp_lds_bytes<double>() > gp_lds_bytes<float>() ? gp_lds_bytes<double>()
+                                                                               : gp_lds_bytes<float>());
     if (mode == MODE_FP64) {
         hipError_t e = gp_lds(k_hrss_gp<MODE_FP64>, lds);
         if (e != hipSuccess) return e;
@@ -820,7 +852,8 @@ hipError_t launch_eval_gp(const Launch &L, int mode, const double *X, int ld, in
                           int from_run, hipStream_t s)
 {
     if (L.nblocks <= 0) return hipSuccess;
-    const size_t lds = (size_t)gp_lds_bytes<double>();
+    const size_t lds = (size_t)(gp_lds_bytes<double>() > gp_lds_bytes<float>() ? gp_lds_bytes<double>()
+                                                                               : gp_lds_bytes<float>());
     if (mode == MODE_FP64) {
         hipError_t e = gp_lds(k_eval_gp<MODE_FP64>, lds);
         if (e != hipSuccess) return e;
