@@ -203,10 +203,10 @@ typedef enum {
                               * per workgroup). */
 #define NS_FLAG_SHALLOW_PLAN 64  /* every candidate is evaluated as a point, with at most 4
                                  * tests planned per round (the two bracket ends, then shrink
-                                 * proposals).  By default the slice chains of a mixture (up to
-                                 * 16 components), the funnel or the Gaussian-Rastrigin
-                                 * likelihood that read their directions from the buffer
-                                 * evaluate sixteen candidates of a step at a time along the
+                                 * proposals).  By default the chains of a mixture (up to 16
+                                 * components) or the funnel and the slice chains of the
+                                 * Gaussian-Rastrigin likelihood that read their directions from the buffer
+                                 * evaluate up to sixteen candidates at a time along each
                                  * step's line: quadratic forms are parabolas in t, held in
                                  * FP64 in every precision (no re-checks), and each chain's
                                  * final point is evaluated as a point.  Decisions and

@@ -455,8 +455,8 @@ static int dirs_blocks(const RunHost &r)
 static int hrss_blocks(const RunHost &r) { return (r.k + r.R.C - 1) / r.R.C; }  // GP: C = 1
 
 // Whether a run's chains may be evaluated along each step's line (k_hrss_line): any likelihood but
-// the GP's, slice chains with the direction buffer, one workgroup's Gram matrices in LDS
-// (sixteen components), chains long enough that a block of fifteen steps is mostly used (a
+// the GP's (nor Gaussian-Rastrigin walks), chains with the direction buffer, one workgroup's Gram
+// matrices in LDS (sixteen components), chains long enough that a block of fifteen steps is mostly used (a
 // shorter chain pays for the whole block: the products of one block cost what the batched tile
 // takes for about three steps), and parameters whose squares stay finite (an overflow to
 // infinity minus infinity would differ from the point evaluation's).
@@ -464,12 +464,12 @@ constexpr int kLineMinSteps = 4;
 constexpr double kLineMax = 1e40;
 static bool line_ok(const RunHost &rh, const ns_prior *prior, const ns_energy *en)
 {
-    if (rh.lik == LIK_GP) return false;
-    if (rh.R.rw || !rh.R.dirbuf || rh.p < kLineMinSteps) return false;
+    if (rh.lik == LIK_GP || (rh.lik == LIK_RG && rh.R.rw)) return false;
+    if (!rh.R.dirbuf || rh.p < kLineMinSteps) return false;
     if (rh.cfg.flags & NS_FLAG_SHALLOW_PLAN) return false;
     if (rh.lik == LIK_MIXTURE && rh.K > 16) return false;
     const bool box = rh.P.prior_kind == PRIOR_BOX;
-    if (line_lds_bytes(rh.D, rh.K, rh.lik, box) > 160 * 1024) return false;
+    if (line_lds_bytes(rh.D, rh.K, rh.lik, box, rh.R.rw) > 160 * 1024) return false;
     auto fits = [](double v) { return fabs(v) <= kLineMax; };
     for (int j = 0; j < rh.d; ++j)
         if (!fits(prior->a[j]) || !fits(prior->b[j]) || (!box && !fits(1.0 / prior->b[j])))
@@ -639,10 +639,10 @@ static ns_status enqueue_hrss_group(ns_ctx *ctx, size_t g, hipStream_t s)
     const Group &G = ctx->groups[g];
     const hipError_t e =
         G.lik == LIK_GP ? launch_hrss_gp(ctx->L_hrss[g], G.mode, s)
-        : G.rw          ? launch_rw(ctx->L_hrss[g], G.D, G.lik, G.mode, G.upwT, s)
-        : use_line(G)   ? launch_hrss_line(ctx->L_hrss[g], G.D, G.lik, ctx->smc,
+        : use_line(G)   ? launch_hrss_line(ctx->L_hrss[g], G.D, G.lik, ctx->smc, G.rw,
                                            G.line == 1, G.mode == MODE_FP64,
                                            plan_occupancy(ctx, ctx->L_hrss[g]), s)
+        : G.rw          ? launch_rw(ctx->L_hrss[g], G.D, G.lik, G.mode, G.upwT, s)
         : G.plan        ? launch_hrss_plan(ctx->L_hrss[g], G.D, G.mode, G.upwT, G.plan,
                                            plan_occupancy(ctx, ctx->L_hrss[g]), s)
                         : launch_hrss(ctx->L_hrss[g], G.D, G.lik, G.mode, G.upwT, s);

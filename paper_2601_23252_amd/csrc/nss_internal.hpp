@@ -122,12 +122,12 @@ hipError_t launch_hrss(const Launch &L, int D, int lik, int mode, int upw, hipSt
 hipError_t launch_hrss_plan(const Launch &L, int D, int mode, int upw, int S, int occ,
                             hipStream_t s);
 size_t hrss_plan_lds_bytes(int D, int K, int S);
-// mixture and funnel chains evaluated along each step's line in FP64 (nss_line.hip); need the
-// direction buffer; smc: tempered slices, box: the runs' priors are boxes (else Gaussian), fp64:
+// chains evaluated along each step's line in FP64 (nss_line.hip); need the direction buffer; smc:
+// tempered slices, rw: the random walk (mixtures and the funnel), box: the runs' priors are boxes (else Gaussian), fp64:
 // the run's precision is FP64, occ: workgroups per CU to compile for (1 or 2)
-hipError_t launch_hrss_line(const Launch &L, int D, int lik, int smc, int box, int fp64, int occ,
-                            hipStream_t s);
-size_t line_lds_bytes(int D, int K, int lik, int box);
+hipError_t launch_hrss_line(const Launch &L, int D, int lik, int smc, int rw, int box, int fp64,
+                            int occ, hipStream_t s);
+size_t line_lds_bytes(int D, int K, int lik, int box, int rw);
 // the random-walk replacement kernel (same grid and tile evaluators as the HRSS kernel)
 hipError_t launch_rw(const Launch &L, int D, int lik, int mode, int upw, hipStream_t s);
 hipError_t launch_logz(const Launch &L, hipStream_t s);

@@ -36,6 +36,10 @@
 // steps: 25.4 ms a launch with points and 7.4 here; a pass takes 3,000 cycles of FP64 arithmetic,
 // eight polynomials side by side for their latency (two: 8.6 ms).
 //
+// The random walk's proposals x + u_n are the same products at t = 1: a block's fifteen are tested
+// at once from the current point, and again after each acceptance (d = 50, 500 chains of 250
+// steps: 364 us a launch with points, 175 here).
+//
 // What it replaces evaluated every candidate as a point, in a tile shared by a workgroup's
 // chains, at two barriers and two to three tiles a step.  One launch with points and here:
 // d = 5, 50 chains of 25 steps 241 and 33 us; d = 32, 500 chains of 160 steps (BF16x3 points)
@@ -64,18 +68,19 @@ constexpr int kLineForms = 16;          // most components
 // t, and the shrink uniforms of a later pass; the final points' FP64 tile overlays the Gram
 // matrices.
 struct LineLayout {
-    int gram, x, v, us, tt, su, chain;  // per-chain offsets and stride (v: Gaussian-Rastrigin)
+    int gram, x, v, us, tt, su, chain;  // per-chain offsets and stride (v: Gaussian-Rastrigin's
+                                        // direction, the random walk's block of proposals)
     int mu, pa, ipb;                    // the workgroup's means and Gaussian prior (1 / std)
     int cand, q, L, mask, total;
 };
-__host__ __device__ inline LineLayout line_layout(int D, int K, int lik, bool box)
+__host__ __device__ inline LineLayout line_layout(int D, int K, int lik, bool box, bool rw)
 {
     const int forms = (lik == LIK_MIXTURE ? K : lik == LIK_RG ? 0 : 1) + (box ? 0 : 1);
     LineLayout o;
     int off = 0;
     o.gram = off; off += al16(forms * 16 * kLineLd * 8);
     o.x = off; off += al16(D * 8);
-    o.v = off; off += lik == LIK_RG ? al16(D * 8) : 0;
+    o.v = off; off += rw ? kLineB * D * 8 : lik == LIK_RG ? al16(D * 8) : 0;
     o.us = off; off += 16 * kStepU * 8;
     o.tt = off; off += 16 * 16 * 8;
     o.su = off; off += 16 * 8;
@@ -92,9 +97,9 @@ __host__ __device__ inline LineLayout line_layout(int D, int K, int lik, bool bo
     o.total = off > t ? off : t;
     return o;
 }
-size_t line_lds_bytes(int D, int K, int lik, int box)
+size_t line_lds_bytes(int D, int K, int lik, int box, int rw)
 {
-    return (size_t)line_layout(D, K, lik, box != 0).total;
+    return (size_t)line_layout(D, K, lik, box != 0, rw != 0).total;
 }
 
 // Bits of a ballot folded over the four rows: bit c = some lane of column c voted.
@@ -162,9 +167,12 @@ __device__ __forceinline__ double cos_2pi(const double (&y)[U])
     return c;
 }
 
-// NR: forms per lane (components 4 q + row, q < NR); TEMP: tempered SMC slices (no constraint);
+// The chains' kernels: slices under L > L*, tempered slices (no constraint), the random walk.
+enum { LINE_SLICE = 0, LINE_TEMPERED = 1, LINE_WALK = 2 };
+
+// NR: forms per lane (components 4 q + row, q < NR); KIND: as above;
 // BOX: the prior is a box.
-template <int D, int LIK, int NR, bool TEMP, bool BOX, int OCC>
+template <int D, int LIK, int NR, int KIND, bool BOX, int OCC>
 __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -175,7 +183,8 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
     constexpr int NA = (D + 63) / 64;
     constexpr int NJB = D / 16, NKS = D / 4;
     constexpr bool MIX = LIK == LIK_MIXTURE, RG = LIK == LIK_RG;
-    const LineLayout lay = line_layout(D, P.K, LIK, BOX);
+    constexpr bool TEMP = KIND == LINE_TEMPERED, RW = KIND == LINE_WALK;
+    const LineLayout lay = line_layout(D, P.K, LIK, BOX, RW);
     const int tid = threadIdx.x, w = uniform_i(tid >> 6), l = tid & 63;
     const int col = l & 15, row = l >> 4;
     const int d = P.d, K = MIX ? P.K : (RG ? 0 : 1), C = R.C, p = R.p;
@@ -285,6 +294,8 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             for (int i = 0; i < NA; ++i) if (l + 64 * i < D) xs[l + 64 * i] = x0r[i];
             us[l] = pus[0];
             us[l + 64] = pus[1];
+            if constexpr (RW)
+                for (int e = l; e < nb * D; e += 64) vs[e] = dirs[(size_t)s0 * D + e];
             wave_sync();
             // W column blocks in pairs (pr, NJB - 1 - pr) of equal triangular work, taken in
             // chunks of at most 20 fragments, the next chunk's requested before this one's
@@ -312,22 +323,24 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                 __builtin_amdgcn_sched_barrier(0);
             };
             if constexpr (MIX) load(wa, 0, 0);
-            // t of the first passes: columns 0, 1 the left end's next tests, 2, 3 the right
-            // end's, then four proposals after no expansion, one left, one right (four steps at
-            // a time, one per row)
-            for (int s4 = 0; s4 < nb; s4 += 4) {
-                const double *uq = us + (s4 + row) * kStepU;
-                const double tl = uq[0], tr = tl + width;
-                const int hyp = (col >> 2) - 1;
-                double sL = hyp == 1 ? tl - width : tl, sR = hyp == 2 ? tr + width : tr;
-                double t = col == 0 ? tl : (col == 1 ? tl - width : (col == 2 ? tr : tr + width));
+            if constexpr (!RW) {
+                // t of the first passes: columns 0, 1 the left end's next tests, 2, 3 the right
+                // end's, then four proposals after no expansion, one left, one right (four steps at
+                // a time, one per row)
+                for (int s4 = 0; s4 < nb; s4 += 4) {
+                    const double *uq = us + (s4 + row) * kStepU;
+                    const double tl = uq[0], tr = tl + width;
+                    const int hyp = (col >> 2) - 1;
+                    double sL = hyp == 1 ? tl - width : tl, sR = hyp == 2 ? tr + width : tr;
+                    double t = col == 0 ? tl : (col == 1 ? tl - width : (col == 2 ? tr : tr + width));
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const double tq = fma(uq[2 + q], sR - sL, sL);
-                    if (col >= 4 && (col & 3) == q) t = tq;
-                    if (tq < 0.0) sL = tq; else sR = tq;
+                    for (int q = 0; q < 4; ++q) {
+                        const double tq = fma(uq[2 + q], sR - sL, sL);
+                        if (col >= 4 && (col & 3) == q) t = tq;
+                        if (tq < 0.0) sL = tq; else sR = tq;
+                    }
+                    tt[(s4 + row) * 16 + col] = t;
                 }
-                tt[(s4 + row) * 16 + col] = t;
             }
             double luh = 0.0;
             if (TEMP || !BOX) luh = log(us[col * kStepU + 1]);
@@ -432,9 +445,114 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             }
             if (!BOX) hp = gpri[15 * kLineLd + col];
             if (s0 + kLineB < p) fetch_block(s0 + kLineB);
+            unsigned n_tests = 0, n_evals = 0;
+
+            if constexpr (RW) {
+                // ---- the block's proposals ----
+                // x + v_c for every proposal c at once (t = 1), from the current point: up to the
+                // first acceptance they are the tests the walk makes; then the point's products
+                // move by that proposal's row and the later proposals are tested again
+                double dg[NR], dgp = 0.0, v0c = 0.0;
+#pragma unroll
+                for (int q = 0; q < NR; ++q) {
+                    const int c = 4 * q + row < K ? 4 * q + row : 0;
+                    dg[q] = gram[(c * 16 + col) * kLineLd + col];
+                }
+                if (!BOX) dgp = gpri[col * kLineLd + col];
+                if constexpr (!MIX) v0c = vs[min(col, kLineB - 1) * D];
+                double big[NA];   // the block's longest move of each coordinate
+#pragma unroll
+                for (int i = 0; i < NA; ++i) big[i] = 0.0;
+                if (BOX)
+                    for (int c = 0; c < nb; ++c)
+#pragma unroll
+                        for (int i = 0; i < NA; ++i)
+                            if (l + 64 * i < D) big[i] = fmax(big[i], fabs(vs[c * D + l + 64 * i]));
+                for (int at = 0; at < nb;) {
+                    const unsigned todo = ((1u << nb) - 1u) & ~((1u << at) - 1u);
+                    unsigned okm = todo, in;
+                    if constexpr (BOX) {
+                        // (rounding is monotone: where the longest move stays inside, all do)
+                        bool all = true;
+#pragma unroll
+                        for (int i = 0; i < NA; ++i)
+                            all = all && x0r[i] + big[i] <= pbr[i] && x0r[i] - big[i] >= par[i];
+                        if (!__all(all)) {
+                            okm = 0;
+                            for (int c = at; c < nb; ++c) {
+                                bool ib = true;
+#pragma unroll
+                                for (int i = 0; i < NA; ++i) {
+                                    if (l + 64 * i < d) {
+                                        const double y = x0r[i] + vs[c * D + l + 64 * i];
+                                        ib = ib && y >= par[i] && y <= pbr[i];
+                                    }
+                                }
+                                okm |= (__all(ib) ? 1u : 0u) << c;
+                            }
+                        }
+                    } else {
+                        okm &= (unsigned)__ballot(-0.5 * fma(2.0, hp, dgp) > luh);
+                    }
+                    if constexpr (MIX) {
+                        double lc[NR];
+                        bool hit = false, amb = false;
+#pragma unroll
+                        for (int q = 0; q < NR; ++q) {
+                            lc[q] = cst[q] - 0.5 * (aa[q] + fma(2.0, h[q], dg[q]));
+                            hit = hit || lc[q] > Lstar;
+                            amb = amb || lc[q] > Lamb;
+                        }
+                        in = fold_rows(__ballot(hit));
+                        const unsigned doubt = fold_rows(__ballot(amb)) & ~in & okm;
+                        if (doubt) {
+                            double se = 0.0;
+#pragma unroll
+                            for (int q = 0; q < NR; ++q) se += exp(lc[q] - Lstar);
+                            se += __shfl_xor(se, 16, 64);
+                            se += __shfl_xor(se, 32, 64);
+                            in |= (unsigned)__ballot(se > 1.0) & doubt;
+                        }
+                    } else {
+                        const double s2 = fmax(aa[0] + fma(2.0, h[0], dg[0]), 0.0);
+                        const double vv = lane_value(x0r[0], 0) + v0c;
+                        const double Lc = -vv * vv / 18.0 - 0.5 * (LOG_2PI + log(9.0)) -
+                                          0.5 * exp(-vv) * s2 -
+                                          (double)(d - 1) * 0.5 * (vv + LOG_2PI);
+                        in = (unsigned)__ballot(Lc > Lstar);
+                    }
+                    const unsigned ac = in & okm;
+                    const int s = ac ? __builtin_ctz(ac) : nb - 1;
+                    const unsigned cons = todo & ((2u << s) - 1u);
+                    n_tests += __builtin_popcount(cons);
+                    n_evals += __builtin_popcount(cons & okm);
+                    if (R.trace && l < 16 && ((cons >> l) & 1u)) {
+                        int *tr = R.trace + ((size_t)j * p + s0 + l) * 4;
+                        tr[0] = 0; tr[1] = 0; tr[2] = (okm >> l) & 1u; tr[3] = ac && l == s;
+                    }
+                    if (ac) {
+                        moved = true;
+#pragma unroll
+                        for (int i = 0; i < NA; ++i)
+                            if (l + 64 * i < D) x0r[i] += vs[s * D + l + 64 * i];
+#pragma unroll
+                        for (int q = 0; q < NR; ++q) {
+                            const int c = 4 * q + row < K ? 4 * q + row : 0;
+                            const double hs = __shfl(h[q], (l & 48) | s, 64);
+                            aa[q] += fma(2.0, hs, __shfl(dg[q], (l & 48) | s, 64));
+                            h[q] += gram[(c * 16 + s) * kLineLd + col];
+                        }
+                        if (!BOX) hp += gpri[s * kLineLd + col];
+                    }
+                    at = s + 1;
+                }
+                c_tests += n_tests;
+                c_evals += n_evals;
+                wave_sync();   // the block's LDS is rewritten
+                continue;
+            }
 
             // ---- the block's steps ----
-            unsigned n_tests = 0, n_evals = 0;
             double tn = tt[col], grn[NR], gpn = 0.0;   // the next step's, read ahead
 #pragma unroll
             for (int q = 0; q < NR; ++q)
@@ -809,14 +927,11 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
     }
 }
 
-template <int D, int LIK, int NR, int OCC>
-static hipError_t line_o(const Launch &L, int smc, int box, int fp64, hipStream_t s)
+template <int D, int LIK, int NR, int KIND, bool BOX, int OCC>
+static hipError_t line_l(const Launch &L, int fp64, hipStream_t s)
 {
-    const size_t lds = line_lds_bytes(D, L.max_K, LIK, box);
-    auto f = smc ? (box ? k_hrss_line<D, LIK, NR, true, true, OCC>
-                        : k_hrss_line<D, LIK, NR, true, false, OCC>)
-                 : (box ? k_hrss_line<D, LIK, NR, false, true, OCC>
-                        : k_hrss_line<D, LIK, NR, false, false, OCC>);
+    const size_t lds = line_lds_bytes(D, L.max_K, LIK, BOX, KIND == LINE_WALK);
+    auto f = k_hrss_line<D, LIK, NR, KIND, BOX, OCC>;
     hipError_t e = hipFuncSetAttribute((const void *)f,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
@@ -827,36 +942,53 @@ static hipError_t line_o(const Launch &L, int smc, int box, int fp64, hipStream_
 // Workgroups per CU of the register allocation: a mixture's W fragments in flight do not fit 256
 // registers at D = 64 and 128, and a launch that leaves one workgroup per CU loses nothing by
 // taking more.
-template <int D, int LIK, int NR>
-static hipError_t line_t(const Launch &L, int smc, int box, int fp64, int occ, hipStream_t s)
+template <int D, int LIK, int NR, int KIND, bool BOX>
+static hipError_t line_b(const Launch &L, int fp64, int occ, hipStream_t s)
 {
     if constexpr (LIK == LIK_MIXTURE && D >= 64)
-        if (occ == 1) return line_o<D, LIK, NR, 1>(L, smc, box, fp64, s);
-    return line_o<D, LIK, NR, 2>(L, smc, box, fp64, s);
+        if (occ == 1) return line_l<D, LIK, NR, KIND, BOX, 1>(L, fp64, s);
+    return line_l<D, LIK, NR, KIND, BOX, 2>(L, fp64, s);
+}
+
+template <int D, int LIK, int NR>
+static hipError_t line_t(const Launch &L, int kind, int box, int fp64, int occ, hipStream_t s)
+{
+    if constexpr (LIK != LIK_RG)
+        if (kind == LINE_WALK)
+            return box ? line_b<D, LIK, NR, LINE_WALK, true>(L, fp64, occ, s)
+                       : line_b<D, LIK, NR, LINE_WALK, false>(L, fp64, occ, s);
+    if (kind == LINE_TEMPERED)
+        return box ? line_b<D, LIK, NR, LINE_TEMPERED, true>(L, fp64, occ, s)
+                   : line_b<D, LIK, NR, LINE_TEMPERED, false>(L, fp64, occ, s);
+    if (kind == LINE_SLICE)
+        return box ? line_b<D, LIK, NR, LINE_SLICE, true>(L, fp64, occ, s)
+                   : line_b<D, LIK, NR, LINE_SLICE, false>(L, fp64, occ, s);
+    return hipErrorInvalidValue;
 }
 
 template <int D>
-static hipError_t line_d(const Launch &L, int lik, int smc, int box, int fp64, int occ,
+static hipError_t line_d(const Launch &L, int lik, int kind, int box, int fp64, int occ,
                          hipStream_t s)
 {
-    if (lik == LIK_FUNNEL) return line_t<D, LIK_FUNNEL, 1>(L, smc, box, fp64, occ, s);
-    if (lik == LIK_RG) return line_t<D, LIK_RG, 1>(L, smc, box, fp64, occ, s);
+    if (lik == LIK_FUNNEL) return line_t<D, LIK_FUNNEL, 1>(L, kind, box, fp64, occ, s);
+    if (lik == LIK_RG) return line_t<D, LIK_RG, 1>(L, kind, box, fp64, occ, s);
     if constexpr (D <= 128) {
-        if (L.max_K <= 4) return line_t<D, LIK_MIXTURE, 1>(L, smc, box, fp64, occ, s);
-        if (L.max_K <= 8) return line_t<D, LIK_MIXTURE, 2>(L, smc, box, fp64, occ, s);
-        if (L.max_K <= kLineForms) return line_t<D, LIK_MIXTURE, 4>(L, smc, box, fp64, occ, s);
+        if (L.max_K <= 4) return line_t<D, LIK_MIXTURE, 1>(L, kind, box, fp64, occ, s);
+        if (L.max_K <= 8) return line_t<D, LIK_MIXTURE, 2>(L, kind, box, fp64, occ, s);
+        if (L.max_K <= kLineForms) return line_t<D, LIK_MIXTURE, 4>(L, kind, box, fp64, occ, s);
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_hrss_line(const Launch &L, int D, int lik, int smc, int box, int fp64, int occ,
-                            hipStream_t s)
+hipError_t launch_hrss_line(const Launch &L, int D, int lik, int smc, int rw, int box, int fp64,
+                            int occ, hipStream_t s)
 {
     if (L.nblocks <= 0) return hipSuccess;
-    if (D == 32) return line_d<32>(L, lik, smc, box, fp64, occ, s);
-    if (D == 64) return line_d<64>(L, lik, smc, box, fp64, occ, s);
-    if (D == 128) return line_d<128>(L, lik, smc, box, fp64, occ, s);
-    if (D == 320) return line_d<320>(L, lik, smc, box, fp64, occ, s);
+    const int kind = rw ? LINE_WALK : smc ? LINE_TEMPERED : LINE_SLICE;
+    if (D == 32) return line_d<32>(L, lik, kind, box, fp64, occ, s);
+    if (D == 64) return line_d<64>(L, lik, kind, box, fp64, occ, s);
+    if (D == 128) return line_d<128>(L, lik, kind, box, fp64, occ, s);
+    if (D == 320) return line_d<320>(L, lik, kind, box, fp64, occ, s);
     return hipErrorInvalidValue;
 }
 

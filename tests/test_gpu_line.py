@@ -89,6 +89,26 @@ def test_rastrigin(N, d, alpha):
     _same(N, G.rastrigin_gauss(d, alpha, m=100, k=41, p=20))
 
 
+@pytest.mark.parametrize("p", [4, 15, 37])
+@pytest.mark.parametrize("name", ["box2", "gauss17", "mix5_d33", "mix9_d20", "illcond50",
+                                  "funnel9", "funnel70", "mixed64"])
+def test_random_walk(N, name, p):
+    """Proposals are tested a block at a time; the box cases start on wide contours (most
+    proposals outside) and, with a small scale, move often within a block."""
+    from paper_2601_23252_amd import problems as G
+    prob, kw = {
+        "box2": lambda: (G.gaussian_problem(2, np.zeros(2), 0.04 * np.eye(2), m=90, k=33), {}),
+        "gauss17": lambda: (G.config2(7, d=17, m=90, k=33), {}),
+        "mix5_d33": lambda: (G.mixture_problem(5, 33, 5, m=90, k=33), dict(width=0.05)),
+        "mix9_d20": lambda: (G.mixture_problem(9, 20, 9, m=90, k=33), {}),
+        "illcond50": lambda: (G.illcond_gaussian(50, m=90, k=33), dict(width=0.02)),
+        "funnel9": lambda: (G.funnel(9, m=90, k=33), dict(width=0.3)),
+        "funnel70": lambda: (G.funnel(70, m=90, k=33), {}),
+        "mixed64": lambda: (G.mixture_problem(3, 64, 2, m=90, k=33), dict(precision="bf16x3")),
+    }[name]()
+    _same(N, prob, p=p, replacement="rw", **kw)
+
+
 @pytest.mark.parametrize("target", ["gauss", "mixture", "funnel", "rastrigin"])
 def test_tempered(N, target):
     from paper_2601_23252_amd import problems as G
@@ -110,13 +130,13 @@ def test_tempered(N, target):
 
 
 def test_limits_take_the_general_path(N):
-    """Seventeen components, a prior whose squares could overflow and a random walk still run
+    """Seventeen components, a prior whose squares could overflow and a Rastrigin random walk run
     (on the point-evaluating kernels)."""
     from paper_2601_23252_amd import problems as G
     _same(N, G.mixture_problem(8, 16, 17, m=80, k=20), p=9, iters=2)
     wide = G.gaussian_problem(4, np.zeros(4), np.eye(4), "box", -1e60, 1e60, m=80, k=20)
     _same(N, wide, p=9, iters=1)
-    _same(N, G.config1(), replacement="rw", iters=2)
+    _same(N, G.rastrigin_gauss(5, 0.5, m=80, k=20, p=9), replacement="rw", iters=2)
 
 
 def test_null_chains_keep_their_parents_value(N):
