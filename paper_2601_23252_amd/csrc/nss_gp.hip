@@ -28,6 +28,7 @@
 //
 //  k_hrss_gp   one HRSS chain per workgroup (App. A.6), candidates evaluated one at a time
 //  k_eval_gp   one point per workgroup (initial live set, tests)
+#include "nss_chol.hpp"
 #include "nss_internal.hpp"
 #include "nss_rng.hpp"
 #include "nss_wave.hpp"
@@ -43,8 +44,6 @@ constexpr int kGpThreads = 64 * kGpWaves;
 constexpr int kGpMaxTiles = 136;                                      // 16 * 17 / 2
 constexpr int kGpSlots = kGpMaxTiles / kGpWaves;                      // tiles per wave
 constexpr int kGpRowLanes = 47;        // panel rows of a wave's elimination (lanes 16..62)
-constexpr int kGpLd = 17;                                             // LDS tile row stride
-constexpr int kTile = 16 * kGpLd;
 constexpr int kGpD = 6;                                               // hyperparameters
 
 // LDS: inputs and targets (FP64), reduction slots, then the factorisation's tiles in T
@@ -62,41 +61,6 @@ constexpr int gp_lds_bytes()
     // partial products of a block step
     return kOffT + (int)sizeof(T) * (2 * 16 * kTile + kGpMaxObs) +
            (sizeof(T) == 4 ? 4 * (16 * kTile + 3 * kGpMaxObs + 16 * 16) : 0);
-}
-
-template <typename T> struct Mf;
-template <> struct Mf<double> {
-    typedef double v4 __attribute__((ext_vector_type(4)));
-    __device__ static v4 mma(double a, double b, v4 c)
-    {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    // accumulator row of register r in lane l (column l & 15)
-    __device__ static int row(int l, int r) { return (l >> 4) + 4 * r; }
-};
-template <> struct Mf<float> {
-    typedef float v4 __attribute__((ext_vector_type(4)));
-    __device__ static v4 mma(float a, float b, v4 c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    __device__ static int row(int l, int r) { return 4 * (l >> 4) + r; }
-};
-
-__device__ __forceinline__ double readlane_t(double v, int lane) { return readlane_d(v, lane); }
-__device__ __forceinline__ float readlane_t(float v, int lane)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
-}
-
-// lower tile index t = I (I + 1) / 2 + K  ->  (I, K), K <= I
-__device__ __forceinline__ void tile_ik(int t, int &I, int &K)
-{
-    int i = (int)((sqrtf(8.f * (float)t + 1.f) - 1.f) * 0.5f);
-    while (i * (i + 1) / 2 > t) --i;
-    while ((i + 1) * (i + 2) / 2 <= t) ++i;
-    I = i;
-    K = t - i * (i + 1) / 2;
 }
 
 struct GpTheta {
@@ -168,62 +132,6 @@ __device__ __forceinline__ T gp_entry(const double *xs, const double *sc, int n,
                     pa[0] * pb[1] - pa[1] * pb[0], pa[2] * pb[3] - pa[3] * pb[2], h);
     if (row == col) v += (T)h.sn2;
     return v;
-}
-
-template <typename T, typename V>
-__device__ __forceinline__ void store_tile(const V &acc, T *p, int l)
-{
-#pragma unroll
-    for (int r = 0; r < 4; ++r) p[Mf<T>::row(l, r) * kGpLd + (l & 15)] = acc[r];
-}
-template <typename T, typename V>
-__device__ __forceinline__ void load_tile(V &acc, const T *p, int l)
-{
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc[r] = p[Mf<T>::row(l, r) * kGpLd + (l & 15)];
-}
-
-// 1/sqrt(x) from the hardware estimate r, for a short dependent chain per pivot: with
-// e = 1 - x r^2, r (1 + e/2 + 3 e^2/8) has the relative error 5 e^3 / 16 (e is about 2^-23 in FP64;
-// FP32 takes Newton's r (1 + e/2)).
-__device__ __forceinline__ double rsq_refined(double x)
-{
-    const double r = __builtin_amdgcn_rsq(x);
-    const double e = fma(-(x * r), r, 1.0);
-    return fma(r * e, fma(e, 0.375, 0.5), r);
-}
-__device__ __forceinline__ float rsq_refined(float x)
-{
-    float r = __builtin_amdgcn_rsqf(x);
-    return r * (1.5f - 0.5f * x * r * r);
-}
-
-// Eliminates block column J with one row per lane (see above): a[c] is the lane's row, lane i < 16
-// row i of the diagonal tile.  On return lane i < 16 holds row i of the factor (its entries above
-// the diagonal are not meaningful), the other lanes their row times the transposed inverse
-// factor.  iv: reciprocal pivots' roots; p0, p1: the products of the first and last eight pivots;
-// bad: a pivot was not positive (the results are then not meaningful).
-template <typename T>
-__device__ __forceinline__ void eliminate(T (&a)[16], T (&iv)[16], double &p0, double &p1, int &bad)
-{
-    p0 = p1 = 1.0;
-    bad = 0;
-#pragma unroll
-    for (int jj = 0; jj < 16; ++jj) {
-        T piv = readlane_t(a[jj], jj);
-        asm volatile("" : "+v"(piv));
-        bad |= piv > T(0) ? 0 : 1;
-        if (jj < 8) p0 *= (double)piv; else p1 *= (double)piv;
-        const T r = rsq_refined(piv);
-        iv[jj] = r;
-        a[jj] *= r;
-#pragma unroll
-        for (int c = jj + 1; c < 16; ++c) a[c] -= a[jj] * readlane_t(a[jj], c);
-        // every row takes this column now: left to itself the compiler sinks the updates to
-        // their columns' turns and keeps all the lane reads until then
-#pragma unroll
-        for (int c = jj + 1; c < 16; ++c) asm volatile("" : "+v"(a[c]));
-    }
 }
 
 // log N(y; 0, K_theta + sigma_n^2 I) at u = log theta with the factorisation in T.  Called by
@@ -360,8 +268,8 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
             T i[4], k[4];
         };
         auto operands = [&](Ops &o, int I, int K) {        // of L_I,J-1 and L_K,J-1
-            const T *pI = prv + I * kTile + (l & 15) * kGpLd + (l >> 4);
-            const T *pK = prv + K * kTile + (l & 15) * kGpLd + (l >> 4);
+            const T *pI = prv + I * kTile + (l & 15) * kTileLd + (l >> 4);
+            const T *pK = prv + K * kTile + (l & 15) * kTileLd + (l >> 4);
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks) { o.i[ks] = -pI[4 * ks]; o.k[ks] = pK[4 * ks]; }
         };
@@ -388,7 +296,7 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
             const int below = kGpRowLanes * w + (l - 16);  // the lane's row among them
             const bool prow = l >= 16 && l < 63 && below < rows;
             const int row = 16 * J + (l < 16 ? l : (prow ? 16 + below : 0));
-            T *rp = cur + (row >> 4) * kTile + (row & 15) * kGpLd;
+            T *rp = cur + (row >> 4) * kTile + (row & 15) * kTileLd;
             const T *src = l == 63 ? yb + 16 * J : rp;
             T a[16], iv[16];
 #pragma unroll
@@ -420,7 +328,7 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
                 if constexpr (refine) {
                     if (l < 16) {
 #pragma unroll
-                        for (int c = 0; c < 16; ++c) ldg[J * kTile + l * kGpLd + c] = (float)a[c];
+                        for (int c = 0; c < 16; ++c) ldg[J * kTile + l * kTileLd + c] = (float)a[c];
                     }
                     if (l == 63) {
 #pragma unroll
@@ -487,7 +395,7 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
                 for (int I = J + 1; I < NT; ++I) wv -= part[16 * I + i];
                 float lc[16];
 #pragma unroll
-                for (int c = 0; c < 16; ++c) lc[c] = ldg[J * kTile + c * kGpLd + i];
+                for (int c = 0; c < 16; ++c) lc[c] = ldg[J * kTile + c * kTileLd + i];
                 const float rv = rdg[16 * J + i];
                 float al = 0.f;
 #pragma unroll

@@ -2,13 +2,10 @@
 //
 //  k_init_draw   prior draws of the m initial live points (Philox purpose INIT)
 //  k_eval        batched likelihood of n points, 16 rows per workgroup (init, tests)
-//  k_select      delete-k: sort (logL, index), threshold L*, unrolled evidence update of the
-//                k deaths, dead record, termination flag (Sec. 2.1; App. D.2.1)
-//  k_cov/k_chol  whitening: survivors' covariance + jitter, lower Cholesky factor (Sec. 3.2)
 //  k_hrss        the k HRSS chains (App. A.6): one wave runs one chain's finite-state machine
 //                (direction, bracket, step-out, shrink), the four waves of a workgroup
 //                evaluate the tile of up to 16 candidate rows together on MFMA
-//  k_logz        final live-set contribution to the evidence (Sec. 2.1)
+//  k_rw          the random-walk chains
 #include "nss_internal.hpp"
 #include "nss_rng.hpp"
 #include "nss_tiles.hpp"
@@ -85,478 +82,6 @@ __global__ __launch_bounds__(256) void k_eval(Launch Lc, const double *X, int ld
         const double L = (MODE == MODE_FP64) ? T.L[tid] : (double)T.L32[tid];
         out[p0 + tid] = sanitize(L, nf);
         if (nf && nonfinite) atomicAdd(nonfinite, nf);
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// delete-k, threshold, unrolled evidence, termination (one workgroup of 1024 threads)
-// ------------------------------------------------------------------------------------------
-__device__ __forceinline__ unsigned long long key_of(double x)
-{
-    if (x == 0.0) x = 0.0;  // -0 -> +0
-    const unsigned long long b = __double_as_longlong(x);
-    return (b >> 63) ? ~b : (b | 0x8000000000000000ull);
-}
-__device__ __forceinline__ double val_of(unsigned long long k)
-{
-    const unsigned long long b = (k >> 63) ? (k & 0x7FFFFFFFFFFFFFFFull) : ~k;
-    return __longlong_as_double(b);
-}
-
-// Block reductions over 1024 threads (16 waves); red has >= 16 doubles.
-__device__ __forceinline__ double block_sum(double v, double *red)
-{
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    v = wave_sum(v);
-    __syncthreads();
-    if (l == 0) red[w] = v;
-    __syncthreads();
-    double s = 0.0;
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s += red[i];
-    return s;
-}
-__device__ __forceinline__ double block_max(double v, double *red)
-{
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    v = wave_max(v);
-    __syncthreads();
-    if (l == 0) red[w] = v;
-    __syncthreads();
-    double s = -INFINITY;
-    for (int i = 0; i < (int)(blockDim.x >> 6); ++i) s = fmax(s, red[i]);
-    return s;
-}
-// Exclusive prefix sum over the block.
-__device__ __forceinline__ double block_exscan(double v, double *red)
-{
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    double inc = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const double t = __shfl_up(inc, o, 64);
-        if (l >= o) inc += t;
-    }
-    __syncthreads();
-    if (l == 63) red[w] = inc;
-    __syncthreads();
-    double pre = 0.0;
-    for (int i = 0; i < w; ++i) pre += red[i];
-    return pre + inc - v;
-}
-
-// packed lower-triangular index e = a(a+1)/2 + b  ->  (a, b)
-__device__ __forceinline__ void unpack_tri(int e, int &a, int &b)
-{
-    a = (int)((sqrt(8.0 * e + 1.0) - 1.0) * 0.5);
-    while (a * (a + 1) / 2 > e) --a;
-    while ((a + 1) * (a + 2) / 2 <= e) ++a;
-    b = e - a * (a + 1) / 2;
-}
-
-__device__ __forceinline__ double lse2(double a, double b)
-{
-    if (a == -INFINITY) return b;
-    if (b == -INFINITY) return a;
-    const double mx = fmax(a, b);
-    return mx + log(exp(a - mx) + exp(b - mx));
-}
-
-__global__ __launch_bounds__(1024) void k_select(Launch Lc, int op)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const DevRun R = Lc.R[Lc.map[blockIdx.x].x];
-    if (R.iscal[0]) return;
-    const int m = R.m, k = R.k, tid = threadIdx.x;
-    int NP = 1;
-    while (NP < m) NP <<= 1;
-    unsigned long long *key = (unsigned long long *)smem;
-    int *idx = (int *)(key + NP);
-    double *red = (double *)(idx + NP + (NP & 1));
-    int *st0 = (int *)(red + 32);
-    for (int t = tid; t < NP; t += blockDim.x) {
-        if (t < m) { key[t] = key_of(R.logL[t]); idx[t] = t; }
-        else { key[t] = ~0ull; idx[t] = 0x7FFFFFFF; }
-    }
-    if (tid == 0) *st0 = m;
-    __syncthreads();
-    // bitonic sort of (key, idx) ascending
-    for (int size = 2; size <= NP; size <<= 1) {
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int t = tid; t < (NP >> 1); t += blockDim.x) {
-                const int i = 2 * t - (t & (stride - 1));
-                const int j = i + stride;
-                const bool asc = ((i & size) == 0);
-                const unsigned long long ki = key[i], kj = key[j];
-                const int ii = idx[i], ij = idx[j];
-                const bool gt = (ki > kj) || (ki == kj && ii > ij);
-                if (gt == asc) { key[i] = kj; key[j] = ki; idx[i] = ij; idx[j] = ii; }
-            }
-            __syncthreads();
-        }
-    }
-    for (int t = tid; t < m; t += blockDim.x) R.perm[t] = idx[t];
-    const double Lstar = val_of(key[k - 1]);
-    for (int t = k + tid; t < m; t += blockDim.x)
-        if (val_of(key[t]) > Lstar) atomicMin(st0, t);
-    if (op == 2) {
-        __syncthreads();
-        if (tid == 0) {
-            R.scal[0] = Lstar;
-            R.iscal[1] = *st0;
-            R.iscal[2] = m - *st0;
-        }
-        return;
-    }
-    // unrolled deaths j = 1..k at live counts n_j = m - j + 1
-    const double logZ0 = R.scal[1], logX0 = R.scal[2], M0 = R.scal[3];
-    const int E = (k + (int)blockDim.x - 1) / (int)blockDim.x;
-    const int j0 = tid * E;
-    double ssum = 0.0;
-    for (int e = 0; e < E; ++e) {
-        const int jj = j0 + e + 1;
-        if (jj <= k) ssum += 1.0 / (double)(m - jj + 1);
-    }
-    const double pre = block_exscan(ssum, red);
-    double lwv[8], Lv[8];
-    double lmax = -INFINITY, run = pre;
-    for (int e = 0; e < E; ++e) {
-        const int jj = j0 + e + 1;
-        lwv[e] = -INFINITY; Lv[e] = 0.0;
-        if (jj <= k) {
-            const double inv = 1.0 / (double)(m - jj + 1);
-            const double L = val_of(key[jj - 1]);
-            const double lw = L + (logX0 - run) + log(-expm1(-inv));
-            run += inv;
-            lwv[e] = lw; Lv[e] = L;
-            lmax = fmax(lmax, lw);
-        }
-    }
-    const double S_k = block_sum(ssum, red);
-    const double mx = block_max(lmax, red);
-    double es = 0.0;
-    for (int e = 0; e < E; ++e) if (lwv[e] != -INFINITY) es += exp(lwv[e] - mx);
-    const double esum = block_sum(es, red);
-    const double lse_new = (mx == -INFINITY) ? -INFINITY : mx + log(esum);
-    const double logZ1 = lse2(logZ0, lse_new);
-    double mt = 0.0;
-    for (int e = 0; e < E; ++e) if (lwv[e] != -INFINITY) mt += exp(lwv[e] - logZ1) * Lv[e];
-    const double msum = block_sum(mt, red);
-    const double M1 = (logZ0 == -INFINITY ? 0.0 : exp(logZ0 - logZ1) * M0) + msum;
-    const double logX1 = logX0 - S_k;
-    // dead record
-    const long long nd0 = (long long)R.ctr[9];
-    for (int t = tid; t < k; t += blockDim.x)
-        if (nd0 + t < R.dead_cap) R.dead[nd0 + t] = val_of(key[t]);
-    if (R.deadx) {   // NS_FLAG_RECORD_POINTS: the dead points' coordinates, point-major [n][d]
-        const int d = Lc.P[Lc.map[blockIdx.x].x].d;
-        for (long long e = tid; e < (long long)k * d; e += blockDim.x) {
-            const int t = (int)(e / d), a = (int)(e - (long long)t * d);
-            if (nd0 + t < R.dead_cap)
-                R.deadx[(nd0 + t) * d + a] = R.X[(size_t)a * R.m_pad + idx[t]];
-        }
-    }
-    __syncthreads();
-    if (tid == 0) {
-        const int t0 = *st0;
-        const double maxL = val_of(key[m - 1]);
-        int done = (R.term_on && (logX1 + maxL - logZ1 < R.log_term)) ? 1 : 0;
-        R.scal[0] = Lstar; R.scal[1] = logZ1; R.scal[2] = logX1; R.scal[3] = M1;
-        R.iscal[1] = t0;
-        R.iscal[2] = m - t0;
-        if (!done && m - t0 <= 0) { R.iscal[4] = 1; done = 1; }
-        R.iscal[0] = done;
-        if (op == 1) R.iscal[3] += 1;
-        R.ctr[9] = (unsigned long long)(nd0 + k);
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// whitening: survivors' covariance (one-pass about a fixed shift c = the best live point),
-// partial sums over groups of survivors, then a single-workgroup reduction + Cholesky
-// ------------------------------------------------------------------------------------------
-// grid (tile, group); tile = lower 16x16 block (ta >= tb).  part2[g][tile][256], part1[g][D]
-__global__ __launch_bounds__(256) void k_cov(Launch Lc)
-{
-    const int2 bm = Lc.map[blockIdx.x];
-    const DevProblem P = Lc.P[bm.x];
-    const DevRun R = Lc.R[bm.x];
-    if (R.iscal[0]) return;
-    // frozen whitening: the first iteration's factor, or one the caller supplied, is kept
-    if (R.freeze && (R.iscal[3] > 0 || R.iscal[6])) return;
-    const int d = P.d;
-    const int nt = P.D / 16, ntile = nt * (nt + 1) / 2;
-    const int G = R.covG;
-    double *part1 = R.part1, *part2 = R.part2;
-    const int tile = bm.y % ntile, g = bm.y / ntile, tid = threadIdx.x;
-    int ta, tb;
-    unpack_tri(tile, ta, tb);
-    const int off = R.smc ? 0 : R.k;   // SMC: every particle
-    const int n = R.m - off;
-    const int s0 = (int)((long long)n * g / G), s1 = (int)((long long)n * (g + 1) / G);
-    const int cidx = R.perm[R.m - 1];
-    __shared__ double ca[32][17], cb[32][17];
-    __shared__ double shift[32];
-    if (tid < 16) {
-        const int aa = ta * 16 + tid, bb = tb * 16 + tid;
-        shift[tid] = (aa < d) ? R.X[(size_t)aa * R.m_pad + cidx] : 0.0;
-        shift[16 + tid] = (bb < d) ? R.X[(size_t)bb * R.m_pad + cidx] : 0.0;
-    }
-    __syncthreads();
-    double acc = 0.0, acc1 = 0.0;
-    for (int sb = s0; sb < s1; sb += 32) {
-        // stage up to 32 survivors: columns of tile a and tile b
-        for (int i = tid; i < 32 * 32; i += 256) {
-            const int s = i >> 5, c = i & 31;
-            const int ss = sb + s;
-            double v = 0.0;
-            if (ss < s1) {
-                const int pi = R.perm[off + ss];
-                const int coord = (c < 16) ? ta * 16 + c : tb * 16 + (c - 16);
-                if (coord < d) v = R.X[(size_t)coord * R.m_pad + pi] - shift[c];
-            }
-            if (c < 16) ca[s][c] = v; else cb[s][c - 16] = v;
-        }
-        __syncthreads();
-        const int ns = (s1 - sb < 32) ? s1 - sb : 32;
-        for (int s = 0; s < ns; ++s) acc += ca[s][tid & 15] * cb[s][tid >> 4];
-        if (ta == tb && tid < 16)
-            for (int s = 0; s < ns; ++s) acc1 += ca[s][tid];
-        __syncthreads();
-    }
-    part2[((size_t)g * ntile + tile) * 256 + tid] = acc;
-    if (ta == tb && tid < 16) part1[(size_t)g * P.D + ta * 16 + tid] = acc1;
-}
-
-__global__ __launch_bounds__(1024) void k_chol(Launch Lc)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int2 bm = Lc.map[blockIdx.x];
-    const DevProblem P = Lc.P[bm.x];
-    const DevRun R = Lc.R[bm.x];
-    if (R.iscal[0]) return;
-    if (R.freeze && (R.iscal[3] > 0 || R.iscal[6])) return;
-    const int G = R.covG, ntile = (P.D / 16) * (P.D / 16 + 1) / 2;
-    const double *part1 = R.part1, *part2 = R.part2;
-    const int D = P.D, d = P.d, tid = threadIdx.x;
-    // packed lower triangle, D(D+1)/2: in LDS up to D = 128, else worked in place in the run's
-    // packed factor (global memory, coherent within the workgroup across its barriers)
-    double *A = D <= 128 ? (double *)smem : R.Lpk;
-    double *mc = (double *)smem + (D <= 128 ? D * (D + 1) / 2 : 0);   // mean - shift, [D]
-    double *red = mc + D;                    // [32]
-    int *fail = (int *)(red + 32);
-    const int n = R.smc ? R.m : R.m - R.k;
-    for (int a = tid; a < D; a += blockDim.x) {
-        double s = 0.0;
-        if (a < d) for (int g = 0; g < G; ++g) s += part1[(size_t)g * D + a];
-        mc[a] = s / n;
-    }
-    if (tid == 0) *fail = 0;
-    __syncthreads();
-    const int np = D * (D + 1) / 2;
-    for (int e = tid; e < np; e += blockDim.x) {
-        int a, b;  // a >= b
-        unpack_tri(e, a, b);
-        double v = 0.0;
-        if (a < d && b < d && (a == b || !R.diag)) {   // the diagonal metric needs variances only
-            const int ta = a >> 4, tb = b >> 4;
-            const int tile = ta * (ta + 1) / 2 + tb;
-            const int off = (b & 15) * 16 + (a & 15);
-            double s = 0.0;
-            for (int g = 0; g < G; ++g) s += part2[((size_t)g * ntile + tile) * 256 + off];
-            v = s / n - mc[a] * mc[b];
-        } else if (a == b) {
-            v = 1.0;  // padded coordinates: identity (never used, keeps the factor regular)
-        }
-        A[e] = v;
-    }
-    __syncthreads();
-    // jitter: 1e-12 * tr / d on the diagonal
-    double tr = 0.0;
-    for (int a = tid; a < d; a += blockDim.x) tr += A[a * (a + 1) / 2 + a];
-    tr = block_sum(tr, red);
-    for (int a = tid; a < d; a += blockDim.x) A[a * (a + 1) / 2 + a] += 1e-12 * tr / d;
-    __syncthreads();
-    // right-looking Cholesky on the packed lower triangle; for the diagonal metric it reduces
-    // to the square roots of the (jittered) variances, taken directly
-    if (R.diag) {
-        for (int a = tid; a < d; a += blockDim.x) {
-            const double v = A[a * (a + 1) / 2 + a];
-            if (!(v > 0.0)) *fail = 1;
-            else A[a * (a + 1) / 2 + a] = sqrt(v);
-        }
-        __syncthreads();
-    } else
-    for (int j = 0; j < d; ++j) {
-        const double ajj = A[j * (j + 1) / 2 + j];
-        if (!(ajj > 0.0)) { if (tid == 0) *fail = 1; break; }
-        const double ljj = sqrt(ajj);
-        __syncthreads();
-        for (int i = j + 1 + tid; i < d; i += blockDim.x) A[i * (i + 1) / 2 + j] /= ljj;
-        __syncthreads();
-        if (tid == 0) A[j * (j + 1) / 2 + j] = ljj;
-        const int rem = d - j - 1;
-        for (int e = tid; e < rem * rem; e += blockDim.x) {
-            const int ii = e / rem, r2 = e - ii * rem;
-            if (r2 > ii) continue;
-            const int i = j + 1 + ii, l2 = j + 1 + r2;
-            A[i * (i + 1) / 2 + l2] -= A[i * (i + 1) / 2 + j] * A[l2 * (l2 + 1) / 2 + j];
-        }
-        __syncthreads();
-    }
-    __syncthreads();
-    const int failed = *fail;
-    if (failed) {
-        // diagonal fallback: sqrt of the (jittered) variances, recomputed from the partials
-        for (int e = tid; e < np; e += blockDim.x) A[e] = 0.0;
-        __syncthreads();
-        for (int a = tid; a < d; a += blockDim.x) {
-            const int ta = a >> 4;
-            const int tile = ta * (ta + 1) / 2 + ta;
-            const int off = (a & 15) * 16 + (a & 15);
-            double s = 0.0;
-            for (int g = 0; g < G; ++g) s += part2[((size_t)g * ntile + tile) * 256 + off];
-            const double v = s / n - mc[a] * mc[a];
-            A[a * (a + 1) / 2 + a] = (v > 0.0) ? sqrt(v) : 1.0;
-        }
-        if (tid == 0) atomicAdd(&R.ctr[8], 1ull);
-    }
-    __syncthreads();
-    for (int a = d; a < D; ++a)
-        if (tid == 0) A[a * (a + 1) / 2 + a] = 0.0;  // padded coordinates never move
-    for (int e = tid; e < np; e += blockDim.x) {
-        int a, b;
-        unpack_tri(e, a, b);
-        R.Lpk[e] = (a < d && b < d) ? A[e] : 0.0;
-    }
-    for (int e = tid; e < D * D; e += blockDim.x) {
-        const int a = e / D, b = e - a * D;
-        R.Lsig[e] = (b <= a && a < d) ? A[a * (a + 1) / 2 + b] : 0.0;
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// directions of every chain and step of the iteration (they do not depend on the chains'
-// outcomes): z ~ N(0, I_d) from Philox purpose DIR, v = L z / |z| (unit Mahalanobis length;
-// random-walk runs: the proposal step v = s L z), dirbuf[(j p + s) D + a], zero for a >= d.
-// 64 directions per workgroup.
-// ------------------------------------------------------------------------------------------
-// directions per k_dirs workgroup: 64, or 32 at D = 320 (their normals fill the LDS)
-__host__ __device__ constexpr int dir_rows(int D) { return D > 128 ? 32 : 64; }
-__host__ __device__ inline int dirs_lds_bytes(int D)
-{
-    const int rows = dir_rows(D);
-    return al16(rows * (D + 1) * 8) + rows * 8 + rows * kStepU * 8 + 2 * rows * 4;
-}
-
-// The normals and uniforms are drawn by all threads; v = L z is one small FP64 MFMA product per
-// workgroup: wave w takes directions 16w..16w+15 as the B operand (lane l: direction
-// 16w + (l & 15), coordinate 4ks + (l >> 4)) against L as the A operand (read from the run's
-// row-major factor, cached; only the normals occupy LDS), and gets
-// V[16w + (l & 15)][16t + (l >> 4) + 4i] in register i of tile t; the lower-triangular L skips
-// k-steps above each tile.  The results go back through the wave's own rows of the normals
-// buffer so that the stores to the direction buffer are whole rows.
-template <int D>
-__global__ __launch_bounds__(256) void k_dirs(Launch Lc)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int2 bm = Lc.map[blockIdx.x];
-    const DevProblem P = Lc.P[bm.x];
-    const DevRun R = Lc.R[bm.x];
-    if (R.iscal[0] || R.iscal[2] <= 0) return;
-    constexpr int LDZ = D + 1, ROWS = dir_rows(D);
-    double *zs = (double *)smem;
-    double *nz = zs + ROWS * LDZ;
-    double *udraw = nz + ROWS;              // [ROWS][kStepU] raw uniforms
-    int *rj = (int *)(udraw + ROWS * kStepU);   // chain of each row (-1 past the end)
-    int *rs = rj + ROWS;                    // step of each row
-    const int tid = threadIdx.x, d = P.d, p = R.p;
-    const long long total = (long long)R.k * p;
-    const long long base = (long long)bm.y * ROWS;
-    const uint32_t it = (uint32_t)R.iscal[3] + 1u;
-    if (tid < ROWS) {
-        const long long idx = base + tid;
-        int j = -1, st = 0;
-        if (idx < total) { j = (int)(idx / p); st = (int)(idx - (long long)j * p); }
-        rj[tid] = j;
-        rs[tid] = st;
-    }
-    __syncthreads();
-    const int nq = (d + 1) >> 1;
-    for (int i = tid; i < ROWS * nq; i += 256) {
-        const int r = i / nq, q = i - r * nq;
-        const int j = rj[r];
-        if (j < 0) continue;
-        double ua, ub, z0, z1;
-        draw2(R.key0, R.key1, PUR_DIR, (uint32_t)j, it, (uint32_t)rs[r], (uint32_t)q, ua, ub);
-        box_muller(ua, ub, z0, z1);
-        zs[r * LDZ + 2 * q] = z0;
-        if (2 * q + 1 < d) zs[r * LDZ + 2 * q + 1] = z1;
-    }
-    // The step's uniforms: ubuf[0] = tL0 = -w U, ubuf[1] = the height uniform uh (purpose
-    // STEP), ubuf[2 + i] = the uniform of the i-th shrink proposal (purpose SHRINK, draw i).
-    for (int i = tid; i < ROWS * kStepU; i += 256) {
-        const int r = i / kStepU, q = i - r * kStepU;
-        const int j = rj[r], st = rs[r];
-        if (j < 0) continue;
-        double ua, ub;
-        if (q < 2) {
-            draw2(R.key0, R.key1, PUR_STEP, (uint32_t)j, it, (uint32_t)st, 0u, ua, ub);
-            udraw[r * kStepU + q] = (q == 0) ? ua : ub;
-        } else {
-            draw2(R.key0, R.key1, PUR_SHRINK, (uint32_t)j, it, (uint32_t)st, (uint32_t)(q - 2), ua, ub);
-            udraw[r * kStepU + q] = ua;
-        }
-    }
-    __syncthreads();
-    if (tid < ROWS && rj[tid] >= 0) {
-        const double *u = udraw + tid * kStepU;
-        double *o = R.ubuf + (base + tid) * kStepU;
-        o[0] = -R.width * u[0];
-        for (int q = 1; q < kStepU; ++q) o[q] = u[q];
-    }
-    const int w = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
-    if (16 * w >= ROWS) return;   // D = 320: two waves hold the 32 directions
-    const int r = 16 * w + li;
-    // |z| of the wave's 16 directions: four partial sums per direction, then lane exchanges
-    double s2 = 0.0;
-    for (int a = lk; a < d; a += 4) {
-        const double z = zs[r * LDZ + a];
-        s2 += z * z;
-    }
-    s2 += __shfl_xor(s2, 16, 64);
-    s2 += __shfl_xor(s2, 32, 64);
-    const double nrm = sqrt(s2);
-    constexpr int NT = D / 16, NKS = D / 4;
-    d4 acc[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = (d4){0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-        const int b = 4 * ks + lk;
-        const double bz = (b < d) ? zs[r * LDZ + b] : 0.0;
-#pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            if (ks < 4 * t + 4) {   // L is zero above its diagonal
-                const double la = R.Lsig[(16 * t + li) * D + b];
-                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(la, bz, acc[t], 0, 0, 0);
-            }
-        }
-    }
-    // HRSS: unit Mahalanobis length; random walk: the proposal step s L z
-    wave_sync();   // this wave's reads of its rows are done
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int a = 16 * t + lk + 4 * i;
-            zs[r * LDZ + a] = (a < d) ? (R.rw ? acc[t][i] * R.width : acc[t][i] / nrm) : 0.0;
-        }
-    }
-    wave_sync();
-    for (int e = l; e < 16 * D; e += 64) {
-        const int rr = e / D, a = e - rr * D;
-        const int row = 16 * w + rr;
-        if (rj[row] >= 0) R.dirbuf[(base + row) * D + a] = zs[row * LDZ + a];
     }
 }
 
@@ -1253,169 +778,6 @@ __global__ __launch_bounds__(256) void k_rw(Launch Lc)
 }
 
 // ------------------------------------------------------------------------------------------
-// adaptive tempered SMC (the slice-sampling mutation runs in k_hrss with R.smc set)
-// ------------------------------------------------------------------------------------------
-// One workgroup per run.  op 0: start at beta = 0 (identity order, log Z = 0).  op 1 (the
-// start of a step): the next inverse temperature by 50 bisection steps on the ESS of the
-// incremental weights exp((b - beta) (logL - max logL)) (target rho m, or beta = 1), the log
-// mean incremental weight added to log Z, systematic resampling with one uniform (purpose
-// RESAMPLE, counter (0, step)) against the cumulative normalised weights, and the gather of
-// the resampled particles into slots 0..m-1.  op 2 (the end of a step): the step count, and
-// done once beta = 1.  scal[0] = beta, scal[1] = log Z; iscal[5] = this step reached beta = 1.
-// The step's draws (resampling, directions, chains) use iteration number iscal[3] + 1.
-constexpr int kSmcPer = kMaxLive / kSelectThreads;   // particles per thread, contiguous
-
-__global__ __launch_bounds__(kSelectThreads) void k_smc(Launch Lc, int op)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ double red[32];
-    const int2 bm = Lc.map[blockIdx.x];
-    const DevProblem P = Lc.P[bm.x];
-    const DevRun R = Lc.R[bm.x];
-    const int m = R.m, tid = threadIdx.x;
-    if (op == 0) {
-        for (int i = tid; i < m; i += blockDim.x) R.perm[i] = i;
-        if (tid == 0) {
-            R.scal[0] = 0.0; R.scal[1] = 0.0; R.scal[2] = 0.0; R.scal[3] = 0.0;
-            R.iscal[1] = 0; R.iscal[2] = m; R.iscal[5] = 0;
-        }
-        return;
-    }
-    if (op == 2) {   // the step's draws used iteration number iscal[3] + 1
-        if (tid == 0 && !R.iscal[0]) {
-            R.iscal[3] += 1;
-            if (R.iscal[5]) R.iscal[0] = 1;
-        }
-        return;
-    }
-    if (R.iscal[0]) return;
-    double *cum = (double *)smem;                         // [m]
-    int *par = (int *)(smem + (size_t)kMaxLive * 8);      // [m]
-    const double beta = R.scal[0];
-    const int i0 = tid * kSmcPer;
-    double Lr[kSmcPer];
-    double lmax = -INFINITY;
-#pragma unroll
-    for (int q = 0; q < kSmcPer; ++q) {
-        Lr[q] = (i0 + q < m) ? R.logL[i0 + q] : -INFINITY;
-        lmax = fmax(lmax, Lr[q]);
-    }
-    lmax = block_max(lmax, red);
-    if (!(lmax > -INFINITY)) {   // every particle has log L = -inf: nothing to weigh
-        if (tid == 0) { R.iscal[4] = 1; R.iscal[0] = 1; }
-        return;
-    }
-    auto ess = [&](double b) -> double {
-        double s1 = 0.0, s2 = 0.0;
-#pragma unroll
-        for (int q = 0; q < kSmcPer; ++q) {
-            if (Lr[q] > -INFINITY) {
-                const double e = exp((b - beta) * (Lr[q] - lmax));
-                s1 += e;
-                s2 += e * e;
-            }
-        }
-        s1 = block_sum(s1, red);
-        s2 = block_sum(s2, red);
-        return s1 * s1 / s2;
-    };
-    const double target = R.ess_frac * m;
-    double nb = 1.0;
-    if (ess(1.0) < target) {
-        double lo = beta, hi = 1.0;
-        for (int t = 0; t < 50; ++t) {
-            const double mid = 0.5 * (lo + hi);
-            if (ess(mid) >= target) lo = mid; else hi = mid;
-        }
-        nb = lo > beta ? lo : hi;
-    }
-    const double db = nb - beta;
-    double w[kSmcPer], loc = 0.0;
-#pragma unroll
-    for (int q = 0; q < kSmcPer; ++q) {
-        w[q] = (Lr[q] > -INFINITY) ? exp(db * (Lr[q] - lmax)) : 0.0;
-        loc += w[q];
-    }
-    const double pre = block_exscan(loc, red);
-    const double sw = block_sum(loc, red);
-    double c = pre;
-#pragma unroll
-    for (int q = 0; q < kSmcPer; ++q) {
-        c += w[q];
-        if (i0 + q < m) cum[i0 + q] = c / sw;
-    }
-    const uint32_t it = (uint32_t)R.iscal[3] + 1u;
-    double u, unused;
-    draw2(R.key0, R.key1, PUR_RESAMPLE, 0u, it, 0u, 0u, u, unused);
-    __syncthreads();
-    // parent of slot j: the first particle whose cumulative weight reaches (u + j) / m
-    for (int j = tid; j < m; j += blockDim.x) {
-        const double pos = (u + j) / m;
-        int lo = 0, hi = m - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (cum[mid] >= pos) hi = mid; else lo = mid + 1;
-        }
-        par[j] = lo;
-        R.parents[j] = lo;
-    }
-    __syncthreads();
-    // gather through the scratch copy, then back into the live arrays
-    const int d = P.d;
-    for (long long e = tid; e < (long long)d * m; e += blockDim.x) {
-        const int a = (int)(e / m), j = (int)(e - (long long)a * m);
-        R.Xtmp[(size_t)a * R.m_pad + j] = R.X[(size_t)a * R.m_pad + par[j]];
-    }
-    for (int j = tid; j < m; j += blockDim.x) R.Ltmp[j] = R.logL[par[j]];
-    __syncthreads();
-    for (long long e = tid; e < (long long)d * m; e += blockDim.x) {
-        const int a = (int)(e / m), j = (int)(e - (long long)a * m);
-        R.X[(size_t)a * R.m_pad + j] = R.Xtmp[(size_t)a * R.m_pad + j];
-    }
-    for (int j = tid; j < m; j += blockDim.x) R.logL[j] = R.Ltmp[j];
-    if (tid == 0) {
-        R.scal[0] = nb;
-        R.scal[1] += db * lmax + log(sw) - log((double)m);
-        R.iscal[1] = 0;
-        R.iscal[2] = m;
-        R.iscal[5] = (nb == 1.0) ? 1 : 0;
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// final live-set contribution (non-destructive): scal[4..6] = ln Z, sqrt(H/m), H
-// ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(1024) void k_logz(Launch Lc)
-{
-    const DevRun R = Lc.R[Lc.map[blockIdx.x].x];
-    __shared__ double red[32];
-    const int m = R.m, k = R.k, n = m - k, tid = threadIdx.x;
-    double mx = -INFINITY;
-    for (int t = k + tid; t < m; t += blockDim.x) mx = fmax(mx, R.logL[R.perm[t]]);
-    mx = block_max(mx, red);
-    double s = 0.0;
-    for (int t = k + tid; t < m; t += blockDim.x) s += exp(R.logL[R.perm[t]] - mx);
-    s = block_sum(s, red);
-    const double logZ = R.scal[1], logX = R.scal[2], M = R.scal[3];
-    const double lme = mx + log(s) - log((double)n);
-    const double zf = lse2(logZ, logX + lme);
-    double mt = 0.0;
-    for (int t = k + tid; t < m; t += blockDim.x) {
-        const double L = R.logL[R.perm[t]];
-        const double lw = logX - log((double)n) + L;
-        if (lw != -INFINITY) mt += exp(lw - zf) * L;
-    }
-    mt = block_sum(mt, red);
-    if (tid == 0) {
-        const double Mf = (logZ == -INFINITY ? 0.0 : exp(logZ - zf) * M) + mt;
-        const double H = Mf - zf;
-        R.scal[4] = zf;
-        R.scal[5] = sqrt(H > 0.0 ? H / m : 0.0);
-        R.scal[6] = H;
-    }
-}
-
-// ------------------------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------------------------
 // register fragment units per wave: whole components (K >= 4) or spread blocks (K < 4)
@@ -1435,7 +797,6 @@ int upw_template(int D, int upw)
 }
 
 size_t hrss_lds_bytes(int D, int K) { return (size_t)hrss_layout(D, K).total; }
-int dirs_rows(int D) { return dir_rows(D); }
 
 int mode_supported(const DevProblem &P, int mode)
 {
@@ -1564,66 +925,4 @@ hipError_t launch_rw(const Launch &L, int D, int lik, int mode, int upw, hipStre
     NSS_DISPATCH(rw_t, L, s);
 }
 
-hipError_t launch_smc(const Launch &L, int op, hipStream_t s)
-{
-    if (L.nblocks <= 0) return hipSuccess;
-    const size_t lds = (size_t)kMaxLive * 12;
-    hipError_t e = set_lds(k_smc, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_smc, dim3(L.nblocks), dim3(kSelectThreads), lds, s, L, op);
-    return hipGetLastError();
-}
-
-hipError_t launch_select(const Launch &L, int op, hipStream_t s)
-{
-    if (L.nblocks <= 0) return hipSuccess;
-    int NP = 1;
-    while (NP < L.max_m) NP <<= 1;
-    const size_t lds = (size_t)NP * 8 + (size_t)(NP + (NP & 1)) * 4 + 32 * 8 + 16;
-    hipError_t e = set_lds(k_select, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_select, dim3(L.nblocks), dim3(kSelectThreads), lds, s, L, op);
-    return hipGetLastError();
-}
-
-hipError_t launch_cov(const Launch &cov, const Launch &one, int D, hipStream_t s)
-{
-    if (one.nblocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_cov, dim3(cov.nblocks), dim3(256), 0, s, cov);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    const int Dl = D <= 128 ? D : 128;   // runs above 128 keep their factor in global memory
-    const size_t lds = (size_t)(Dl * (Dl + 1) / 2 + D + 32) * 8 + 16;
-    e = set_lds(k_chol, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_chol, dim3(one.nblocks), dim3(1024), lds, s, one);
-    return hipGetLastError();
-}
-
-template <int D>
-static hipError_t dirs_t(const Launch &L, hipStream_t s)
-{
-    const size_t lds = (size_t)dirs_lds_bytes(D);
-    hipError_t e = set_lds(k_dirs<D>, lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_dirs<D>, dim3(L.nblocks), dim3(256), lds, s, L);
-    return hipGetLastError();
-}
-
-hipError_t launch_dirs(const Launch &L, int D, hipStream_t s)
-{
-    if (L.nblocks <= 0) return hipSuccess;
-    if (D == 32) return dirs_t<32>(L, s);
-    if (D == 64) return dirs_t<64>(L, s);
-    if (D == 128) return dirs_t<128>(L, s);
-    if (D == 320) return dirs_t<320>(L, s);
-    return hipErrorInvalidValue;
-}
-
-hipError_t launch_logz(const Launch &L, hipStream_t s)
-{
-    if (L.nblocks <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_logz, dim3(L.nblocks), dim3(1024), 0, s, L);
-    return hipGetLastError();
-}
 }  // namespace nss
