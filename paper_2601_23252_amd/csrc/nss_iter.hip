@@ -639,23 +639,28 @@ __global__ __launch_bounds__(1024) void k_chol_wide(Launch Lc)
 // directions of every chain and step of the iteration (they do not depend on the chains'
 // outcomes): z ~ N(0, I_d) from Philox purpose DIR, v = L z / |z| (unit Mahalanobis length;
 // random-walk runs: the proposal step v = s L z), dirbuf[(j p + s) D + a], zero for a >= d.
-// 64 directions per workgroup.
+// 64 directions per workgroup (32 from D = 128).
 // ------------------------------------------------------------------------------------------
-// directions per k_dirs workgroup: 64, or 32 at D = 320 (their normals fill the LDS)
-__host__ __device__ constexpr int dir_rows(int D) { return D > 128 ? 32 : 64; }
+// directions per k_dirs workgroup: 64, or 32 from D = 128 (at 320 their normals fill the LDS)
+__host__ __device__ constexpr int dir_rows(int D) { return D > 64 ? 32 : 64; }
 __host__ __device__ inline int dirs_lds_bytes(int D)
 {
     const int rows = dir_rows(D);
     return al16(rows * (D + 1) * 8) + rows * 8 + rows * kStepU * 8 + 2 * rows * 4;
 }
 
-// The normals and uniforms are drawn by all threads; v = L z is one small FP64 MFMA product per
-// workgroup: wave w takes directions 16w..16w+15 as the B operand (lane l: direction
-// 16w + (l & 15), coordinate 4ks + (l >> 4)) against L as the A operand (read from the run's
-// row-major factor, cached; only the normals occupy LDS), and gets
-// V[16w + (l & 15)][16t + (l >> 4) + 4i] in register i of tile t; the lower-triangular L skips
-// k-steps above each tile.  The results go back through the wave's own rows of the normals
-// buffer so that the stores to the direction buffer are whole rows.
+// The normals and uniforms are drawn by all threads; V = L Z is one small FP64 MFMA product per
+// workgroup.  The row tiles of L go to the waves in pairs (t, NT - 1 - t) of equal triangular work,
+// each with all the workgroup's directions or its share of them, so that L is read once per
+// workgroup (as the A operand, from the run's row-major factor; the normals in LDS are the B
+// operand, lane l: direction 16 g + (l & 15), coordinate 4 ks + (l >> 4)).  Register i of a tile's
+// result is V[16 t + (l >> 4) + 4 i][16 g + (l & 15)]; the results go back through the normals'
+// rows so that the stores to the direction buffer are whole rows.  What bounds it is the vector
+// arithmetic of the generator, log, sine and cosine, then the product and the stores, one after the
+// other in a workgroup: 32 directions a workgroup at D >= 128 keep four workgroups on a compute
+// unit at different ones (64: 3.75 ms against 3.56 for 64 runs of d <= 128 and 250 chains; with L
+// read by every wave for 16 directions, as before, 5.59 ms; 1.25e6 directions of d = 100: 1.88 ms
+// then, 1.10 now).
 template <int D>
 __global__ __launch_bounds__(256) void k_dirs(Launch Lc)
 {
@@ -711,53 +716,93 @@ __global__ __launch_bounds__(256) void k_dirs(Launch Lc)
     __syncthreads();
     if (tid < ROWS && rj[tid] >= 0) {
         const double *u = udraw + tid * kStepU;
-        double *o = R.ubuf + (base + tid) * kStepU;
+        const auto o = as_global(R.ubuf) + (base + tid) * kStepU;
         o[0] = -R.width * u[0];
         for (int q = 1; q < kStepU; ++q) o[q] = u[q];
     }
     const int w = tid >> 6, l = tid & 63, li = l & 15, lk = l >> 4;
-    if (16 * w >= ROWS) return;   // D = 320: two waves hold the 32 directions
-    const int r = 16 * w + li;
-    // |z| of the wave's 16 directions: four partial sums per direction, then lane exchanges
-    double s2 = 0.0;
-    for (int a = lk; a < d; a += 4) {
-        const double z = zs[r * LDZ + a];
-        s2 += z * z;
+    // |z| of 16 directions a wave: four partial sums per direction, then lane exchanges; HRSS
+    // scales to unit Mahalanobis length, the random walk by the proposal's s
+    if (16 * w < ROWS) {
+        const int r = 16 * w + li;
+        double s2 = 0.0;
+        for (int a = lk; a < d; a += 4) {
+            const double z = zs[r * LDZ + a];
+            s2 += z * z;
+        }
+        s2 += __shfl_xor(s2, 16, 64);
+        s2 += __shfl_xor(s2, 32, 64);
+        if (lk == 0) nz[r] = sqrt(s2);
     }
-    s2 += __shfl_xor(s2, 16, 64);
-    s2 += __shfl_xor(s2, 32, 64);
-    const double nrm = sqrt(s2);
-    constexpr int NT = D / 16, NKS = D / 4;
-    d4 acc[NT];
+    constexpr int NT = D / 16, NPR = NT / 2, NG = ROWS / 16;   // row tiles, pairs, column groups
+    constexpr int WPP = NPR < 4 ? 4 / NPR : 1;                 // waves per pair
+    constexpr int GPW = NG / WPP < 1 ? 1 : NG / WPP;           // column groups per wave
+    constexpr int PPW = (NPR + 3) / 4;                         // pairs per wave
+    const auto L = as_global((const double *)R.Lsig) + li * D + lk;
+    d4 acc[PPW][2][GPW];
+    const int g0 = (w % WPP) * GPW;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = (d4){0.0, 0.0, 0.0, 0.0};
+    for (int q = 0; q < PPW; ++q) {
+        const int pr = w / WPP + 4 * q;
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-        const int b = 4 * ks + lk;
-        const double bz = (b < d) ? zs[r * LDZ + b] : 0.0;
+        for (int g = 0; g < GPW; ++g) acc[q][0][g] = acc[q][1][g] = (d4){0.0, 0.0, 0.0, 0.0};
+        if (pr >= NPR) continue;
+        const int ta = pr, tb = NT - 1 - pr;
+        const auto La = L + 16 * ta * D, Lb = L + 16 * tb * D;
+        const int na = 4 * ta + 4, nb = 4 * tb + 4;            // L is zero above its diagonal
+        // four k-steps of both tiles requested at a time
+        for (int k0 = 0; k0 < nb; k0 += 4) {
+            double a0[4], a1[4], z[GPW][4];
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-            if (ks < 4 * t + 4) {   // L is zero above its diagonal
-                const double la = R.Lsig[(16 * t + li) * D + b];
-                acc[t] = __builtin_amdgcn_mfma_f64_16x16x4f64(la, bz, acc[t], 0, 0, 0);
+            for (int i = 0; i < 4; ++i) {
+                a1[i] = Lb[4 * (k0 + i)];
+                a0[i] = k0 < na ? La[4 * (k0 + i)] : 0.0;
+#pragma unroll
+                for (int g = 0; g < GPW; ++g) {
+                    const int bb = 4 * (k0 + i) + lk;
+                    z[g][i] = bb < d ? zs[(16 * (g0 + g) + li) * LDZ + bb] : 0.0;
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int g = 0; g < GPW; ++g) {
+                    acc[q][1][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a1[i], z[g][i], acc[q][1][g], 0, 0, 0);
+                    if (k0 < na)
+                        acc[q][0][g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a0[i], z[g][i], acc[q][0][g], 0, 0, 0);
+                }
+        }
+    }
+    __syncthreads();   // every wave has read the normals
+#pragma unroll
+    for (int q = 0; q < PPW; ++q) {
+        const int pr = w / WPP + 4 * q;
+        if (pr >= NPR) continue;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int t = h ? NT - 1 - pr : pr;
+#pragma unroll
+            for (int g = 0; g < GPW; ++g) {
+                const int r = 16 * (g0 + g) + li;
+                const double n = nz[r], sc = R.rw ? R.width : 1.0 / n;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int a = 16 * t + lk + 4 * i;
+                    const double y = acc[q][h][g][i];
+                    double v = y * sc;
+                    if (!R.rw) v = fma(fma(-v, n, y), sc, v);   // the quotient y / n
+                    zs[r * LDZ + a] = a < d ? v : 0.0;
+                }
             }
         }
     }
-    // HRSS: unit Mahalanobis length; random walk: the proposal step s L z
-    wave_sync();   // this wave's reads of its rows are done
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int a = 16 * t + lk + 4 * i;
-            zs[r * LDZ + a] = (a < d) ? (R.rw ? acc[t][i] * R.width : acc[t][i] / nrm) : 0.0;
-        }
-    }
-    wave_sync();
-    for (int e = l; e < 16 * D; e += 64) {
+    __syncthreads();
+    const auto out = as_global(R.dirbuf) + base * D;
+    const long long left = total - base;
+    const int nrow = left < ROWS ? (int)left : ROWS;
+    for (int e = tid; e < nrow * D; e += 256) {
         const int rr = e / D, a = e - rr * D;
-        const int row = 16 * w + rr;
-        if (rj[row] >= 0) R.dirbuf[(base + row) * D + a] = zs[row * LDZ + a];
+        out[e] = zs[rr * LDZ + a];
     }
 }
 
