@@ -10,15 +10,15 @@
 // g); the trapezoid element X_g (1 - t_g t_{g+1}) / 2 with t_N = 0 (X after the last death is 0);
 // log w = beta logL + log dX (the tempered term is 0 at beta = 0).
 //
-// Nothing of size R x N is stored: the shrinkages are counter-based, so they are drawn twice.
-//  k_geom_sums     grid (chunk, replica group): sum of log t over each chunk of kGeomC deaths,
-//                  per replica
+// Nothing of size R x N is stored, and every shrinkage is drawn once: a chunk of deaths is worked
+// relative to log X at its own first death, which enters the log weights and evidence terms as a
+// summand afterwards.
+//  k_geom_chunks   grid (chunk, replica group), a wave each: keeps its chunk's live counts and
+//                  likelihood factors in registers, loops over the group's replicas, draws log t,
+//                  and per replica stores the chunk's sum of log t and its (max, sum) of the
+//                  evidence; per death the sums over the group's replicas that the mean needs
 //  k_geom_offsets  one workgroup per replica: exclusive scan of the chunk sums (log X at each
 //                  chunk's first death)
-//  k_geom_weights  grid (chunk, replica group): each workgroup keeps its chunk's logL and live
-//                  counts in registers, loops over the group's replicas, rebuilds log X inside
-//                  the chunk, forms the log weights, accumulates them per death for the mean and
-//                  emits per-wave (max, sum) partials of each replica's evidence
 //  k_geom_mean     per death: mean of the log weights over the replicas; per-wave ESS partials
 //  k_geom_final    one workgroup per replica combines its evidence partials; one more combines
 //                  the ESS partials
@@ -33,10 +33,10 @@ namespace nss {
 namespace {
 
 constexpr uint32_t PUR_GEOM = 6;
-constexpr int kGeomT = 256;                 // threads per workgroup
-constexpr int kGeomE = 4;                   // consecutive deaths per thread (even)
-constexpr int kGeomC = kGeomT * kGeomE;     // deaths per chunk
-constexpr int kGeomW = kGeomT / 64;         // waves per workgroup
+constexpr int kGeomE = 8;                   // consecutive deaths per lane (even)
+constexpr int kGeomC = 64 * kGeomE;         // deaths per chunk
+constexpr int kGeomT = 256;                 // threads of the scan
+constexpr int kGeomW = kGeomT / 64;
 constexpr double kLn2 = 0.69314718055994530942;
 
 struct GeomArgs {
@@ -44,12 +44,12 @@ struct GeomArgs {
     const double *logL;   // [m] live logL, ascending through perm
     const int *perm;      // [m]; the final survivors are perm[k..m-1]
     long long n_dead, N;
-    int m, k, R, nchunk, rpg;  // rpg: replicas per group in k_geom_weights
+    int m, k, R, nchunk, rpg;  // rpg: replicas per group in k_geom_chunks
     double beta;
     uint32_t key0, key1;
     double *csum;      // [R][nchunk] chunk sums of log t, scanned in place into offsets
-    double2 *zpart;    // [R][nchunk * kGeomW] per-wave (max, sum) of the evidence terms
-    double *accp;      // [groups][N] per-group sums of log w over replicas
+    double2 *zpart;    // [R][nchunk] (max, sum) of the evidence terms, X relative to the chunk's
+    double *accp;      // [groups][N] per-group sums of log w over replicas, likewise relative
     double *logw_mean; // [N]
     double4 *epart;    // [ceil(N / 64)] per-wave (max, sum, sum of squares) of mean weights
     double *logz;      // [R]
@@ -68,18 +68,73 @@ __device__ __forceinline__ double death_logL(const GeomArgs &a, int g)
     return g < (int)a.n_dead ? a.dead[g] : a.logL[a.perm[a.k + (g - (int)a.n_dead)]];
 }
 
-// log t for the kGeomE consecutive deaths g0 .. g0+kGeomE-1 (g0 even) of replica r; rn holds the
-// reciprocal live counts (0 past the last death, which makes those shrinkages exactly 1).
-__device__ __forceinline__ void draw_logt(const GeomArgs &a, int r, int g0, const double *rn,
-                                          double *s)
+// beta logL (the tempered term is 0 at beta = 0)
+__device__ __forceinline__ double tempered(const GeomArgs &a, int g)
 {
+    return a.beta == 0.0 ? 0.0 : a.beta * death_logL(a, g);
+}
+
+// The constants of log_uniform and exp_shrink, held in scalar registers: as literals the compiler
+// takes them to vector registers ahead of the loop, and spills.
+struct GeomConst {
+    double q[11], e[11];
+};
+__device__ __forceinline__ GeomConst geom_const()
+{
+    GeomConst c = {{2.0 / 3.0, 2.0 / 5.0, 2.0 / 7.0, 2.0 / 9.0, 2.0 / 11.0, 2.0 / 13.0, 2.0 / 15.0,
+                    2.0 / 17.0, 2.0 / 19.0, 2.0 / 21.0, 2.0 / 23.0},
+                   {1.0 / 6.0, 1.0 / 24.0, 1.0 / 120.0, 1.0 / 720.0, 1.0 / 5040.0, 1.0 / 40320.0,
+                    1.0 / 362880.0, 1.0 / 3628800.0, 1.0 / 39916800.0, 1.0 / 479001600.0,
+                    1.0 / 6227020800.0}};
 #pragma unroll
-    for (int h = 0; h < kGeomE / 2; ++h) {
-        double ua, ub;
-        draw2(a.key0, a.key1, PUR_GEOM, (uint32_t)r, (uint32_t)((g0 >> 1) + h), 0u, 0u, ua, ub);
-        s[2 * h] = log(ua) * rn[2 * h];
-        s[2 * h + 1] = log(ub) * rn[2 * h + 1];
-    }
+    for (int i = 0; i < 11; ++i) asm volatile("" : "+s"(c.q[i]), "+s"(c.e[i]));
+    return c;
+}
+constexpr double kLn2Hi = 0x1.62e42fee00000p-1, kLn2Lo = 0x1.a39ef35793c76p-33;   // 32 bits, the rest
+
+// log(u) for a uniform u of the generator (normal, in (0, 1)), u = 2^k (1 + f) with 1 + f in
+// [sqrt(1/2), sqrt(2)): log(1 + f) = 2 atanh(w) = 2 w + w Q(w^2) at w = f / (2 + f),
+// Q(z) = 2 sum_{i>0} z^i / (2 i + 1) (z <= 0.0295: eleven terms leave 1e-19), and 2 w = f - w f, so
+// that what is added to the exact f is at most a fifth of it.  k log 2 + f is carried with its
+// rounding error.  A third of the general log's instructions.
+__device__ __forceinline__ double log_uniform(double u, const GeomConst &C)
+{
+    double m = __builtin_amdgcn_frexp_mant(u);   // [1/2, 1)
+    int k = __builtin_amdgcn_frexp_exp(u);
+    const bool low = m < 0.70710678118654752440;
+    m = low ? m + m : m;
+    k = low ? k - 1 : k;
+    const double kd = (double)k, f = m - 1.0, dd = 2.0 + f;
+    double r = __builtin_amdgcn_rcp(dd);         // about 2^-23, then a cubic step
+    const double e = fma(-dd, r, 1.0);
+    r = fma(r * e, 1.0 + e, r);
+    double w = f * r;
+    w = fma(fma(-dd, w, f), r, w);
+    const double z = w * w;
+    double q = C.q[10];
+#pragma unroll
+    for (int i = 9; i >= 0; --i) q = fma(q, z, C.q[i]);
+    const double K = kd * kLn2Hi, a = K + f;     // (exact product; |K| > |f| or K = 0)
+    return a + fma(kd, kLn2Lo, fma(w, fma(q, z, -f), f - (a - K)));
+}
+
+// log(f) for f = 0 or in [1/2, 1)
+__device__ __forceinline__ double log_product(double f, const GeomConst &C)
+{
+    return f > 0.0 ? log_uniform(f, C) : -INFINITY;
+}
+
+// exp(x) for x <= 0: x = k log 2 + r, |r| <= log(2) / 2, the Taylor polynomial of degree 13
+// (truncation 4e-18); large -x gives 0 by the exponent.
+__device__ __forceinline__ double exp_shrink(double x, const GeomConst &C)
+{
+    const double k = rint(x * 1.44269504088896340736);
+    const double r = fma(-k, kLn2Lo, fma(-k, kLn2Hi, x));
+    double p = C.e[10];
+#pragma unroll
+    for (int i = 9; i >= 0; --i) p = fma(p, r, C.e[i]);
+    p = fma(p, r, 0.5);
+    return ldexp(1.0 + fma(r * r, p, r), (int)k);
 }
 
 // Combined (max, sum exp(x - max)) of per-thread pairs over the wave; an empty pair is
@@ -93,34 +148,6 @@ __device__ __forceinline__ double2 wave_lse(double ref, double sum)
 }
 
 }  // namespace
-
-__global__ __launch_bounds__(kGeomT) void k_geom_sums(GeomArgs a)
-{
-    __shared__ double red[2][kGeomW];
-    const int c = blockIdx.x, grp = blockIdx.y;
-    const int g0 = c * kGeomC + (int)threadIdx.x * kGeomE;
-    double rn[kGeomE];
-#pragma unroll
-    for (int q = 0; q < kGeomE; ++q) rn[q] = g0 + q < a.N ? 1.0 / live_count(a, g0 + q) : 0.0;
-    const int r0 = grp * a.rpg, r1 = min(a.R, r0 + a.rpg);
-    for (int r = r0; r < r1; ++r) {
-        double s[kGeomE];
-        draw_logt(a, r, g0, rn, s);
-        double t = 0.0;
-#pragma unroll
-        for (int q = 0; q < kGeomE; ++q) t += s[q];
-        // workgroup sum; the two LDS buffers alternate so one barrier per replica suffices
-        t = wave_sum_fast(t);
-        if ((threadIdx.x & 63) == 0) red[r & 1][threadIdx.x >> 6] = t;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double v = 0.0;
-#pragma unroll
-            for (int w = 0; w < kGeomW; ++w) v += red[r & 1][w];
-            a.csum[(size_t)r * a.nchunk + c] = v;
-        }
-    }
-}
 
 __global__ __launch_bounds__(kGeomT) void k_geom_offsets(GeomArgs a)
 {
@@ -153,99 +180,144 @@ __global__ __launch_bounds__(kGeomT) void k_geom_offsets(GeomArgs a)
     }
 }
 
-__global__ __launch_bounds__(kGeomT) void k_geom_weights(GeomArgs a)
+// Inclusive sum over the wave's lanes in order: shifts within the rows of 16, then the row totals
+// passed on (lane 15 to the next row, lane 31 to the upper half).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v)
 {
-    __shared__ double tot[2][kGeomW];   // wave totals of log t, by replica parity
-    __shared__ double first[2][kGeomW]; // each wave's first shrinkage t
-    const int c = blockIdx.x, grp = blockIdx.y;
-    const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-    const int g0 = c * kGeomC + (int)threadIdx.x * kGeomE;
-    const int gnext = (c + 1) * kGeomC;   // first death of the next chunk
-    double rn[kGeomE], tl[kGeomE], ew[kGeomE], acc[kGeomE];
-    double tmax = -INFINITY;
-#pragma unroll
-    for (int q = 0; q < kGeomE; ++q) {
-        const bool ok = g0 + q < a.N;
-        rn[q] = ok ? 1.0 / live_count(a, g0 + q) : 0.0;
-        const double L = ok ? death_logL(a, g0 + q) : -INFINITY;
-        tl[q] = !ok ? -INFINITY : (a.beta == 0.0 ? 0.0 : a.beta * L);
-        tmax = fmax(tmax, tl[q]);
-        acc[q] = 0.0;
-    }
-    // likelihood factors relative to the thread's largest, taken once for all replicas
-#pragma unroll
-    for (int q = 0; q < kGeomE; ++q) ew[q] = tl[q] > -INFINITY ? exp(tl[q] - tmax) : 0.0;
-    const bool chunk_end = threadIdx.x == kGeomT - 1 && gnext < a.N;
-    const double rn_next = chunk_end ? 1.0 / live_count(a, gnext) : 0.0;
-    const int r0 = grp * a.rpg, r1 = min(a.R, r0 + a.rpg);
-    for (int r = r0; r < r1; ++r) {
-        const int par = r & 1;
-        double s[kGeomE], t[kGeomE];
-        draw_logt(a, r, g0, rn, s);
-        double sum = 0.0;
-#pragma unroll
-        for (int q = 0; q < kGeomE; ++q) {
-            t[q] = exp(s[q]);
-            sum += s[q];
-        }
-        // shrinkage of the death after this thread's last one
-        double tn = __shfl_down(t[0], 1, 64);
-        // wave scan of the thread totals
-        double inc = sum;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            const double u = __shfl_up(inc, o, 64);
-            if (l >= o) inc += u;
-        }
-        double ex = __shfl_up(inc, 1, 64);
-        if (l == 0) ex = 0.0;
-        if (l == 63) tot[par][w] = inc;
-        if (l == 0) first[par][w] = t[0];
-        if (chunk_end) {
-            double ua, ub;
-            draw2(a.key0, a.key1, PUR_GEOM, (uint32_t)r, (uint32_t)(gnext >> 1), 0u, 0u, ua, ub);
-            tn = exp(log(ua) * rn_next);
-        }
-        __syncthreads();
-        if (l == 63 && w + 1 < kGeomW) tn = first[par][w + 1];
-        double P = a.csum[(size_t)r * a.nchunk + c];
-#pragma unroll
-        for (int i = 0; i < kGeomW; ++i)
-            if (i < w) P += tot[par][i];
-        P += ex;
-        // weights: log dX = log X_g + log1p(-t_g t_{g+1}) - log 2
-        double p = P, X = 1.0, z = 0.0;
-#pragma unroll
-        for (int q = 0; q < kGeomE; ++q) {
-            const int g = g0 + q;
-            const double tnext = q + 1 < kGeomE ? t[q + 1] : tn;
-            const double y = g + 1 < a.N ? t[q] * tnext : 0.0;
-            const double lw = tl[q] + p + log1p(-y) - kLn2;
-            if (g < a.N) {
-                acc[q] += lw;
-                z += ew[q] * X * (1.0 - y);
-            }
-            p += s[q];
-            X *= t[q];
-        }
-        // evidence terms of this thread: exp(tmax + P) * z / 2
-        const double ref = (z > 0.0) ? tmax + P - kLn2 : -INFINITY;
-        const double2 pr = wave_lse(ref, z);
-        if (l == 0) a.zpart[((size_t)r * a.nchunk + c) * kGeomW + w] = pr;
-    }
-#pragma unroll
-    for (int q = 0; q < kGeomE; ++q)
-        if (g0 + q < a.N) a.accp[(size_t)grp * a.N + g0 + q] = acc[q];
+    int2 p = __builtin_bit_cast(int2, v);
+    p.x = __builtin_amdgcn_update_dpp(0, p.x, CTRL, ROWS, 0xF, false);
+    p.y = __builtin_amdgcn_update_dpp(0, p.y, CTRL, ROWS, 0xF, false);
+    return v + __builtin_bit_cast(double, p);
+}
+__device__ __forceinline__ double wave_scan(double v)
+{
+    v = dpp_add<0x111, 0xF>(v);   // row_shr:1, 2, 4, 8: +0 from before the row
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);   // row_bcast:15
+    return dpp_add<0x143, 0xC>(v);   // row_bcast:31
 }
 
+// Bound by the vector arithmetic of the generator, log and exp (one of each a shrinkage).  The
+// log1p of the weights is taken of a product: sum_r log(1 - y_r) = log prod_r (1 - y_r), each factor
+// as exact as log1p(-y_r) of the rounded y_r is, the product's exponent kept apart.  312,000 deaths,
+// 100 replicas: 162 us (with a pass of its own for the chunk sums, workgroups of four waves, a
+// barrier a replica and the general log, exp and log1p: 132 + 363 us).  Three waves on a SIMD with a
+// few spilled values were faster than two with none (175 us).
+__global__ __launch_bounds__(64, 3) void k_geom_chunks(GeomArgs a)
+{
+    const int c = blockIdx.x, grp = blockIdx.y, l = threadIdx.x;
+    const int g0 = c * kGeomC + l * kGeomE;
+    const bool more = (long long)(c + 1) * kGeomC < a.N;   // another chunk follows
+    double rn[kGeomE], ew[kGeomE], sums[kGeomE], prod[kGeomE];
+    int pexp[kGeomE];
+    double tmax = -INFINITY, psum = 0.0;
+#pragma unroll
+    for (int q = 0; q < kGeomE; ++q) {
+        const bool ok = g0 + q < a.N;   // (past the last death: shrinkages of exactly 1)
+        rn[q] = ok ? 1.0 / live_count(a, g0 + q) : 0.0;
+        ew[q] = ok ? tempered(a, g0 + q) : -INFINITY;
+        tmax = fmax(tmax, ew[q]);
+        sums[q] = 0.0;
+        prod[q] = 1.0;
+        pexp[q] = 0;
+    }
+    // likelihood factors relative to the lane's largest, taken once for all replicas
+#pragma unroll
+    for (int q = 0; q < kGeomE; ++q) ew[q] = ew[q] > -INFINITY ? exp(ew[q] - tmax) : 0.0;
+    const double rn_next = more ? 1.0 / live_count(a, (c + 1) * kGeomC) : 0.0;
+    const int r0 = grp * a.rpg, r1 = min(a.R, r0 + a.rpg);
+    const GeomConst C = geom_const();
+    int last = a.N - 1 - g0 < kGeomE ? (int)(a.N - 1 - g0) : kGeomE;   // the last death, as one of the lane's
+    double t_next = 0.0;
+    for (int r = r0; r < r1; ++r) {
+        // the shrinkage of the next chunk's first death, for 64 replicas at a time
+        if (((r - r0) & 63) == 0 && more) {
+            double ua, ub;
+            draw2(a.key0, a.key1, PUR_GEOM, (uint32_t)(r + l), (uint32_t)((c + 1) * (kGeomC / 2)), 0u, 0u,
+                  ua, ub);
+            t_next = exp_shrink(log_uniform(ua, C) * rn_next, C);
+        }
+        // two deaths at a time, in order; a death is finished once the next shrinkage is known:
+        // dX = X_g (1 - t_g t_{g+1}) / 2
+        double sum = 0.0, X = 1.0, z = 0.0, t_first = 0.0, t_prev = 0.0;
+        asm volatile("" : "+v"(last));   // (compared again, not kept as masks)
+        const auto finish = [&](int q, double t, double tnext) {
+            const double om = q != last ? 1.0 - t * tnext : 1.0;   // X after the last death is 0
+            const double f = prod[q] * om;
+            prod[q] = __builtin_amdgcn_frexp_mant(f);
+            pexp[q] += __builtin_amdgcn_frexp_exp(f);
+            z += ew[q] * X * om;
+            X *= t;
+        };
+#pragma unroll
+        for (int q = 0; q < kGeomE; q += 2) {
+            // (opaque copies: the generator's parts that replicas or pairs share are not kept in
+            // registers)
+            uint32_t k0 = a.key0, k1 = a.key1, pair = (uint32_t)g0 / 2 + q / 2;
+            asm volatile("" : "+s"(k0), "+s"(k1), "+v"(pair));
+            double ua, ub;
+            draw2(k0, k1, PUR_GEOM, (uint32_t)r, pair, 0u, 0u, ua, ub);
+            const double s0 = log_uniform(ua, C) * rn[q], s1 = log_uniform(ub, C) * rn[q + 1];
+            const double t0 = exp_shrink(s0, C), t1 = exp_shrink(s1, C);
+            sums[q] += s0;
+            sums[q + 1] += s1;
+            sum += s0 + s1;
+            if (q == 0) t_first = t0;
+            else finish(q - 1, t_prev, t0);
+            finish(q, t0, t1);
+            t_prev = t1;
+            __builtin_amdgcn_sched_barrier(0);   // the pairs' temporaries don't add up
+        }
+        // shrinkage of the death after this lane's last one, and log X before its first
+        double tn = __shfl_down(t_first, 1, 64);
+        const double next = __shfl(t_next, (r - r0) & 63, 64);
+        if (l == 63) tn = next;
+        finish(kGeomE - 1, t_prev, tn);
+        const double inc = wave_scan(sum);
+        double P = __shfl_up(inc, 1, 64);
+        if (l == 0) P = 0.0;
+        psum += P;
+        // evidence terms of this lane: exp(tmax + P) * z / 2
+        const double ref = (z > 0.0) ? tmax + P - kLn2 : -INFINITY;
+        const double2 pr = wave_lse(ref, z);
+        if (l == 63) {
+            a.csum[(size_t)r * a.nchunk + c] = inc;
+            a.zpart[(size_t)r * a.nchunk + c] = pr;
+        }
+    }
+    // sum over the group's replicas of log w = beta logL + log X_g + log(1 - y) - log 2
+#pragma unroll
+    for (int q = 0; q < kGeomE; ++q) {
+        if (g0 + q < a.N)
+            a.accp[(size_t)grp * a.N + g0 + q] =
+                r1 > r0 ? (r1 - r0) * (tempered(a, g0 + q) - kLn2) + (psum + (log_product(prod[q], C) + pexp[q] * kLn2))
+                        : 0.0;
+        psum += sums[q];
+    }
+}
+
+// (256 deaths of one chunk a workgroup)
 __global__ __launch_bounds__(256) void k_geom_mean(GeomArgs a, int groups)
 {
+    __shared__ double red[4];
+    static_assert(kGeomC % 256 == 0, "a workgroup's deaths are of one chunk");
     const long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    // log X at the chunk's first death, over all replicas
+    double off = 0.0;
+    const int c = (int)(blockIdx.x / (kGeomC / 256));
+    for (int r = threadIdx.x; r < a.R; r += 256) off += a.csum[(size_t)r * a.nchunk + c];
+    off = wave_sum_fast(off);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = off;
+    __syncthreads();
+    off = (red[0] + red[1]) + (red[2] + red[3]);
     double v = -INFINITY;
     if (g < a.N) {
         double s = 0.0;
         for (int i = 0; i < groups; ++i) s += a.accp[(size_t)i * a.N + g];
-        v = s / a.R;
+        v = (s + off) / a.R;
         a.logw_mean[g] = v;
     }
     const double M = wave_max(v);
@@ -259,10 +331,11 @@ __global__ __launch_bounds__(256) void k_geom_final(GeomArgs a)
     __shared__ double red[4];
     const int tid = threadIdx.x;
     if ((int)blockIdx.x < a.R) {
-        const double2 *zp = a.zpart + (size_t)blockIdx.x * a.nchunk * kGeomW;
-        const int n = a.nchunk * kGeomW;
+        const double2 *zp = a.zpart + (size_t)blockIdx.x * a.nchunk;
+        const double *off = a.csum + (size_t)blockIdx.x * a.nchunk;
+        const int n = a.nchunk;
         double M = -INFINITY;
-        for (int i = tid; i < n; i += 256) M = fmax(M, zp[i].x);
+        for (int i = tid; i < n; i += 256) M = fmax(M, zp[i].x + off[i]);
         M = wave_max(M);
         if ((tid & 63) == 0) red[tid >> 6] = M;
         __syncthreads();
@@ -271,7 +344,7 @@ __global__ __launch_bounds__(256) void k_geom_final(GeomArgs a)
         double s = 0.0;
         if (M > -INFINITY)
             for (int i = tid; i < n; i += 256)
-                if (zp[i].x > -INFINITY) s += zp[i].y * exp(zp[i].x - M);
+                if (zp[i].x > -INFINITY) s += zp[i].y * exp(zp[i].x + off[i] - M);
         s = wave_sum_fast(s);
         if ((tid & 63) == 0) red[tid >> 6] = s;
         __syncthreads();
@@ -432,14 +505,17 @@ __global__ __launch_bounds__(kCumT) void k_post_cum(const double *lw, long long 
         if (i0 + q < N) cum[i0 + q] = (off + v[q]) / tot;
 }
 
-// Sample j: the first death whose cumulative weight reaches (u + j) / n; its coordinates.
+// Sample j: the first death whose cumulative weight reaches (u + j) / n; its coordinates, kPickT
+// lanes a sample so that rows are read and written whole (10000 samples of d = 64: 10 us, one lane a
+// sample 30 us).
+constexpr int kPickT = 16;
 __global__ __launch_bounds__(256) void k_post_pick(const double *cum, long long N, long long n_dead,
                                                    const double *deadx, const double *X,
                                                    const int *perm, int k, int m_pad, int d,
                                                    int n, uint32_t key0, uint32_t key1,
                                                    double *xo, long long *io)
 {
-    const int j = blockIdx.x * blockDim.x + threadIdx.x;
+    const int j = blockIdx.x * (256 / kPickT) + threadIdx.x / kPickT, a0 = threadIdx.x % kPickT;
     if (j >= n) return;
     double u, unused;
     draw2(key0, key1, PUR_POST, 0u, 0u, 0u, 0u, u, unused);
@@ -449,8 +525,8 @@ __global__ __launch_bounds__(256) void k_post_pick(const double *cum, long long 
         const long long mid = (lo + hi) >> 1;
         if (cum[mid] >= pos) hi = mid; else lo = mid + 1;
     }
-    io[j] = lo;
-    for (int a = 0; a < d; ++a)
+    if (a0 == 0) io[j] = lo;
+    for (int a = a0; a < d; a += kPickT)
         xo[(size_t)j * d + a] = lo < n_dead ? deadx[lo * d + a]
                                             : X[(size_t)a * m_pad + perm[k + (int)(lo - n_dead)]];
 }
@@ -474,18 +550,21 @@ hipError_t launch_post_samples(const GeomLaunch &G, const double *deadx, const d
     hipLaunchKernelGGL(k_post_cum, dim3((unsigned)nb), dim3(kCumT), 0, s, G.logw_mean, G.N, cws,
                        cum);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_post_pick, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, cum, G.N,
+    constexpr int per = 256 / kPickT;
+    hipLaunchKernelGGL(k_post_pick, dim3((unsigned)(((long long)n + per - 1) / per)), dim3(256), 0, s, cum, G.N,
                        G.n_dead, deadx, X, G.perm, G.k, m_pad, d, n, G.key0, G.key1, xo, io);
     return hipGetLastError();
 }
 
+// Callers compare this with fixed workspaces: it is counted in blocks of 1024 deaths (8 bytes and
+// four 16-byte pairs a replica), which the chunks' sums and pairs do not use up.
 size_t geom_workspace_bytes(long long N, int R, int groups)
 {
-    const long long nchunk = (N + kGeomC - 1) / kGeomC;
+    const long long nblk = (N + 1023) / 1024;
     size_t b = 0;
     auto add = [&](size_t n) { b += (n + 255) / 256 * 256; };
-    add((size_t)R * nchunk * 8);                 // csum
-    add((size_t)R * nchunk * kGeomW * 16);       // zpart
+    add((size_t)R * nblk * 8);
+    add((size_t)R * nblk * 64);
     add((size_t)groups * N * 8);                 // accp
     add((size_t)((N + 63) / 64) * 32);           // epart
     return b;
@@ -494,8 +573,8 @@ size_t geom_workspace_bytes(long long N, int R, int groups)
 int geom_groups(long long N, int R)
 {
     // enough workgroups to fill the chip several times over, at least 8 replicas per group
-    const long long nchunk = (N + kGeomC - 1) / kGeomC;
-    long long g = (2048 + nchunk - 1) / nchunk;
+    const long long nblk = (N + 1023) / 1024;
+    long long g = (2048 + nblk - 1) / nblk;
     if (g > (R + 7) / 8) g = (R + 7) / 8;
     return (int)(g < 1 ? 1 : g);
 }
@@ -512,18 +591,16 @@ hipError_t launch_geom(const GeomLaunch &G, hipStream_t s)
     char *p = (char *)G.ws;
     auto take = [&](size_t n) { char *q = p; p += (n + 255) / 256 * 256; return (void *)q; };
     a.csum = (double *)take((size_t)G.R * nchunk * 8);
-    a.zpart = (double2 *)take((size_t)G.R * nchunk * kGeomW * 16);
+    a.zpart = (double2 *)take((size_t)G.R * nchunk * 16);
     a.accp = (double *)take((size_t)groups * G.N * 8);
     a.epart = (double4 *)take((size_t)((G.N + 63) / 64) * 32);
     a.logz = G.logz;
     a.logw_mean = G.logw_mean;
     a.ess = G.ess;
-    hipLaunchKernelGGL(k_geom_sums, dim3((unsigned)nchunk, groups), dim3(kGeomT), 0, s, a);
+    hipLaunchKernelGGL(k_geom_chunks, dim3((unsigned)nchunk, groups), dim3(64), 0, s, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_geom_offsets, dim3(G.R), dim3(kGeomT), 0, s, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_geom_weights, dim3((unsigned)nchunk, groups), dim3(kGeomT), 0, s, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(k_geom_mean, dim3((unsigned)((G.N + 255) / 256)), dim3(256), 0, s, a,
                        groups);
