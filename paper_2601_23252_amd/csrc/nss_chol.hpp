@@ -76,8 +76,10 @@ __device__ __forceinline__ float rsq_refined(float x)
 // row i of the diagonal tile.  On return lane i < 16 holds row i of the factor (its entries above
 // the diagonal are not meaningful), the other lanes their row times the transposed inverse
 // factor.  iv: reciprocal pivots' roots; p0, p1: the products of the first and last eight pivots;
-// bad: a pivot was not positive (the results are then not meaningful).
-template <typename T>
+// bad: a pivot was not positive (the results are then not meaningful).  ROUNDED: the roots and
+// quotients are rounded to nearest, as sqrt and / are (about 60 cycles more on a pivot's chain), for
+// a matrix whose last pivots are its rounding error: there another rounding is another factor.
+template <typename T, bool ROUNDED = false>
 __device__ __forceinline__ void eliminate(T (&a)[16], T (&iv)[16], double &p0, double &p1, int &bad)
 {
     p0 = p1 = 1.0;
@@ -90,7 +92,15 @@ __device__ __forceinline__ void eliminate(T (&a)[16], T (&iv)[16], double &p0, d
         if (jj < 8) p0 *= (double)piv; else p1 *= (double)piv;
         const T r = rsq_refined(piv);
         iv[jj] = r;
-        a[jj] *= r;
+        if constexpr (ROUNDED) {
+            T root = piv * r;
+            root = fma(fma(-root, root, piv), T(0.5) * r, root);
+            const T inv = fma(fma(-root, r, T(1)), r, r);
+            const T q = a[jj] * inv;
+            a[jj] = (threadIdx.x & 63) == jj ? root : fma(fma(-q, root, a[jj]), inv, q);
+        } else {
+            a[jj] *= r;
+        }
 #pragma unroll
         for (int c = jj + 1; c < 16; ++c) a[c] -= a[jj] * readlane_t(a[jj], c);
         // every row takes this column now: left to itself the compiler sinks the updates to

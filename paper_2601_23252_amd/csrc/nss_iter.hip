@@ -362,8 +362,11 @@ __global__ __launch_bounds__(256) void k_cov(Launch Lc)
 // and are eliminated with one row per lane (the diagonal tile's rows in a wave's first lanes, 48
 // rows below it in the others), while the other waves' tiles take the previous column on MFMA.
 // Bound by the pivots' dependent chain, about 4,000 cycles per 16 columns, and two barriers a
-// block column.  d = 5, 32, 50, 64: 7.4, 14.7, 24 and 38 us; a column at a time with three barriers
-// each took 10.8, 32.6, 62 and 101.
+// block column.  d = 5, 32, 50, 64: 8.1, 15.7, 25 and 39 us; a column at a time with three barriers
+// each took 10.8, 32.6, 62 and 101.  The sums, products, roots and quotients are those of that
+// column-by-column factor in its order, bit for bit: with fewer survivors than dimensions the
+// covariance is singular but for the jitter and its last columns are rounding errors, which the
+// chains' steps follow (a factor of other roundings moved such runs' points by 1e-7).
 constexpr int kCholThreads = 512, kCholWaves = 8;
 constexpr int kCholSlots = 5;            // 36 tiles at D = 128
 constexpr size_t kCholLds = (2 * 8 * kTile + 128 + 32) * 8 + 16;
@@ -396,14 +399,18 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(Launch Lc)
     // sum of a tile's products over the groups: element (row, col) of tile t
     auto summed = [&](int t, int row, int col) -> double {
         const auto src = part2 + (size_t)t * 256 + col * 16 + row;
-        double s0 = 0.0, s1 = 0.0;
-        int g = 0;
-        for (; g + 1 < G; g += 2) {
-            s0 += src[(size_t)g * ntile * 256];
-            s1 += src[(size_t)(g + 1) * ntile * 256];
-        }
-        if (g < G) s0 += src[(size_t)g * ntile * 256];
-        return s0 + s1;
+        double s = 0.0;
+#pragma unroll 4
+        for (int g = 0; g < G; ++g) s += src[(size_t)g * ntile * 256];
+        return s;
+    };
+    // the jitter, 1e-12 * tr / d: the trace as a sum over lanes a = 0..127 and their two waves
+    auto jitter = [&](double v) -> double {
+        v = wave_sum(v);
+        __syncthreads();
+        if (l == 0) red[w] = v;
+        __syncthreads();
+        return 1e-12 * (red[0] + red[1]) / d;
     };
     auto variance = [&](int a) -> double {   // without the jitter
         const int I = a >> 4;
@@ -412,8 +419,7 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(Launch Lc)
     if (R.diag) {   // the diagonal metric: square roots of the (jittered) variances
         __syncthreads();
         const double v = tid < d ? variance(tid) : 0.0;
-        const double tr = block_sum(v, red);
-        const double vj = v + 1e-12 * tr / d;
+        const double vj = v + jitter(v);
         if (tid < d && !(vj > 0.0)) *fail = 1;
         __syncthreads();
         if (tid < d) {
@@ -440,7 +446,7 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(Launch Lc)
         }
     }
     __syncthreads();   // mc
-    double tr = 0.0;
+    double *diag = pan;
 #pragma unroll
     for (int s = 0; s < kCholSlots; ++s) {
         if (tI[s] < 0) continue;
@@ -449,14 +455,14 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(Launch Lc)
             const int a = 16 * tI[s] + Mf<double>::row(l, r), b = 16 * tK[s] + (l & 15);
             if (a < d && b < d) {
                 acc[s][r] = acc[s][r] / n - mc[a] * mc[b];
-                if (a == b) tr += acc[s][r];
+                if (a == b) diag[a] = acc[s][r];
             } else if (a == b) {
                 acc[s][r] = 1.0;   // padded coordinates: identity (never stored)
             }
         }
     }
-    // jitter: 1e-12 * tr / d on the diagonal
-    const double jit = 1e-12 * block_sum(tr, red) / d;
+    __syncthreads();
+    const double jit = jitter(tid < d ? diag[tid] : 0.0);
 #pragma unroll
     for (int s = 0; s < kCholSlots; ++s)
 #pragma unroll
@@ -491,7 +497,7 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(Launch Lc)
             int bad;
 #pragma unroll
             for (int c = 0; c < 16; ++c) a[c] = rp[c];
-            eliminate<double>(a, iv, p0, p1, bad);
+            eliminate<double, true>(a, iv, p0, p1, bad);
             if (w == 0 && l == 0 && bad) *fail = 1;
             if (prow || (w == 0 && l < 16)) {
                 const int ro = a0 * (a0 + 1) / 2;

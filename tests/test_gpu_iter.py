@@ -82,3 +82,23 @@ def test_singular_covariance_falls_back_to_the_variances(N):
     else:   # the jitter carried it: the factor is finite and reproduces the covariance
         assert np.all(np.isfinite(st["Lsig"]))
     r.close()
+
+
+@pytest.mark.parametrize("d", [24, 33, 64, 100, 128])
+def test_whitening_factor_of_few_survivors(N, d):
+    """20 survivors in d > 20 dimensions: the covariance is singular but for the jitter (1e-12 of the
+    mean variance), which the factor still holds: no fallback, and L L^T equals the covariance to the
+    rounding of 20 + d summands."""
+    from paper_2601_23252_amd import problems as G
+    prob = G.gaussian_problem(d, np.zeros(d), 0.04 * np.eye(d))
+    r = N.NSRun(prob, m=40, k=20, p=1, seed=d)
+    s = r.state()
+    pts = s["x"][s["perm"][20:]]
+    r.step()
+    L = r.state()["Lsig"]
+    C = np.cov(pts.T, bias=True).reshape(d, d)
+    C = C + 1e-12 * np.trace(C) / d * np.eye(d)
+    sd = np.sqrt(np.diag(C))
+    assert r.stats()["whiten_fallbacks"] == 0
+    assert np.abs((L @ L.T - C) / np.outer(sd, sd)).max() < (20 + d) * np.finfo(float).eps * 4
+    r.close()
