@@ -37,17 +37,19 @@
 // eight polynomials side by side for their latency (two: 8.6 ms).
 //
 // The random walk's proposals x + u_n are the same products at t = 1: a block's fifteen are tested
-// at once from the current point, and again after each acceptance (d = 50, 500 chains of 250
-// steps: 364 us a launch with points, 175 here).
+// at once from the current point, and again after each acceptance, their moves in registers for
+// the box (d = 50, 500 chains of 250 steps: 364 us a launch with points, 122 here; 175 with the
+// block's proposals copied and tested against the box one by one).
 //
 // What it replaces evaluated every candidate as a point, in a tile shared by a workgroup's
 // chains, at two barriers and two to three tiles a step.  One launch with points and here:
 // d = 5, 50 chains of 25 steps 241 and 33 us; d = 32, 500 chains of 160 steps (BF16x3 points)
-// 1561 and 178 us; 8 components at d = 64, 1000 chains of 320 steps in FP64 7800 and 905 us.
+// 1561 and 178 us; 8 components at d = 64, 1000 chains of 320 steps in FP64 7800 and 855 us.
 // (Without the planned first pass, the shifted row and the fragments requested ahead: 56, 301
 // and 1900 us.)  One wave per SIMD runs at those sizes, so the bound is the walk's length, about
 // 2,500 cycles a step; at 8 components the products take as long again, twice what the FP64
-// matrix rate allows.
+// matrix rate allows (W's fragments come from L2 for every wave; more sums side by side on the
+// matrix unit changed nothing).
 #include "nss_internal.hpp"
 #include "nss_rng.hpp"
 #include "nss_tiles.hpp"
@@ -80,7 +82,7 @@ __host__ __device__ inline LineLayout line_layout(int D, int K, int lik, bool bo
     int off = 0;
     o.gram = off; off += al16(forms * 16 * kLineLd * 8);
     o.x = off; off += al16(D * 8);
-    o.v = off; off += rw ? kLineB * D * 8 : lik == LIK_RG ? al16(D * 8) : 0;
+    o.v = off; off += rw ? al16(kLineB * (D + 1) * 8) : lik == LIK_RG ? al16(D * 8) : 0;
     o.us = off; off += 16 * kStepU * 8;
     o.tt = off; off += 16 * 16 * 8;
     o.su = off; off += 16 * 8;
@@ -181,7 +183,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
     const DevRun R = Lc.R[bm.x];
     if (R.iscal[0] || R.iscal[2] <= 0) return;
     constexpr int NA = (D + 63) / 64;
-    constexpr int NJB = D / 16, NKS = D / 4;
+    constexpr int NJB = D / 16, NKS = D / 4, LDV = D + 1;   // LDV: row stride of the walk's proposals
     constexpr bool MIX = LIK == LIK_MIXTURE, RG = LIK == LIK_RG;
     constexpr bool TEMP = KIND == LINE_TEMPERED, RW = KIND == LINE_WALK;
     const LineLayout lay = line_layout(D, P.K, LIK, BOX, RW);
@@ -286,6 +288,35 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                 pus[i] = l + 64 * i < nb * kStepU ? ub[(size_t)s0 * kStepU + l + 64 * i] : 0.5;
         };
         fetch_block(0);
+        // W column blocks in pairs (pr, NJB - 1 - pr) of equal triangular work, taken in
+        // chunks of at most 20 fragments, the next chunk's requested before this one's
+        // products (a trip to L2 costs about what the products of a chunk take), and the next
+        // block's first before the walk
+        constexpr int NPR = NJB / 2, NF = 4 * (NJB + 1), NCH = NF > 20 ? 2 : 1;
+        constexpr int CH = NF / NCH, NSEQ = NPR * NCH;   // chunks per component
+        double wa[CH], wb[CH];
+        // fragment f of pair pr: column block j0 or j1 in turn while both have k-steps
+        auto frag = [](int pr, int f, int &jb, int &ks, bool &lo) {
+            const int n0 = 4 * (pr + 1);
+            lo = f < 2 * n0 && !(f & 1);
+            jb = lo ? pr : NJB - 1 - pr;
+            ks = f < 2 * n0 ? f >> 1 : f - n0;
+        };
+        auto load = [&](double *wf, int c, int sq) {
+            const auto src = as_global(P.wf64) +
+                             (size_t)(c < K ? c : K - 1) * NJB * NKS * 64 + l;
+#pragma unroll
+            for (int i = 0; i < CH; ++i) {
+                int jb, ks;
+                bool lo;
+                frag(sq / NCH, (sq % NCH) * CH + i, jb, ks, lo);
+                wf[i] = src[(jb * NKS + ks) * 64];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        // (not where the walk's own values leave no registers for it)
+        constexpr bool AHEAD = MIX && (RW ? D < 128 : NR == 1 || (NR == 2 && !TEMP));
+        if constexpr (AHEAD) load(wa, 0, 0);
 
         for (int s0 = 0; s0 < p; s0 += kLineB) {
             const int nb = min(kLineB, p - s0);
@@ -294,35 +325,20 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             for (int i = 0; i < NA; ++i) if (l + 64 * i < D) xs[l + 64 * i] = x0r[i];
             us[l] = pus[0];
             us[l + 64] = pus[1];
-            if constexpr (RW)
-                for (int e = l; e < nb * D; e += 64) vs[e] = dirs[(size_t)s0 * D + e];
-            wave_sync();
-            // W column blocks in pairs (pr, NJB - 1 - pr) of equal triangular work, taken in
-            // chunks of at most 20 fragments, the next chunk's requested before this one's
-            // products (a trip to L2 costs about what the products of a chunk take)
-            constexpr int NPR = NJB / 2, NF = 4 * (NJB + 1), NCH = NF > 20 ? 2 : 1;
-            constexpr int CH = NF / NCH, NSEQ = NPR * NCH;   // chunks per component
-            double wa[CH], wb[CH];
-            // fragment f of pair pr: column block j0 or j1 in turn while both have k-steps
-            auto frag = [](int pr, int f, int &jb, int &ks, bool &lo) {
-                const int n0 = 4 * (pr + 1);
-                lo = f < 2 * n0 && !(f & 1);
-                jb = lo ? pr : NJB - 1 - pr;
-                ks = f < 2 * n0 ? f >> 1 : f - n0;
-            };
-            auto load = [&](double *wf, int c, int sq) {
-                const auto src = as_global(P.wf64) +
-                                 (size_t)(c < K ? c : K - 1) * NJB * NKS * 64 + l;
+            if constexpr (RW && MIX) {
 #pragma unroll
-                for (int i = 0; i < CH; ++i) {
-                    int jb, ks;
-                    bool lo;
-                    frag(sq / NCH, (sq % NCH) * CH + i, jb, ks, lo);
-                    wf[i] = src[(jb * NKS + ks) * 64];
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            if constexpr (MIX) load(wa, 0, 0);
+                for (int ks = 0; ks < NKS; ++ks)
+                    if (col < kLineB) vs[col * LDV + 4 * ks + row] = b[ks];
+            } else if constexpr (RW) {
+#pragma unroll
+                for (int c = 0; c < kLineB; ++c)
+#pragma unroll
+                    for (int i = 0; i < NA; ++i)
+                        if (l + 64 * i < D)
+                            vs[c * LDV + l + 64 * i] = dirs[(size_t)(s0 + min(c, nb - 1)) * D + l + 64 * i];
+            }
+            wave_sync();
+            if constexpr (MIX && !AHEAD) load(wa, 0, 0);
             if constexpr (!RW) {
                 // t of the first passes: columns 0, 1 the left end's next tests, 2, 3 the right
                 // end's, then four proposals after no expansion, one left, one right (four steps at
@@ -384,10 +400,12 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                         mul(wa, 0);
                         put(gram + c * 16 * kLineLd, G);
                         if (c + 1 < K) {
-                            load(wa, c + 2, 0);
+                            load(wa, c + 2 < K ? c + 2 : 0, 0);
                             begin(c + 1);
                             mul(wb, 0);
                             put(gram + (c + 1) * 16 * kLineLd, G);
+                        } else if (AHEAD && c > 0) {
+                            load(wa, 0, 0);
                         }
                     }
                 } else {
@@ -397,7 +415,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                         for (int sq = 0; sq < NSEQ; sq += 2) {
                             load(wb, c, sq + 1);
                             mul(wa, sq);
-                            load(wa, sq + 2 < NSEQ ? c : c + 1, sq + 2 < NSEQ ? sq + 2 : 0);
+                            load(wa, sq + 2 < NSEQ ? c : (c + 1 < K ? c + 1 : 0), sq + 2 < NSEQ ? sq + 2 : 0);
                             mul(wb, sq + 1);
                         }
                         put(gram + c * 16 * kLineLd, G);
@@ -459,15 +477,21 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                     dg[q] = gram[(c * 16 + col) * kLineLd + col];
                 }
                 if (!BOX) dgp = gpri[col * kLineLd + col];
-                if constexpr (!MIX) v0c = vs[min(col, kLineB - 1) * D];
-                double big[NA];   // the block's longest move of each coordinate
+                if constexpr (!MIX) v0c = vs[min(col, kLineB - 1) * LDV];
+                // the proposals' moves of the lane's coordinates (a padded coordinate's is 0 and
+                // its box open) and the longest
+                double vb[BOX ? kLineB : 1][NA], big[NA];
+                if constexpr (BOX) {
 #pragma unroll
-                for (int i = 0; i < NA; ++i) big[i] = 0.0;
-                if (BOX)
-                    for (int c = 0; c < nb; ++c)
+                    for (int i = 0; i < NA; ++i) {
+                        big[i] = 0.0;
 #pragma unroll
-                        for (int i = 0; i < NA; ++i)
-                            if (l + 64 * i < D) big[i] = fmax(big[i], fabs(vs[c * D + l + 64 * i]));
+                        for (int c = 0; c < kLineB; ++c) {
+                            vb[c][i] = l + 64 * i < D && c < nb ? vs[c * LDV + l + 64 * i] : 0.0;
+                            big[i] = fmax(big[i], fabs(vb[c][i]));
+                        }
+                    }
+                }
                 for (int at = 0; at < nb;) {
                     const unsigned todo = ((1u << nb) - 1u) & ~((1u << at) - 1u);
                     unsigned okm = todo, in;
@@ -478,18 +502,18 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                         for (int i = 0; i < NA; ++i)
                             all = all && x0r[i] + big[i] <= pbr[i] && x0r[i] - big[i] >= par[i];
                         if (!__all(all)) {
-                            okm = 0;
-                            for (int c = at; c < nb; ++c) {
+                            unsigned ok = 0;
+#pragma unroll
+                            for (int c = 0; c < kLineB; ++c) {
                                 bool ib = true;
 #pragma unroll
                                 for (int i = 0; i < NA; ++i) {
-                                    if (l + 64 * i < d) {
-                                        const double y = x0r[i] + vs[c * D + l + 64 * i];
-                                        ib = ib && y >= par[i] && y <= pbr[i];
-                                    }
+                                    const double y = x0r[i] + vb[c][i];
+                                    ib = ib && y >= par[i] && y <= pbr[i];
                                 }
-                                okm |= (__all(ib) ? 1u : 0u) << c;
+                                ok |= (__all(ib) ? 1u : 0u) << c;
                             }
+                            okm = todo & ok;
                         }
                     } else {
                         okm &= (unsigned)__ballot(-0.5 * fma(2.0, hp, dgp) > luh);
@@ -534,7 +558,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                         moved = true;
 #pragma unroll
                         for (int i = 0; i < NA; ++i)
-                            if (l + 64 * i < D) x0r[i] += vs[s * D + l + 64 * i];
+                            if (l + 64 * i < D) x0r[i] += vs[s * LDV + l + 64 * i];
 #pragma unroll
                         for (int q = 0; q < NR; ++q) {
                             const int c = 4 * q + row < K ? 4 * q + row : 0;
