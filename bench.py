@@ -738,7 +738,7 @@ def bench_rw(args):
                          "kernel_ms": st["hrss_ms"] / max(1, st["hrss_launches"]),
                          "logz": z, "z": (z - tz) / err, "collapsed": collapsed, **extra}
             if d == 100 and name == "rw":
-                timed = (st, dt)
+                timed = (st, dt, prob["k"] * p)
             R.close()
             print(f"[bench] d={d} {name}: {row[name]['mean']:.2f} +- {row[name]['std']:.2f} "
                   f"(max {row[name]['max']:.0f}, z {row[name]['z']:.2f}, "
@@ -746,10 +746,9 @@ def bench_rw(args):
                   + (f", acceptance {extra['acceptance']:.3f}" if extra else "") + ")",
                   file=sys.stderr, flush=True)
         table.append(row)
-    st, dt = timed
-    fpe = algorithmic_flop_per_eval(1, 100)
+    st, dt, steps = timed
     hrss_s = st["hrss_ms"] / 1e3
-    achieved = st["evals"] * fpe / hrss_s
+    achieved = line_flop(1, 100, float(st["iterations"]) * steps, st["evals"]) / hrss_s
     out = {
         "metric": "random-walk replacement likelihood evals/s (condition-100 Gaussian, d=100)",
         "value": st["evals"] / dt, "unit": "evals/s", "n_gpus": 1, "steps": 1, "warmup": 0,
@@ -760,7 +759,7 @@ def bench_rw(args):
                    "tests_per_s": st["tests"] / dt},
         "roofline": {"bound": "mfma", "achieved": achieved / 1e12, "peak": 78.6,
                      "unit": "TFLOP/s", "frac": achieved / 78.6e12, "traffic": None,
-                     "kernel": "k_rw<128, FP64, mixture, 1>", "flop_per_eval": fpe,
+                     "kernel": "k_hrss_line (random walk, d = 100)",
                      "avg_launch_ms": st["hrss_ms"] / max(1, st["hrss_launches"])},
         "evals_per_step": table,
     }
