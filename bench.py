@@ -40,15 +40,15 @@ sys.path.insert(0, ROOT)
 # (precision, chain length, chains per workgroup, planned tests per round), recorded for the
 # kernel sources with this sha256 prefix; reported as null once the sources differ or for a
 # shape the counters were not taken on.
-TRAFFIC = {("fp16x3", 320, 4, 8): 196.7e6}
-TRAFFIC_SOURCE_SHA = "fd6c2f8f156d9218"
+TRAFFIC = {("fp16x3", 320, 4, 8): 188.7e6}
+TRAFFIC_SOURCE_SHA = "c5036605d8601153"
 
 
 # VALU lane-instructions per evaluation issued by the chain kernel (SQ_INSTS_VALU x 64 /
 # evaluations of the profiled launches), keyed like TRAFFIC, for the kernel sources with this
 # prefix: the instruction view of the same kernel (its chain logic runs on the vector ALU).
 HRSS_VALU_PER_EVAL = {("fp16x3", 320, 4, 8): 24544.0}
-HRSS_VALU_SOURCE_SHA = "fd6c2f8f156d9218"
+HRSS_VALU_SOURCE_SHA = "c5036605d8601153"
 
 KERNEL_SOURCES = ("nss_kernels.hip", "nss_hrss_plan.hip", "nss_tiles.hpp", "nss_internal.hpp")
 
@@ -410,13 +410,13 @@ def bench_batch(args):
     B.close()
 
 
-# The geometric-uncertainty kernels are bound by vector-ALU issue (Philox, FP64 log, exp and
-# log1p per replica-death; no HBM stream).  VALU lane-instructions per replica-death of one
-# ns_geom_uncertainty call (SQ_INSTS_VALU over its five kernels x 64 lanes / (R N)), recorded
+# The geometric-uncertainty kernels are bound by vector-ALU issue (Philox, FP64 log and exp
+# per replica-death; no HBM stream).  VALU lane-instructions per replica-death of one
+# ns_geom_uncertainty call (SQ_INSTS_VALU over its kernels x 64 lanes / (R N)), recorded
 # for the kernel source with this sha256 prefix; the peak is one lane-instruction per lane per
 # cycle: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz.
-GEOM_VALU_PER_UNIT = 455.2
-GEOM_SOURCE_SHA = "ac3a36c198ebef19"
+GEOM_VALU_PER_UNIT = 135.2
+GEOM_SOURCE_SHA = "c1228c8182f4952e"
 VALU_PEAK = 256 * 4 * 16 * 2.4e9
 
 
@@ -478,7 +478,7 @@ def bench_geom(args):
         out["roofline"] = {"bound": "alu", "achieved": achieved / 1e12,
                            "peak": VALU_PEAK / 1e12, "unit": "TOP/s (VALU lane-instructions)",
                            "frac": achieved / VALU_PEAK, "traffic": None,
-                           "kernel": "ns_geom_uncertainty (k_geom_weights 71%, k_geom_sums 26%)",
+                           "kernel": "ns_geom_uncertainty (k_geom_chunks 87%)",
                            "valu_per_replica_death": ops}
     else:
         out["roofline"] = None
@@ -522,11 +522,11 @@ def lnz_rastrigin_gauss(d, alpha, r=5.14, amp=10.0):
     return mx + math.log(sum(math.exp(t - mx) for t in terms)) - d * math.log(2 * r)
 
 
-# VALU lane-instructions per likelihood evaluation of the Gaussian-Rastrigin k_hrss at d=100
+# VALU lane-instructions per likelihood evaluation of the Gaussian-Rastrigin k_hrss_line at d=100
 # (SQ_INSTS_VALU x 64 / evaluations of the profiled launches), for the kernel source with this
 # sha256 prefix.
-RG_VALU_PER_EVAL = 53026.0
-RG_SOURCE_SHA = "fff455ad04dd563f"
+RG_VALU_PER_EVAL = 35622.0
+RG_SOURCE_SHA = "d2f5037ac61b1803"
 
 
 def _rastrigin_table(args):
@@ -608,17 +608,17 @@ def bench_rastrigin(args):
     dt = time.perf_counter() - t0
     print(f"[bench] timed runs done in {dt:.1f} s", file=sys.stderr, flush=True)
     table = [] if args.no_table else _rastrigin_table(args)
-    src = os.path.join(ROOT, "paper_2601_23252_amd", "csrc", "nss_kernels.hip")
+    src = os.path.join(ROOT, "paper_2601_23252_amd", "csrc", "nss_line.hip")
     with open(src, "rb") as f:
         sha = hashlib.sha256(f.read()).hexdigest()[:16]
     roof = None
     shape = R.launch_shape()
-    # the VALU count was taken at two chains per workgroup (the rule's shape for k = 500)
-    if RG_VALU_PER_EVAL is not None and sha == RG_SOURCE_SHA and hrss_ms > 0 and shape[0] == 2:
+    # (a chain is one wave: the count does not depend on the chains per workgroup)
+    if RG_VALU_PER_EVAL is not None and sha == RG_SOURCE_SHA and hrss_ms > 0:
         achieved = RG_VALU_PER_EVAL * evals / (hrss_ms / 1e3)
         roof = {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK / 1e12,
                 "unit": "TOP/s (VALU lane-instructions)", "frac": achieved / VALU_PEAK,
-                "traffic": None, "kernel": "k_hrss<128, FP64, Gaussian-Rastrigin>",
+                "traffic": None, "kernel": "k_hrss_line<128, Gaussian-Rastrigin>",
                 "valu_per_eval": RG_VALU_PER_EVAL,
                 "avg_launch_ms": hrss_ms / max(1, launches)}
     out = {
