@@ -79,37 +79,13 @@ __device__ __forceinline__ GpTheta gp_theta(const double *u)
     return h;
 }
 
-// exp(x) for x <= 0: x = k log 2 + r with |r| <= log(2) / 2, the Taylor polynomial of degree 13
-// (truncation 4e-18), no test for overflow; large -x gives 0 by the exponent.
-__device__ __forceinline__ double exp_neg(double x)
-{
-    const double k = rint(x * 1.44269504088896340736);
-    double r = fma(-k, 0.693147180369123816490, x);   // the leading 33 bits of log 2
-    r = fma(-k, 1.90821492927058770002e-10, r);
-    double p = 1.0 / 6227020800.0;
-    p = fma(p, r, 1.0 / 479001600.0);
-    p = fma(p, r, 1.0 / 39916800.0);
-    p = fma(p, r, 1.0 / 3628800.0);
-    p = fma(p, r, 1.0 / 362880.0);
-    p = fma(p, r, 1.0 / 40320.0);
-    p = fma(p, r, 1.0 / 5040.0);
-    p = fma(p, r, 1.0 / 720.0);
-    p = fma(p, r, 1.0 / 120.0);
-    p = fma(p, r, 1.0 / 24.0);
-    p = fma(p, r, 1.0 / 6.0);
-    p = fma(p, r, 0.5);
-    p = fma(p, r, 1.0);
-    p = fma(p, r, 1.0);
-    return ldexp(p, (int)k);
-}
-
 // The kernel at input differences d1, d2, with s1, s2 the sines of pi d / P.
 template <typename T>
 __device__ __forceinline__ T gp_cov(double d1, double d2, double s1, double s2, const GpTheta &h)
 {
     if constexpr (sizeof(T) == 8) {
         const double a1 = d1 * h.il1, a2 = d2 * h.il2;
-        return h.sf2 * exp_neg(-0.5 * (a1 * a1 + a2 * a2) - 2.0 * (s1 * s1 + s2 * s2) * h.ilp2);
+        return h.sf2 * exp(-0.5 * (a1 * a1 + a2 * a2) - 2.0 * (s1 * s1 + s2 * s2) * h.ilp2);
     } else {
         const float a1 = (float)(d1 * h.il1), a2 = (float)(d2 * h.il2);
         const float f1 = (float)s1, f2 = (float)s2;
