@@ -103,11 +103,12 @@ __device__ __forceinline__ T gp_entry(const double *xs, const double *sc, int n,
 {
     if (row >= n || col >= n) return (row == col) ? T(1) : T(0);
     if (col > row) return T(0);
+    // (the combined sine of a point and itself is a rounding error, not 0: below l_p = 1e-15 its
+    // square counts)
+    if (row == col) return (T)h.sf2 + (T)h.sn2;
     const double *pa = sc + 4 * row, *pb = sc + 4 * col;
-    T v = gp_cov<T>(xs[2 * row] - xs[2 * col], xs[2 * row + 1] - xs[2 * col + 1],
-                    pa[0] * pb[1] - pa[1] * pb[0], pa[2] * pb[3] - pa[3] * pb[2], h);
-    if (row == col) v += (T)h.sn2;
-    return v;
+    return gp_cov<T>(xs[2 * row] - xs[2 * col], xs[2 * row + 1] - xs[2 * col + 1],
+                     pa[0] * pb[1] - pa[1] * pb[0], pa[2] * pb[3] - pa[3] * pb[2], h);
 }
 
 // log N(y; 0, K_theta + sigma_n^2 I) at u = log theta with the factorisation in T.  Called by

@@ -10,7 +10,7 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("coord", [1, 2])
+@pytest.mark.parametrize("coord", [1, 2, 3])
 @pytest.mark.parametrize("value", [-40.0, -50.0, -100.0])
 def test_tiny_length_scales(oracle_lib, coord, value):
     from paper_2601_23252_amd import nss, problems as G
