@@ -50,12 +50,6 @@ __device__ __forceinline__ void store_tile(const V &acc, T *p, int l)
 #pragma unroll
     for (int r = 0; r < 4; ++r) p[Mf<T>::row(l, r) * kTileLd + (l & 15)] = acc[r];
 }
-template <typename T, typename V>
-__device__ __forceinline__ void load_tile(V &acc, const T *p, int l)
-{
-#pragma unroll
-    for (int r = 0; r < 4; ++r) acc[r] = p[Mf<T>::row(l, r) * kTileLd + (l & 15)];
-}
 
 // 1/sqrt(x) from the hardware estimate r, for a short dependent chain per pivot: with
 // e = 1 - x r^2, r (1 + e/2 + 3 e^2/8) has the relative error 5 e^3 / 16 (e is about 2^-23 in FP64;
@@ -71,38 +65,50 @@ __device__ __forceinline__ float rsq_refined(float x)
     float r = __builtin_amdgcn_rsqf(x);
     return r * (1.5f - 0.5f * x * r * r);
 }
+// By two Newton steps r (3/2 - x r^2 / 2) instead (FP32: one): the GP's roots, whose roundings its
+// ill-conditioned factors follow.
+__device__ __forceinline__ double rsq_newton(double x)
+{
+    double r = __builtin_amdgcn_rsq(x);
+    const double h = 0.5 * x;
+    r *= fma(-r, h * r, 1.5);
+    r *= fma(-r, h * r, 1.5);
+    return r;
+}
+__device__ __forceinline__ float rsq_newton(float x) { return rsq_refined(x); }
 
 // Eliminates a block column with one row per lane: a[c] is the lane's row, lane i < 16
 // row i of the diagonal tile.  On return lane i < 16 holds row i of the factor (its entries above
 // the diagonal are not meaningful), the other lanes their row times the transposed inverse
-// factor.  iv: reciprocal pivots' roots; p0, p1: the products of the first and last eight pivots;
-// bad: a pivot was not positive (the results are then not meaningful).  ROUNDED: the roots and
-// quotients are rounded to nearest, as sqrt and / are (about 60 cycles more on a pivot's chain), for
-// a matrix whose last pivots are its rounding error: there another rounding is another factor.
+// factor (of a row of the identity: a column of the inverse).  roots: the product of the pivots'
+// roots; bad: a pivot was not positive (the results are then not meaningful).  ROUNDED: the roots
+// and quotients are rounded to nearest, as sqrt and / are (about 60 cycles more on a pivot's
+// chain), for a matrix whose last pivots are its rounding error: there another rounding is another
+// factor.
 template <typename T, bool ROUNDED = false>
-__device__ __forceinline__ void eliminate(T (&a)[16], T (&iv)[16], double &p0, double &p1, int &bad)
+__device__ __forceinline__ void eliminate(T (&a)[16], double &roots, int &bad)
 {
-    p0 = p1 = 1.0;
+    roots = 1.0;
     bad = 0;
 #pragma unroll
     for (int jj = 0; jj < 16; ++jj) {
         T piv = readlane_t(a[jj], jj);
         asm volatile("" : "+v"(piv));
         bad |= piv > T(0) ? 0 : 1;
-        if (jj < 8) p0 *= (double)piv; else p1 *= (double)piv;
-        const T r = rsq_refined(piv);
-        iv[jj] = r;
         if constexpr (ROUNDED) {
+            const T r = rsq_refined(piv);
             T root = piv * r;
             root = fma(fma(-root, root, piv), T(0.5) * r, root);
             const T inv = fma(fma(-root, r, T(1)), r, r);
             const T q = a[jj] * inv;
             a[jj] = (threadIdx.x & 63) == jj ? root : fma(fma(-q, root, a[jj]), inv, q);
         } else {
+            const T r = rsq_newton(piv);
+            roots *= (double)(piv * r);
             a[jj] *= r;
         }
 #pragma unroll
-        for (int c = jj + 1; c < 16; ++c) a[c] -= a[jj] * readlane_t(a[jj], c);
+        for (int c = jj + 1; c < 16; ++c) a[c] = fma(-a[jj], readlane_t(a[jj], c), a[c]);
         // every row takes this column now: left to itself the compiler sinks the updates to
         // their columns' turns and keeps all the lane reads until then
 #pragma unroll

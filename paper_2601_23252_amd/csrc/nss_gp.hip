@@ -7,24 +7,31 @@
 // each a product over the input dimensions).
 //
 // One workgroup of 8 waves evaluates one candidate at a time.  The kernel matrix is built as
-// 16x16 tiles of the lower triangle in the accumulator layout of the 16x16x4 MFMA (tile t is
-// held by wave t mod 8 in registers) and factorised by a right-looking blocked Cholesky.  For
-// each block column J the column's tiles, up to date, go to LDS, and the column is factored with
-// one row per lane: a wave takes the 16 rows of the diagonal tile in its first lanes, 47 rows
-// below it in the next and the right-hand side y_J in the last, and eliminates the 16 columns in
-// turn, each row less its pivot entry times the pivot rows' entries (lane reads).  The diagonal
-// factor, the panel L_IJ and z_J = L_JJ^{-1} y_J all come out of that one loop; up to six waves
-// run it side by side, each repeating the diagonal rows, so there is no inverse and no second
-// serial stage.  The other tiles meanwhile take the previous column's rank-16 update on MFMA
-// with operands from LDS.  The log-determinant and |z|^2 are summed on the way:
+// 16x16 tiles of the lower triangle, transposed, in the accumulator layout of the 16x16x4 MFMA
+// (tile t is held by wave t mod 8 in registers) and factorised by a right-looking blocked
+// Cholesky.  For each block column J the wave that holds the diagonal tile brings it up to date
+// and eliminates it with one row per lane: 16 lanes its rows, 16 more the rows of the identity,
+// which come out as the columns of the inverse factor.  Every tile below is then multiplied by
+// that inverse on MFMA.  A transposed accumulator is laid out as an operand of the next product
+// (lane l, register r: row l & 15, k-step r), so the panel goes from the registers to LDS and
+// back as whole 16- and 32-byte pieces.  While one wave eliminates, the others bring the later
+// columns' tiles up to date, and one of them takes the forward solve a block column behind:
+// z_J = L_JJ^{-1} y_J, y_I -= L_IJ z_J, one row per lane.
 //   log L = -|z|^2 / 2 - sum_i log L_ii - n/2 log(2 pi).
 // A pivot that is not positive makes the factorisation fail (FP64: log L = -inf).
 //
-// What bounds it at n = 256 (about 250,000 cycles an evaluation): 16 eliminations of about 4,000
-// cycles on the 256 pivots' dependent chain, the entries' exponentials (50,000), and the trailing
-// products, of which the FP64 matrix rate would allow 43,000.  One launch of 500 chains of 30
-// steps takes 16.2 ms; with one wave factoring and inverting each diagonal tile and a panel stage
-// after it (14,000 and 6,000 cycles a block column) it took 26.4 ms.
+// The order of every FP64 sum is fixed, by explicit fused operations where the compiler could
+// choose: the prior reaches sigma_f^2 / sigma_n^2 = 1e8, where another rounding of an entry, a
+// root or a product moves log L by 1e-9 of itself, and results are to stay what they are.
+//
+// What bounds it at n = 256 (about 255,000 cycles an evaluation): the chain of 16 block columns,
+// each about 3,000 cycles to bring the diagonal tile up to date and into rows, 4,000 for its 16
+// dependent pivots and 1,800 for the panel, then the entries' exponentials (50,000) and what the
+// updates leave uncovered.  500 chains of 30 steps: 26.2 ms a pass with one wave factoring, then
+// inverting, each diagonal tile and the tiles in a layout that had to be turned for every product,
+// 16.7 here; at n = 100 in the FP32 mode 5.5 and 3.8 ms.  (n and the tile indices have to be
+// wave-uniform to the compiler: as vector values they came back from scratch memory for every
+// tile, 25.3 ms.)
 //
 //  k_hrss_gp   one HRSS chain per workgroup (App. A.6), candidates evaluated one at a time
 //  k_eval_gp   one point per workgroup (initial live set, tests)
@@ -43,7 +50,7 @@ constexpr int kGpWaves = 8;                                           // per wor
 constexpr int kGpThreads = 64 * kGpWaves;
 constexpr int kGpMaxTiles = 136;                                      // 16 * 17 / 2
 constexpr int kGpSlots = kGpMaxTiles / kGpWaves;                      // tiles per wave
-constexpr int kGpRowLanes = 47;        // panel rows of a wave's elimination (lanes 16..62)
+constexpr int kFrag = 256;             // a tile in LDS as an operand: lane l's four values at 4 l
 constexpr int kGpD = 6;                                               // hyperparameters
 
 // LDS: inputs and targets (FP64), reduction slots, then the factorisation's tiles in T
@@ -54,13 +61,15 @@ constexpr int kOffChain = kOffMisc + 256;                             // chain p
 constexpr int kOffSc = kOffChain + 128;                               // double [256][4]
 constexpr int kOffT = kOffSc + 4 * kGpMaxObs * 8;
 template <typename T>
+constexpr int kGpInv = sizeof(T) == 4 ? 16 : 2;   // inverse factors kept (the FP32 solve reads all)
+template <typename T>
 constexpr int gp_lds_bytes()
 {
-    // two columns of tiles (the one being factored and the one being read), the right-hand side;
-    // the FP32 refinement adds the diagonal factors and their reciprocal pivots, z, alpha and the
-    // partial products of a block step
-    return kOffT + (int)sizeof(T) * (2 * 16 * kTile + kGpMaxObs) +
-           (sizeof(T) == 4 ? 4 * (16 * kTile + 3 * kGpMaxObs + 16 * 16) : 0);
+    // two columns of tiles (the one being written and the one being read), the diagonal tile, the
+    // inverse factors, the right-hand side and z; the FP32 refinement adds alpha and the partial
+    // products of a block step
+    return kOffT + (int)sizeof(T) * (2 * 16 * kFrag + (1 + kGpInv<T>) * kTile + 2 * kGpMaxObs) +
+           (sizeof(T) == 4 ? 4 * (kGpMaxObs + 16 * 16) : 0);
 }
 
 struct GpTheta {
@@ -79,13 +88,20 @@ __device__ __forceinline__ GpTheta gp_theta(const double *u)
     return h;
 }
 
+// sin(u - v) from p = (sin, cos) u, q = (sin, cos) v
+__device__ __forceinline__ double sin_diff(double2 p, double2 q)
+{
+    return fma(p.x, q.y, -(p.y * q.x));
+}
+
 // The kernel at input differences d1, d2, with s1, s2 the sines of pi d / P.
 template <typename T>
 __device__ __forceinline__ T gp_cov(double d1, double d2, double s1, double s2, const GpTheta &h)
 {
     if constexpr (sizeof(T) == 8) {
         const double a1 = d1 * h.il1, a2 = d2 * h.il2;
-        return h.sf2 * exp(-0.5 * (a1 * a1 + a2 * a2) - 2.0 * (s1 * s1 + s2 * s2) * h.ilp2);
+        const double a = fma(a1, a1, a2 * a2), s = fma(s1, s1, s2 * s2);
+        return h.sf2 * exp(fma(a, -0.5, -(h.ilp2 * (s + s))));
     } else {
         const float a1 = (float)(d1 * h.il1), a2 = (float)(d2 * h.il2);
         const float f1 = (float)s1, f2 = (float)s2;
@@ -106,16 +122,26 @@ __device__ __forceinline__ T gp_entry(const double *xs, const double *sc, int n,
     // (the combined sine of a point and itself is a rounding error, not 0: below l_p = 1e-15 its
     // square counts)
     if (row == col) return (T)h.sf2 + (T)h.sn2;
-    const double *pa = sc + 4 * row, *pb = sc + 4 * col;
+    const double2 *pa = (const double2 *)(sc + 4 * row), *pb = (const double2 *)(sc + 4 * col);
     return gp_cov<T>(xs[2 * row] - xs[2 * col], xs[2 * row + 1] - xs[2 * col + 1],
-                     pa[0] * pb[1] - pa[1] * pb[0], pa[2] * pb[3] - pa[3] * pb[2], h);
+                     sin_diff(pa[0], pb[0]), sin_diff(pa[1], pb[1]), h);
 }
 
-// log N(y; 0, K_theta + sigma_n^2 I) at u = log theta with the factorisation in T.  Called by
-// every thread of the workgroup with the same u (the result is uniform); the inputs and
-// targets must be staged at kOffXs / kOffYs.  failed = a pivot was not positive.  A negative
-// spin_max makes the evaluation fail as timed out at once (a host-set test mode of the failure
-// path).
+// sum_c a_c b_c as a row of sixteen lanes' pairwise exchanges give it to its first lane, the first
+// exchange's sum fused with the lane's own product
+template <typename T>
+__device__ __forceinline__ T dot16(const T (&a)[16], const T (&b)[16])
+{
+    auto f = [&](int i, int j) { return fma(a[i], b[i], a[j] * b[j]); };
+    return ((f(0, 1) + f(2, 3)) + (f(7, 6) + f(5, 4))) +
+           ((f(15, 14) + f(13, 12)) + (f(8, 9) + f(10, 11)));
+}
+
+// -|z|^2 / 2 - sum_i log L_ii of N(y; 0, K_theta + sigma_n^2 I) at u = log theta with the
+// factorisation in T.  Called by every thread of the workgroup with the same u (the result is
+// uniform); the inputs and targets must be staged at kOffXs / kOffYs.  failed = a pivot was not
+// positive.  A negative spin_max makes the evaluation fail as timed out at once (a host-set test
+// mode of the failure path).
 //
 // A function of its own rather than inlined in the chain's loop: there, the loop's state and what
 // the compiler hoists out of it (addresses, the math functions' constants) took registers that
@@ -138,18 +164,17 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
     typedef typename M::v4 v4;
     const double *xs = (const double *)(smem + kOffXs);
     const double *ys = (const double *)(smem + kOffYs);
-    double *red = (double *)(smem + kOffMisc);
+    double *red = (double *)(smem + kOffMisc);   // log det / 2, |z|^2, partial sums, root products
     int *flag = (int *)(red + 16);
     double *sc = (double *)(smem + kOffSc);
-    T *pan = (T *)(smem + kOffT);    // [2][16] tiles
-    T *yb = pan + 2 * 16 * kTile;
+    T *pan = (T *)(smem + kOffT);    // [2][16] panel tiles
+    T *dg = pan + 2 * 16 * kFrag;    // the diagonal tile, in rows
+    T *li = dg + kTile;              // [kGpInv] inverse factors, in rows
+    T *yb = li + kGpInv<T> * kTile;
+    T *zb = yb + kGpMaxObs;
     constexpr bool refine = sizeof(T) == 4;
-    // FP32 refinement: L_JJ of every block and its reciprocal pivots, z, alpha = L^{-T} z, the
-    // partial products of one block step
-    float *ldg = (float *)(yb + kGpMaxObs);
-    float *rdg = ldg + 16 * kTile;
-    float *zall = rdg + kGpMaxObs;
-    float *alpha = zall + kGpMaxObs;
+    // FP32 refinement: alpha = L^{-T} z, the partial products of one block step
+    float *alpha = (float *)(zb + kGpMaxObs);
     float *part = alpha + kGpMaxObs;
     if (spin_max < 0) return GpResult{-INFINITY, 1, 1};
     // the thread index, opaque to the compiler in each evaluation and each block column: keeps
@@ -158,6 +183,7 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane0 = tid & 63, w = uniform_i(tid >> 6);
+    n = uniform_i(n);   // (an argument arrives in a vector register)
     const int NT = (n + 15) >> 4, NTT = NT * (NT + 1) / 2;
     const GpTheta h = gp_theta(u);
 
@@ -168,17 +194,18 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
         sincospi(xs[2 * i + 1] * h.iper, &s1, &c1);
         sc[4 * i] = s0; sc[4 * i + 1] = c0; sc[4 * i + 2] = s1; sc[4 * i + 3] = c1;
     }
-    if (tid == 0) *flag = 0;
+    if (tid == 0) { *flag = 0; red[0] = red[1] = 0.0; }
     __syncthreads();
 
-    // The wave's tiles, four at a time through its share of the column buffers: the entries'
-    // code then stands in a loop over tiles, with a lane's four entries side by side, instead of
-    // once per register slot.
+    // The wave's tiles, four at a time through its share of the panel buffers: the entries' code
+    // then stands in a loop over tiles, with a lane's four entries side by side, instead of once
+    // per register slot.  Lane l, register r of tile (I, K): row 16 I + (l & 15), column
+    // 16 K + M::row(l, r).
     int tI[kGpSlots], tK[kGpSlots];
     v4 acc[kGpSlots];
 #pragma unroll
     for (int s0 = 0; s0 < kGpSlots; s0 += 4) {
-        T *stage = pan + 4 * w * kTile;
+        T *stage = pan + 4 * w * kFrag + 4 * lane0;
 #pragma unroll 1
         for (int q = 0; q < 4; ++q) {
             const int t = w + kGpWaves * (s0 + q);
@@ -186,34 +213,32 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
             const int l = lane0;
             int I, K;
             tile_ik(t, I, K);
-            const int col = 16 * K + (l & 15);
+            const int row = 16 * I + (l & 15);
             v4 e;
             if (I > K && 16 * I + 16 <= n) {   // all observations, all below the diagonal
-                const double2 xc = *(const double2 *)(xs + 2 * col);
-                const double2 c1 = *(const double2 *)(sc + 4 * col);
-                const double2 c2 = *(const double2 *)(sc + 4 * col + 2);
+                const double2 xr = *(const double2 *)(xs + 2 * row);
+                const double2 r1 = *(const double2 *)(sc + 4 * row);
+                const double2 r2 = *(const double2 *)(sc + 4 * row + 2);
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int row = 16 * I + M::row(l, r);
-                    const double2 xr = *(const double2 *)(xs + 2 * row);
-                    const double2 r1 = *(const double2 *)(sc + 4 * row);
-                    const double2 r2 = *(const double2 *)(sc + 4 * row + 2);
-                    e[r] = gp_cov<T>(xr.x - xc.x, xr.y - xc.y, r1.x * c1.y - r1.y * c1.x,
-                                     r2.x * c2.y - r2.y * c2.x, h);
+                    const int col = 16 * K + M::row(l, r);
+                    const double2 xc = *(const double2 *)(xs + 2 * col);
+                    const double2 c1 = *(const double2 *)(sc + 4 * col);
+                    const double2 c2 = *(const double2 *)(sc + 4 * col + 2);
+                    e[r] = gp_cov<T>(xr.x - xc.x, xr.y - xc.y, sin_diff(r1, c1), sin_diff(r2, c2), h);
                 }
             } else {
 #pragma unroll 1
                 for (int r = 0; r < 4; ++r) {
-                    const T v = gp_entry<T>(xs, sc, n, 16 * I + M::row(l, r), col, h);
+                    const T v = gp_entry<T>(xs, sc, n, row, 16 * K + M::row(l, r), h);
                     e[0] = r == 0 ? v : e[0];
                     e[1] = r == 1 ? v : e[1];
                     e[2] = r == 2 ? v : e[2];
                     e[3] = r == 3 ? v : e[3];
                 }
             }
-            store_tile<T>(e, stage + q * kTile, l);
+            *(v4 *)(stage + q * kFrag) = e;
         }
-        wave_sync();
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int s = s0 + q;
@@ -222,128 +247,132 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
                 int I = -1, K = -1;
                 if (t < NTT) {
                     tile_ik(t, I, K);
-                    load_tile<T>(acc[s], stage + q * kTile, lane0);
+                    acc[s] = *(const v4 *)(stage + q * kFrag);
                 } else {
 #pragma unroll
                     for (int r = 0; r < 4; ++r) acc[s][r] = T(0);
                 }
-                tI[s] = I;
-                tK[s] = K;
+                tI[s] = uniform_i(I);
+                tK[s] = uniform_i(K);
             }
         }
-        wave_sync();
     }
-    __syncthreads();   // the column buffers are free
-    double det = 1.0, quad = 0.0;    // wave 0
-    int ebits = 0;
-    for (int J = 0; J < NT; ++J) {
+    // Block column J = 0..NT: the elimination of column J, the update of the later tiles by column
+    // J - 1 and the forward solve of block J - 1 side by side, then the panel of column J.
+    for (int J = 0;; ++J) {
         int l = lane0;
         asm volatile("" : "+v"(l));
-        T *cur = pan + (J & 1) * 16 * kTile;
-        const T *prv = pan + ((J & 1) ^ 1) * 16 * kTile;   // column J - 1 of the factor
-        struct Ops {
-            T i[4], k[4];
-        };
-        auto operands = [&](Ops &o, int I, int K) {        // of L_I,J-1 and L_K,J-1
-            const T *pI = prv + I * kTile + (l & 15) * kTileLd + (l >> 4);
-            const T *pK = prv + K * kTile + (l & 15) * kTileLd + (l >> 4);
+        T *cur = pan + (J & 1) * 16 * kFrag;
+        const T *prv = pan + ((J & 1) ^ 1) * 16 * kFrag;   // column J - 1 of the factor
+        // A_IK^T -= L_K,J-1 L_I,J-1^T
+        auto multiply = [&](v4 &a, const v4 &oK, const v4 &oI) {
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) { o.i[ks] = -pI[4 * ks]; o.k[ks] = pK[4 * ks]; }
+            for (int ks = 0; ks < 4; ++ks) a = M::mma(oK[ks], -oI[ks], a);
         };
-        auto multiply = [&](v4 &a, const Ops &o) {         // A_IK -= L_I,J-1 L_K,J-1^T
+        auto operand = [&](int I) { return *(const v4 *)(prv + I * kFrag + 4 * l); };
+        const int tJ = J * (J + 3) / 2;                    // the diagonal tile
+        const int pw = tJ & (kGpWaves - 1);
+        if (J < NT && w == pw) {
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) a = M::mma(o.i[ks], o.k[ks], a);
-        };
-        // column J's tiles first
+            for (int s = 0; s < kGpSlots; ++s) {
+                if (w + kGpWaves * s == tJ) {
+                    if (J > 0) {
+                        const v4 o = operand(J);
+                        multiply(acc[s], o, o);
+                    }
 #pragma unroll
-        for (int s = 0; s < kGpSlots; ++s) {
-            if (tK[s] == J) {
-                if (J > 0) {
-                    Ops o;
-                    operands(o, tI[s], J);
-                    multiply(acc[s], o);
+                    for (int r = 0; r < 4; ++r) dg[(l & 15) * kTileLd + M::row(l, r)] = acc[s][r];
                 }
-                store_tile<T>(acc[s], cur + tI[s] * kTile, l);
             }
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        __syncthreads();
-        const int rows = 16 * (NT - 1 - J);                // rows below the diagonal tile
-        if (w == 0 || kGpRowLanes * w < rows) {
-            const int below = kGpRowLanes * w + (l - 16);  // the lane's row among them
-            const bool prow = l >= 16 && l < 63 && below < rows;
-            const int row = 16 * J + (l < 16 ? l : (prow ? 16 + below : 0));
-            T *rp = cur + (row >> 4) * kTile + (row & 15) * kTileLd;
-            const T *src = l == 63 ? yb + 16 * J : rp;
-            T a[16], iv[16];
+            wave_sync();
+            T a[16];
 #pragma unroll
-            for (int c = 0; c < 16; ++c) a[c] = src[c];
-            double p0, p1;
+            for (int c = 0; c < 16; ++c) {
+                const T v = dg[(l & 15) * kTileLd + c];
+                a[c] = !(l & 16) ? v : (l & 15) == c ? T(1) : T(0);
+            }
+            double roots;
             int bad;
-            eliminate<T>(a, iv, p0, p1, bad);
-            if (prow) {
+            eliminate<T>(a, roots, bad);
+            if ((l >> 4) == 1) {   // lane 16 + c: column c of the inverse
+                T *lj = li + (J & (kGpInv<T> - 1)) * kTile + (l & 15);
 #pragma unroll
-                for (int c = 0; c < 16; ++c) rp[c] = a[c];
+                for (int r = 0; r < 16; ++r) lj[r * kTileLd] = a[r];
             }
-            // y_I -= L_IJ z_J, z_J in the last lane
-            T y0 = T(0), y1 = T(0);
-#pragma unroll
-            for (int c = 0; c < 16; c += 2) {
-                y0 += a[c] * readlane_t(a[c], 63);
-                y1 += a[c + 1] * readlane_t(a[c + 1], 63);
-            }
-            if (prow) yb[row] -= y0 + y1;
-            if (w == 0) {
-                // the determinant as mantissa and exponent, |z|^2 in the last lane
-                ebits += __builtin_amdgcn_frexp_exp(p0) + __builtin_amdgcn_frexp_exp(p1);
-                det *= __builtin_amdgcn_frexp_mant(p0) * __builtin_amdgcn_frexp_mant(p1);
-                ebits += __builtin_amdgcn_frexp_exp(det);
-                det = __builtin_amdgcn_frexp_mant(det);
-                if (l == 0 && bad) *flag = 1;
-#pragma unroll
-                for (int c = 0; c < 16; ++c) quad = fma((double)a[c], (double)a[c], quad);
-                if constexpr (refine) {
-                    if (l < 16) {
-#pragma unroll
-                        for (int c = 0; c < 16; ++c) ldg[J * kTile + l * kTileLd + c] = (float)a[c];
-                    }
-                    if (l == 63) {
-#pragma unroll
-                        for (int c = 0; c < 16; ++c) zall[16 * J + c] = (float)a[c];
-                    }
-                    if (l == 0) {
-#pragma unroll
-                        for (int c = 0; c < 16; ++c) rdg[16 * J + c] = (float)iv[c];
-                    }
-                }
+            if (l == 0) {
+                red[10 + (J & 1)] = roots;
+                if (bad) *flag = 1;
             }
         }
-        // the tiles of the later columns take column J - 1
         if (J > 0) {
+            if (w == ((pw + 2) & (kGpWaves - 1))) {
+                // the forward solve of block J - 1, one row per lane
+                const int j0 = 16 * (J - 1);
+                T a[16], b[16];
+                if (l < 16) {
+                    const T *lj = li + ((J - 1) & (kGpInv<T> - 1)) * kTile + l * kTileLd;
 #pragma unroll
-            for (int s = 0; s < kGpSlots; s += 2) {   // two tiles' operands and products together
+                    for (int c = 0; c < 16; ++c) { a[c] = lj[c]; b[c] = yb[j0 + c]; }
+                    zb[j0 + l] = dot16<T>(a, b);
+                }
+                wave_sync();
+#pragma unroll
+                for (int c = 0; c < 16; ++c) b[c] = zb[j0 + c];
+                double q2 = fma((double)b[0], (double)b[0], (double)b[1] * (double)b[1]);
+#pragma unroll
+                for (int c = 2; c < 16; ++c) q2 = fma((double)b[c], (double)b[c], q2);
+                const double ld = log(red[10 + ((J - 1) & 1)]);
+                if (l == 0) {
+                    red[0] += ld;
+                    red[1] += q2;
+                }
+                for (int i = l; i < 16 * (NT - J); i += 64) {
+                    const T *fr = prv + (J + (i >> 4)) * kFrag + 4 * (i & 15);
+#pragma unroll
+                    for (int g = 0; g < 4; ++g) {
+                        const v4 o = *(const v4 *)(fr + 64 * g);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) a[M::row(16 * g, r)] = o[r];
+                    }
+                    yb[16 * J + i] -= dot16<T>(a, b);
+                }
+            }
+            // the tiles of this and the later columns take column J - 1, two at a time
+#pragma unroll
+            for (int s = 0; s < kGpSlots; s += 2) {
                 const int s1 = s + 1 < kGpSlots ? s + 1 : s;
-                const bool b0 = tK[s] > J, b1 = s1 > s && tK[s1] > J;
-                if (b0 || b1) {
-                    Ops o0, o1;   // (a tile that is not due reads its own, unused)
-                    operands(o0, max(tI[s], 0), max(tK[s], 0));
-                    operands(o1, max(tI[s1], 0), max(tK[s1], 0));
-                    if (b0) multiply(acc[s], o0);
-                    if (b1) multiply(acc[s1], o1);
+                const bool b0 = tK[s] >= J && w + kGpWaves * s != tJ;
+                const bool b1 = s1 > s && tK[s1] >= J && w + kGpWaves * s1 != tJ;
+                if (b0 || b1) {   // (a tile that is not due reads its own operands, unused)
+                    const v4 i0 = operand(max(tI[s], 0)), k0 = operand(max(tK[s], 0));
+                    const v4 i1 = operand(max(tI[s1], 0)), k1 = operand(max(tK[s1], 0));
+                    if (b0) multiply(acc[s], k0, i0);
+                    if (b1) multiply(acc[s1], k1, i1);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
         __syncthreads();
-        if constexpr (refine) {   // the factor's tiles, kept for the solve
+        if (J == NT) break;
+        // the panel: L_IJ^T = L_JJ^{-1} A_IJ^T
+        T lf[4];
 #pragma unroll
-            for (int s = 0; s < kGpSlots; ++s)
-                if (tK[s] == J && tI[s] > J) load_tile<T>(acc[s], cur + tI[s] * kTile, l);
+        for (int ks = 0; ks < 4; ++ks)
+            lf[ks] = li[(J & (kGpInv<T> - 1)) * kTile + (l & 15) * kTileLd + M::row(l, ks)];
+#pragma unroll
+        for (int s = 0; s < kGpSlots; ++s) {
+            if (tK[s] == J && tI[s] > J) {
+                v4 o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o[r] = T(0);
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks) o = M::mma(lf[ks], acc[s][ks], o);
+                *(v4 *)(cur + tI[s] * kFrag + 4 * l) = o;
+                if constexpr (refine) acc[s] = o;   // kept for the solve
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-    }
-    if (w == 0 && lane0 == 63) {
-        red[0] = 0.5 * (log(det) + (double)ebits * 0.69314718055994530942);
-        red[1] = quad;
+        __syncthreads();
     }
     if constexpr (refine) {
         // alpha = L^{-T} z, block rows from the last: alpha_J = L_JJ^{-T} (z_J - sum_{I > J}
@@ -354,39 +383,30 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
 #pragma unroll
             for (int s = 0; s < kGpSlots; ++s) {
                 if (tK[s] == J && tI[s] > J) {
-                    float v = 0.f;
+                    const float al = alpha[16 * tI[s] + (l & 15)];
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        v += (float)acc[s][r] * alpha[16 * tI[s] + M::row(l, r)];
-                    v += __shfl_xor(v, 16, 64);
-                    v += __shfl_xor(v, 32, 64);
-                    if (l < 16) part[16 * tI[s] + l] = v;
+                    for (int r = 0; r < 4; ++r) {
+                        const float v = row_sum16((float)acc[s][r] * al);
+                        if ((l & 15) == 0) part[16 * tI[s] + M::row(l, r)] = v;
+                    }
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
             __syncthreads();
-            if (w == 0) {
-                // lane i: component i, with column i of L_JJ (a solve from the last row up)
+            if (w == 0) {   // lane i: component i
                 const int i = l & 15;
-                float wv = zall[16 * J + i];
+                float wv = zb[16 * J + i], a0 = 0.f, a1 = 0.f;
                 for (int I = J + 1; I < NT; ++I) wv -= part[16 * I + i];
-                float lc[16];
 #pragma unroll
-                for (int c = 0; c < 16; ++c) lc[c] = ldg[J * kTile + c * kTileLd + i];
-                const float rv = rdg[16 * J + i];
-                float al = 0.f;
-#pragma unroll
-                for (int c = 15; c >= 0; --c) {
-                    const float ac = readlane_t(wv * rv, c);
-                    if (i == c) al = ac;
-                    if (i < c) wv -= lc[c] * ac;
+                for (int c = 0; c < 16; c += 2) {
+                    a0 += (float)li[J * kTile + c * kTileLd + i] * readlane_t(wv, c);
+                    a1 += (float)li[J * kTile + (c + 1) * kTileLd + i] * readlane_t(wv, c + 1);
                 }
-                if (l < 16) alpha[16 * J + l] = al;
+                if (l < 16) alpha[16 * J + l] = a0 + a1;
             }
             __syncthreads();
         }
     }
-    __syncthreads();
     const double ld = red[0];
     double q = red[1];
     const int failed = *flag;
@@ -416,7 +436,15 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
         q = qv;
     }
     __syncthreads();   // the LDS slots are reused by the next evaluation
-    return GpResult{-0.5 * q - ld - 0.5 * (double)n * LOG_2PI, failed, 0};
+    return GpResult{fma(q, -0.5, -ld), failed, 0};
+}
+
+// n/2 log(2 pi), rounded: log L of a chain's point is the evaluator's value less this
+__device__ __forceinline__ double gp_norm(int n)
+{
+    double c = 0.5 * (double)n * LOG_2PI;
+    asm volatile("" : "+v"(c));   // (not fused with the subtraction)
+    return c;
 }
 
 template <typename T>
@@ -490,6 +518,7 @@ __global__ __launch_bounds__(kGpThreads) void k_eval_gp(Launch Lc, const double 
     double L;
     if constexpr (MODE == MODE_FP64) L = gp_eval<double>(u, P.gp_n, smem, failed, timed_out);
     else L = gp_eval<float>(u, P.gp_n, smem, failed, timed_out);
+    L = fma(-0.5 * (double)P.gp_n, LOG_2PI, L);
     if (timed_out && from_run && threadIdx.x == 0) atomicAdd(&R.ctr[10], 1ull);
     if (threadIdx.x == 0) {
         unsigned long long nf = 0;
@@ -534,6 +563,7 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
     unsigned long long c_evals = 0, c_tests = 0, c_prej = 0, c_outcap = 0, c_shcap = 0,
                        c_nonfin = 0, c_rc = 0, c_viol = 0, c_wait = 0;
     const int spin_max = P.gp_spin_max;
+    const double norm = gp_norm(n);
     __syncthreads();
 
     // log prior density (Gaussian prior; the box prior is uniform on its support)
@@ -547,8 +577,8 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
         return lp + P.logprior_norm;
     };
 
-    // The chain as one loop with a single evaluation site (the evaluator is large and fully
-    // inlined): each pass picks the next test of the current phase, evaluates it and advances.
+    // The chain as one loop with a single evaluation site: each pass picks the next test of the
+    // current phase, evaluates it and advances.
     enum { PH_NEW = 0, PH_LEFT = 1, PH_RIGHT = 2, PH_SHRINK = 3, PH_FINAL = 4 };
     int phase = PH_NEW, st = 0, nl = 0, nr = 0, ns = 0;
     double tL = 0.0, tR = 0.0, logy = -INFINITY;
@@ -636,7 +666,7 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
             // the single evaluation site
             bool failed = false, tout = false;
             if constexpr (MODE == MODE_FP64) {
-                L = gp_eval<double>(y, n, smem, failed, tout, spin_max);
+                L = gp_eval<double>(y, n, smem, failed, tout, spin_max) - norm;
                 c_wait += uniform_i(tout);
             } else {
                 int need64 = (phase == PH_FINAL);
@@ -644,13 +674,13 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
                     need64 = 1;
                     ++c_rc;
                 } else if (!need64) {
-                    L = gp_eval<float>(y, n, smem, failed, tout, spin_max);
+                    L = gp_eval<float>(y, n, smem, failed, tout, spin_max) - norm;
                     c_wait += uniform_i(tout);
                     need64 = uniform_i((failed && !tout) || !(L == L) || gp_near(L, Lstar, P, y));
                     if (need64) ++c_rc; else exact = 0;
                 }
                 if (need64) {
-                    L = gp_eval<double>(y, n, smem, failed, tout, spin_max);
+                    L = gp_eval<double>(y, n, smem, failed, tout, spin_max) - norm;
                     c_wait += uniform_i(tout);
                 }
             }
