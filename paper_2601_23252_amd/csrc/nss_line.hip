@@ -1,5 +1,5 @@
 // gfx950 HRSS chains evaluated along each step's line: likelihoods of quadratic forms (Gaussian
-// mixtures, Neal's funnel), and the Gaussian-Rastrigin likelihood's sum over coordinates.
+// mixtures), and those summed over a candidate's coordinates (Neal's funnel, Gaussian-Rastrigin).
 //
 // A step's candidates all lie on x + t v, and a form |W (x + t v - mu)|^2 is on that line the
 // parabola a + 2 b t + g t^2 with a = |W (x - mu)|^2, b = W (x - mu) . W v, g = |W v|^2.  The
@@ -36,6 +36,12 @@
 // steps: 25.4 ms a launch with points and 7.4 here; a pass takes 3,000 cycles of FP64 arithmetic,
 // eight polynomials side by side for their latency (two: 8.6 ms).
 //
+// The funnel's radius is a parabola too, but exp(-v) weighs it by up to e^20 in the neck, where it
+// is far smaller than at a point in the mouth: there a parabola's rounding, relative to the larger
+// one, decided (1e-6 of log L at v = -18).  It is summed from each candidate's coordinates in the
+// same way, which costs what the products with the directions did (32 funnels of d <= 128 beside 32
+// Gaussians, 55.9 ms a pass with the parabola and 55.2 so).
+//
 // The random walk's proposals x + u_n are the same products at t = 1: a block's fifteen are tested
 // at once from the current point, and again after each acceptance, their moves in registers for
 // the box (d = 50, 500 chains of 250 steps: 364 us a launch with points, 122 here; 175 with the
@@ -70,19 +76,19 @@ constexpr int kLineForms = 16;          // most components
 // t, and the shrink uniforms of a later pass; the final points' FP64 tile overlays the Gram
 // matrices.
 struct LineLayout {
-    int gram, x, v, us, tt, su, chain;  // per-chain offsets and stride (v: Gaussian-Rastrigin's
-                                        // direction, the random walk's block of proposals)
+    int gram, x, v, us, tt, su, chain;  // per-chain offsets and stride (v: the direction where
+                                        // candidates are points, the walk's block of proposals)
     int mu, pa, ipb;                    // the workgroup's means and Gaussian prior (1 / std)
     int cand, q, L, mask, total;
 };
 __host__ __device__ inline LineLayout line_layout(int D, int K, int lik, bool box, bool rw)
 {
-    const int forms = (lik == LIK_MIXTURE ? K : lik == LIK_RG ? 0 : 1) + (box ? 0 : 1);
+    const int forms = (lik == LIK_MIXTURE ? K : 0) + (box ? 0 : 1);
     LineLayout o;
     int off = 0;
     o.gram = off; off += al16(forms * 16 * kLineLd * 8);
     o.x = off; off += al16(D * 8);
-    o.v = off; off += rw ? al16(kLineB * (D + 1) * 8) : lik == LIK_RG ? al16(D * 8) : 0;
+    o.v = off; off += rw ? al16(kLineB * (D + 1) * 8) : lik != LIK_MIXTURE ? al16(D * 8) : 0;
     o.us = off; off += 16 * kStepU * 8;
     o.tt = off; off += 16 * 16 * 8;
     o.su = off; off += 16 * 8;
@@ -189,7 +195,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
     const LineLayout lay = line_layout(D, P.K, LIK, BOX, RW);
     const int tid = threadIdx.x, w = uniform_i(tid >> 6), l = tid & 63;
     const int col = l & 15, row = l >> 4;
-    const int d = P.d, K = MIX ? P.K : (RG ? 0 : 1), C = R.C, p = R.p;
+    const int d = P.d, K = MIX ? P.K : 0, C = R.C, p = R.p;
     const double Lstar = R.scal[0], beta = Lstar;   // tempered: the inverse temperature
     const int t0 = R.iscal[1], nsurv = R.iscal[2];
     const uint32_t it = (uint32_t)R.iscal[3] + 1u;
@@ -431,24 +437,18 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                     }
                     put(gpri, Gp);
                 }
-            } else if (!RG || !BOX) {
-                // the funnel's form: the coordinates after the first (and the Gaussian prior's)
+            } else if (!BOX) {   // the Gaussian prior's form alone
                 const bool dcol = col < nb;
                 const auto vrow = dirs + (size_t)(s0 + (dcol ? col : 0)) * D;
-                d4v G = (d4v){0.0, 0.0, 0.0, 0.0}, Gp = (d4v){0.0, 0.0, 0.0, 0.0};
+                d4v Gp = (d4v){0.0, 0.0, 0.0, 0.0};
 #pragma unroll 16
                 for (int ks = 0; ks < NKS; ++ks) {
                     const int kk = 4 * ks + row;
                     const double bv = dcol ? vrow[kk] : (xcol ? xs[kk] : 0.0);
-                    const double bb = kk > 0 ? bv : 0.0;
-                    if (!RG) G = __builtin_amdgcn_mfma_f64_16x16x4f64(bb, bb, G, 0, 0, 0);
-                    if (!BOX) {
-                        const double bp = kk < d ? (xcol ? bv - spa[kk] : bv) * sipb[kk] : 0.0;
-                        Gp = __builtin_amdgcn_mfma_f64_16x16x4f64(bp, bp, Gp, 0, 0, 0);
-                    }
+                    const double bp = kk < d ? (xcol ? bv - spa[kk] : bv) * sipb[kk] : 0.0;
+                    Gp = __builtin_amdgcn_mfma_f64_16x16x4f64(bp, bp, Gp, 0, 0, 0);
                 }
-                if (!RG) put(gram, G);
-                if (!BOX) put(gpri, Gp);
+                put(gpri, Gp);
             }
             wave_sync();
             // the point's products with the directions (row 15; column 0 is the current step's),
@@ -458,8 +458,8 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             for (int q = 0; q < NR; ++q) {
                 const int c = 4 * q + row;
                 const double *g15 = gram + ((c < K ? c : 0) * 16 + 15) * kLineLd;
-                h[q] = RG ? 0.0 : g15[col];
-                aa[q] = RG ? 0.0 : g15[15];
+                h[q] = MIX ? g15[col] : 0.0;
+                aa[q] = MIX ? g15[15] : 0.0;
             }
             if (!BOX) hp = gpri[15 * kLineLd + col];
             if (s0 + kLineB < p) fetch_block(s0 + kLineB);
@@ -474,7 +474,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
 #pragma unroll
                 for (int q = 0; q < NR; ++q) {
                     const int c = 4 * q + row < K ? 4 * q + row : 0;
-                    dg[q] = gram[(c * 16 + col) * kLineLd + col];
+                    dg[q] = MIX ? gram[(c * 16 + col) * kLineLd + col] : 0.0;
                 }
                 if (!BOX) dgp = gpri[col * kLineLd + col];
                 if constexpr (!MIX) v0c = vs[min(col, kLineB - 1) * LDV];
@@ -538,7 +538,14 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                             in |= (unsigned)__ballot(se > 1.0) & doubt;
                         }
                     } else {
-                        const double s2 = fmax(aa[0] + fma(2.0, h[0], dg[0]), 0.0);
+                        double s2 = 0.0;
+                        const double *vc = vs + min(col, kLineB - 1) * LDV;
+                        for (int a = row ? row : 4; a < d; a += 4) {
+                            const double y = xs[a] + vc[a];
+                            s2 = fma(y, y, s2);
+                        }
+                        s2 += __shfl_xor(s2, 16, 64);
+                        s2 += __shfl_xor(s2, 32, 64);
                         const double vv = lane_value(x0r[0], 0) + v0c;
                         const double Lc = -vv * vv / 18.0 - 0.5 * (LOG_2PI + log(9.0)) -
                                           0.5 * exp(-vv) * s2 -
@@ -559,12 +566,19 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
 #pragma unroll
                         for (int i = 0; i < NA; ++i)
                             if (l + 64 * i < D) x0r[i] += vs[s * LDV + l + 64 * i];
+                        if constexpr (MIX) {
 #pragma unroll
-                        for (int q = 0; q < NR; ++q) {
-                            const int c = 4 * q + row < K ? 4 * q + row : 0;
-                            const double hs = __shfl(h[q], (l & 48) | s, 64);
-                            aa[q] += fma(2.0, hs, __shfl(dg[q], (l & 48) | s, 64));
-                            h[q] += gram[(c * 16 + s) * kLineLd + col];
+                            for (int q = 0; q < NR; ++q) {
+                                const int c = 4 * q + row < K ? 4 * q + row : 0;
+                                const double hs = __shfl(h[q], (l & 48) | s, 64);
+                                aa[q] += fma(2.0, hs, __shfl(dg[q], (l & 48) | s, 64));
+                                h[q] += gram[(c * 16 + s) * kLineLd + col];
+                            }
+                        } else {
+                            wave_sync();
+#pragma unroll
+                            for (int i = 0; i < NA; ++i) if (l + 64 * i < D) xs[l + 64 * i] = x0r[i];
+                            wave_sync();
                         }
                         if (!BOX) hp += gpri[s * kLineLd + col];
                     }
@@ -580,7 +594,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             double tn = tt[col], grn[NR], gpn = 0.0;   // the next step's, read ahead
 #pragma unroll
             for (int q = 0; q < NR; ++q)
-                grn[q] = RG ? 0.0 : gram[((4 * q + row < K ? 4 * q + row : 0) * 16) * kLineLd + col];
+                grn[q] = MIX ? gram[((4 * q + row < K ? 4 * q + row : 0) * 16) * kLineLd + col] : 0.0;
             if (!BOX) gpn = gpri[col];
             for (int sb = 0; sb < nb; ++sb) {
                 const int st = s0 + sb;
@@ -614,7 +628,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
 #pragma unroll
                     for (int q = 0; q < NR; ++q) {
                         const int c = 4 * q + row < K ? 4 * q + row : 0;
-                        if (!RG) grn[q] = gram[(c * 16 + sn) * kLineLd + min(sn + col, 15)];
+                        if (MIX) grn[q] = gram[(c * 16 + sn) * kLineLd + min(sn + col, 15)];
                     }
                     if (!BOX) gpn = gpri[sn * kLineLd + min(sn + col, 15)];
                 }
@@ -623,10 +637,14 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                     v0 = lane_value(vr[0], 0);
                     x00 = lane_value(x0r[0], 0);
                 }
-                if constexpr (RG) {   // the point and the direction, for the coordinate sums
+                if constexpr (!MIX) {   // the point and the direction, for the coordinate sums
+                    const bool sum0 = RG || l > 0;   // (not the funnel's v)
 #pragma unroll
                     for (int i = 0; i < NA; ++i)
-                        if (l + 64 * i < D) { xs[l + 64 * i] = x0r[i]; vs[l + 64 * i] = vr[i]; }
+                        if (l + 64 * i < D) {
+                            xs[l + 64 * i] = i > 0 || sum0 ? x0r[i] : 0.0;
+                            vs[l + 64 * i] = i > 0 || sum0 ? vr[i] : 0.0;
+                        }
                     wave_sync();
                 }
                 // box prior: t inside [tin0, tin1] keeps every coordinate in the box whatever
@@ -765,7 +783,19 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                                       doubt;
                         }
                     } else {
-                        const double s2 = fmax(fma(t, fma(t, g[0], b2[0]), aa[0]), 0.0);
+                        // the lane's coordinates 8 i + 2 row, + 1
+                        double q0 = 0.0, q1 = 0.0;
+#pragma unroll 4
+                        for (int a = 2 * row; a < d; a += 8) {   // (zero from d up)
+                            const double2 x2 = *(const double2 *)(xs + a);
+                            const double2 v2 = *(const double2 *)(vs + a);
+                            const double y0 = fma(t, v2.x, x2.x), y1 = fma(t, v2.y, x2.y);
+                            q0 = fma(y0, y0, q0);
+                            q1 = fma(y1, y1, q1);
+                        }
+                        double s2 = q0 + q1;
+                        s2 += __shfl_xor(s2, 16, 64);
+                        s2 += __shfl_xor(s2, 32, 64);
                         const double vv = fma(t, v0, x00);
                         Lv = -vv * vv / 18.0 - 0.5 * (LOG_2PI + log(9.0)) - 0.5 * exp(-vv) * s2
                              - (double)(d - 1) * 0.5 * (vv + LOG_2PI);
