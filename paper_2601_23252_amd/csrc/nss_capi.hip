@@ -8,6 +8,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <map>
 #include <mutex>
 #include <string>
@@ -25,6 +26,7 @@ struct RunHost {
     DevRun R;
     // 16-bit W fragments per format, and the rounded remainders for the split modes
     double wmax = 0.0;   // largest magnitude in the mixture's inverse Cholesky factors
+    double form_max = 0.0;   // bound on its quadratic forms over the prior (several components)
     const uint4 *wf_bf16 = nullptr, *wf_fp16 = nullptr, *wf_bf16_lo = nullptr,
                 *wf_fp16_lo = nullptr;
     int done = 0;
@@ -258,6 +260,50 @@ static uint16_t to_fp16(float f)
 }
 
 
+// With one component the forms of every point and candidate that matter are below the contour's
+// own, which sets what their rounding is relative to.  With several, a far component's form at the
+// chain's point may be anything up to its bound over the prior and rounds a candidate near that
+// component by 1e-16 of it: beyond 1e8 (a few 1e-8 of log L) the candidates are evaluated as
+// points.  (Components of width 1e-9 in a box of 20: the parabola missed log L by 100.)
+constexpr double kLineForm = 1e8;
+
+// Bound on |W (x - mu)|^2 over a prior's support (a Gaussian prior's: ten deviations): the farthest
+// squared distance times the sum of W's squares or, where that is more than `enough`, the square of
+// its largest singular value by power iteration.
+static double form_bound(const double *W, int d, const ns_prior *prior, const double *mu,
+                         double enough)
+{
+    const bool box = prior->kind == NS_PRIOR_BOX;
+    double far2 = 0.0, s2 = 0.0;
+    for (int j = 0; j < d; ++j) {
+        const double lo = box ? prior->a[j] : prior->a[j] - 10.0 * prior->b[j];
+        const double hi = box ? prior->b[j] : prior->a[j] + 10.0 * prior->b[j];
+        const double r = std::max(fabs(lo - mu[j]), fabs(hi - mu[j]));
+        far2 += r * r;
+    }
+    double f2 = 0.0;
+    for (int j = 0; j < d * d; ++j) f2 += W[j] * W[j];
+    if (f2 * far2 <= enough) return f2 * far2;
+    std::vector<double> v(d), u(d);
+    for (int j = 0; j < d; ++j) v[j] = 1.0 + 0.1 * (j % 7);
+    for (int it = 0; it < 20; ++it) {
+        double n2 = 0.0, m2 = 0.0;
+        for (int j = 0; j < d; ++j) n2 += v[j] * v[j];
+        for (int r = 0; r < d; ++r) {   // u = W v (lower triangular), then v = W^T u
+            double t = 0.0;
+            for (int j = 0; j <= r; ++j) t += W[(size_t)r * d + j] * v[j];
+            u[r] = t;
+            m2 += t * t;
+        }
+        s2 = m2 / n2;
+        const double sc = 1.0 / sqrt(m2);
+        std::fill(v.begin(), v.end(), 0.0);
+        for (int r = 0; r < d; ++r)
+            for (int j = 0; j <= r; ++j) v[j] += W[(size_t)r * d + j] * (u[r] * sc);
+    }
+    return s2 * far2;
+}
+
 static ns_status prepare_problem(ns_ctx *ctx, RunHost &rh, const ns_prior *prior,
                                  const ns_energy *en)
 {
@@ -338,6 +384,11 @@ static ns_status prepare_problem(ns_ctx *ctx, RunHost &rh, const ns_prior *prior
                 W[r * D + s] = Wd[r * d + s];
                 if (!(fabs(Wd[r * d + s]) <= rh.wmax)) rh.wmax = fabs(Wd[r * d + s]);
             }
+        if (K > 1) {
+            const double f = form_bound(Wd.data(), d, prior, en->mean + (size_t)c * d,
+                                        kLineForm);
+            if (!(f <= rh.form_max)) rh.form_max = f;
+        }
         for (int j = 0; j < d; ++j) {
             mu[(size_t)c * D + j] = en->mean[(size_t)c * d + j];
             mu32[(size_t)c * D + j] = (float)mu[(size_t)c * D + j];
@@ -482,7 +533,7 @@ static bool line_ok(const RunHost &rh, const ns_prior *prior, const ns_energy *e
     if (rh.lik == LIK_RG) return true;
     for (size_t i = 0; i < (size_t)rh.K * rh.d; ++i)
         if (!fits(en->mean[i])) return false;
-    return rh.wmax <= kLineMax;
+    return rh.wmax <= kLineMax && rh.form_max <= kLineForm;
 }
 
 struct MapBuilder {

@@ -90,3 +90,24 @@ def test_funnel_neck(oracle_lib, rw):
     inside = [np.all(np.abs(y - moves[j]) <= 20.0) for j in first]
     hits = sum((tr[j, 0, 3] if rw else tr[j, 0, 0]) > 0 for j in first)
     assert hits >= max(2, sum(inside) // 2)
+
+
+@pytest.mark.parametrize("rw", [False, True])
+def test_narrow_far_component(oracle_lib, rw):
+    """A component of width 1e-9 three away: its form is 1e18 at the chain's point and 0.5 at the
+    candidate, where L* lies 10 below log L."""
+    from paper_2601_23252_amd import problems as G
+    O = oracle_lib
+    prob = dict(G.mixture_problem(1, 2, 2, m=M, k=K, p=4), mu=np.array([[0.0, 0.0], [3.0, 1.0]]),
+                cov=np.array([np.eye(2), 1e-18 * np.eye(2)]))
+    y = np.array([3.0 + 5e-10, 1.0 - 5e-10])
+    Lstar = O.Problem(prob).loglik(y[None])[0] - 10.0
+    scale = 4.0
+    if rw:
+        kw = dict(replacement="rw", width=1.0)
+        moves = [scale * _direction(O, j, 0, 2) for j in range(K)]
+    else:
+        kw = dict(width=1.0)
+        moves = _slice_moves(O, 2, scale, 1.0)
+    tr = _same_as_points(prob, y, moves, _parents(O), Lstar, scale, **kw)
+    assert np.sum((tr[:, 0, 3] if rw else tr[:, 0, 0]) > 0) >= 3
