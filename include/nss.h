@@ -257,7 +257,8 @@ typedef struct {
     int64_t nonfinite;      /* NaN/+inf log-likelihoods treated as -inf */
     int64_t rechecks;       /* mixed precision: decisions taken on an FP64 re-evaluation
                              * because the 16-bit estimate was within the guard band of L* */
-    int64_t band_violations;/* mixed precision: accepted points whose FP64 logL <= L* */
+    int64_t band_violations;/* accepted points whose FP64 logL <= L* (16-bit tests: kept; along a
+                             * line: dropped, the chain keeps its parent) */
     int64_t whiten_fallbacks; /* iterations whose covariance factorisation failed (diagonal used) */
     int64_t n_dead;         /* dead points recorded */
     double hrss_ms;         /* NS_FLAG_TIMING: summed HRSS kernel time (HIP events) */

@@ -228,11 +228,11 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
     for (int i = 0; i < NA; ++i) { x0r[i] = 0.0; vr[i] = 0.0; }
     double logL0 = -INFINITY;
     bool moved = false;
+    int parent = j;   // tempered SMC: the resampled particle j, gathered into slot j
     unsigned long long c_evals = 0, c_tests = 0, c_outcap = 0, c_shcap = 0, c_viol = 0;
 
     __syncthreads();
     if (has_chain) {
-        int parent = j;   // tempered SMC: the resampled particle j, gathered into slot j
         if constexpr (!TEMP) {
             double u, unused;
             draw2(R.key0, R.key1, PUR_RESAMPLE, (uint32_t)j, it, 0u, 0u, u, unused);
@@ -962,7 +962,14 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
         unsigned long long nonfin = 0;
         // (in FP64 a chain that never moved keeps its parent's value)
         if (moved || !fp64) logL0 = sanitize(T.L[w], nonfin);
-        if (!TEMP && moved && !(logL0 > Lstar)) ++c_viol;
+        if (!TEMP && moved && !(logL0 > Lstar)) {
+            // a form's last bits let in a point on the contour: the chain keeps its parent
+            ++c_viol;
+            logL0 = R.logL[parent];
+#pragma unroll
+            for (int i = 0; i < NA; ++i)
+                if (l + 64 * i < d) x0r[i] = R.X[(size_t)(l + 64 * i) * R.m_pad + parent];
+        }
         const int slot = TEMP ? j : R.perm[j];
 #pragma unroll
         for (int i = 0; i < NA; ++i) {

@@ -111,3 +111,28 @@ def test_narrow_far_component(oracle_lib, rw):
         moves = _slice_moves(O, 2, scale, 1.0)
     tr = _same_as_points(prob, y, moves, _parents(O), Lstar, scale, **kw)
     assert np.sum((tr[:, 0, 3] if rw else tr[:, 0, 0]) > 0) >= 3
+
+
+def test_a_point_on_the_contour_is_not_kept(oracle_lib):
+    """L* equal to the last proposal's own log L, to the last bit: the proposal is not above it,
+    and the chain keeps its parent, whatever a form's last bits say."""
+    from paper_2601_23252_amd import problems as G
+    O = oracle_lib
+    d = 5
+    prob = G.gaussian_problem(d, np.zeros(d), 0.09 * np.eye(d), "box", -20.0, 20.0, m=M, k=K, p=4)
+    kw = dict(replacement="rw", width=1.0)
+    scale = 1.5
+    y = np.full(d, 0.01)
+    moves = [scale * _direction(O, j, 3, d) for j in range(K)]   # the last step's proposal
+    parents = _parents(O)
+    below = O.Problem(prob).loglik(y[None])[0] - 1e-3
+    s, tr = _run(prob, y, moves, parents, below, scale, True, **kw)
+    chains = [j for j in range(K) if parents.index(parents[j]) == j and tr[j, 3, 3] == 1]
+    assert len(chains) >= 5
+    for j in chains:
+        Lstar = s["logL"][j]   # chain j's slot: the deleted points are 0..K-1, L* the last
+        a, _ = _run(prob, y, moves, parents, Lstar, scale, False, **kw)
+        b, _ = _run(prob, y, moves, parents, Lstar, scale, True, **kw)
+        assert np.all(a["logL"] > Lstar)
+        assert np.array_equal(a["x"], b["x"])
+        assert np.array_equal(a["logL"], b["logL"])
