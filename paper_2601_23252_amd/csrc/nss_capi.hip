@@ -513,6 +513,7 @@ static int hrss_blocks(const RunHost &r) { return (r.k + r.R.C - 1) / r.R.C; }  
 // infinity minus infinity would differ from the point evaluation's).
 constexpr int kLineMinSteps = 4;
 constexpr double kLineMax = 1e40;
+constexpr double kLineMaxBox = 1e29, kLineMaxWidth = 1e18;
 static bool line_ok(const RunHost &rh, const ns_prior *prior, const ns_energy *en)
 {
     if (rh.lik == LIK_GP || (rh.lik == LIK_RG && rh.R.rw)) return false;
@@ -522,10 +523,13 @@ static bool line_ok(const RunHost &rh, const ns_prior *prior, const ns_energy *e
     const bool box = rh.P.prior_kind == PRIOR_BOX;
     if (line_lds_bytes(rh.D, rh.K, rh.lik, box, rh.R.rw) > 160 * 1024) return false;
     auto fits = [](double v) { return fabs(v) <= kLineMax; };
+    auto fits_box = [](double v) { return fabs(v) <= kLineMaxBox; };
     for (int j = 0; j < rh.d; ++j)
-        if (!fits(prior->a[j]) || !fits(prior->b[j]) || (!box && !fits(1.0 / prior->b[j])))
+        if (box ? !fits_box(prior->a[j]) || !fits_box(prior->b[j])
+                : !fits(prior->a[j]) || !fits(prior->b[j]) || !fits(1.0 / prior->b[j]))
             return false;
-    if (!fits(rh.R.width)) return false;
+    // (its FP32 bounds of t: distances stay in range, an infinite one lies beyond every t)
+    if (!(rh.R.width <= kLineMaxWidth)) return false;
     if (rh.lik == LIK_FUNNEL) {   // exp(-x_0) has to stay finite
         const double a = prior->a[0], b = prior->b[0];
         return box ? (a >= -600.0 && b <= 600.0) : fabs(a) + 40.0 * b <= 600.0;

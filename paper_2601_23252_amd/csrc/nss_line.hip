@@ -649,7 +649,10 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                 }
                 // box prior: t inside [tin0, tin1] keeps every coordinate in the box whatever
                 // the rounding of x + t v, t outside [tou0, tou1] puts one out; the margins
-                // cover the FP32 quotients and, away from the faces, the rounding of y
+                // cover the FP32 quotients and, away from the faces, the rounding of y.  The
+                // quotients are taken where FP32's range holds them (distances below 1e30 by the
+                // caller's check of the box, |v| in [1e-30, 1e30), the smallest quotient 1e-30;
+                // an infinite one is a coordinate that rests, or lies beyond every t)
                 float tin0 = -INFINITY, tin1 = INFINITY, tou0 = -INFINITY, tou1 = INFINITY;
                 if (BOX) {
                     float m0 = INFINITY, m1 = INFINITY;
@@ -659,10 +662,13 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                         const bool pos = vr[i] > 0.0;
                         const double hi = pbr[i] - x0r[i], lo = x0r[i] - par[i];
                         const float va = fabsf((float)vr[i]), rv = __builtin_amdgcn_rcpf(va);
-                        const bool flat = !(va > 1e-30f);
-                        face = face || !(hi > near_[i]) || !(lo > near_[i]) || (flat && vr[i] != 0.0);
-                        m1 = fminf(m1, flat ? INFINITY : (float)(pos ? hi : lo) * rv);
-                        m0 = fminf(m0, flat ? INFINITY : (float)(pos ? lo : hi) * rv);
+                        constexpr unsigned v0 = __builtin_bit_cast(unsigned, 1e-30f),
+                                           v1 = __builtin_bit_cast(unsigned, 1e30f);
+                        const bool range = __builtin_bit_cast(unsigned, va) - v0 < v1 - v0;
+                        face = face || !(hi > near_[i]) || !(lo > near_[i]) ||
+                               !(range || vr[i] == 0.0);
+                        m1 = fminf(m1, (float)(pos ? hi : lo) * rv);
+                        m0 = fminf(m0, (float)(pos ? lo : hi) * rv);
                     }
                     m1 = wave_min_pos(m1);
                     m0 = wave_min_pos(m0);
@@ -670,7 +676,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                     tin0 = -m0 * (1.f - 2e-5f);
                     tou1 = m1 * (1.f + 2e-5f);
                     tou0 = -m0 * (1.f + 2e-5f);
-                    if (__any(face)) {   // decided coordinate by coordinate
+                    if (__any(face) || fminf(m0, m1) < 1e-30f) {   // coordinate by coordinate
                         tin0 = INFINITY; tin1 = -INFINITY;
                         tou0 = -INFINITY; tou1 = INFINITY;
                     }

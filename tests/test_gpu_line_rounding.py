@@ -136,3 +136,30 @@ def test_a_point_on_the_contour_is_not_kept(oracle_lib):
         assert np.all(a["logL"] > Lstar)
         assert np.array_equal(a["x"], b["x"])
         assert np.array_equal(a["logL"], b["logL"])
+
+
+@pytest.mark.parametrize("edge, scale", [(1e39, 1e38), (1e35, 1e34), (1e-33, 1e-34), (1.0, 1e39),
+                                         (1.0, 1e33), (1e-3, 1e-36)])
+def test_boxes_beyond_single_precision(edge, scale):
+    """Box edges, directions and their quotients outside FP32's range: the same proposals are in
+    the box as for the point-evaluating kernels, which test every coordinate in FP64.  (The
+    likelihood's width is the box's; 400 shrinks bring t from 1 to below 1e-40.)"""
+    from paper_2601_23252_amd import nss, problems as G
+    d = 3
+    prob = G.gaussian_problem(d, np.zeros(d), (0.3 * edge) ** 2 * np.eye(d), "box", -edge, edge,
+                              m=M, k=K, p=9)
+    out = []
+    for shallow in (False, True):
+        R = nss.NSRun(prob, m=M, k=K, p=9, seed=SEED, trace=True, freeze_whitening=True,
+                      shallow_plan=shallow, shrink_cap=400, term_frac=0.0)
+        s = R.state()
+        R.set_state(s["x"], s["logL"], -np.inf, 0.0, 0.0, 0, Lsig=scale * np.eye(d))
+        R.step()
+        t = R.stats()
+        out.append((R.state(), R.trace(), [t[q] for q in ("evals", "tests", "prior_rejects",
+                                                          "shrink_caps")]))
+        R.close()
+    (a, ta, ca), (b, tb, cb) = out
+    assert np.array_equal(ta, tb) and ca == cb
+    assert np.array_equal(a["x"], b["x"]) and np.array_equal(a["logL"], b["logL"])
+    assert np.all(np.abs(a["x"]) <= edge)
