@@ -427,9 +427,11 @@ int32_t ns_chains_per_workgroup(const ns_ctx *ctx, int32_t run);
 
 /* NS_FLAG_AUTOTUNE's process-wide cache of tuned launch shapes, as a JSON file:
  * {"nss_tune": 2, "entries": [{"D", "lik", "mode", "upw", "rw", "chains", "planned", "C",
- * "plan"}, ...]} (the group shape: padded dimension, likelihood, precision, fragment capacity,
- * replacement, total chains, whether the plan kernel is allowed; the choice: chains per
- * workgroup and tests per round, 0 meaning the 4-test kernel).  ns_tune_save writes the cache
+ * "plan"[, "kernel"]}, ...]} (the group shape: padded dimension, likelihood, precision, fragment
+ * capacity, replacement, total chains, whether the plan kernel is allowed; the choice: chains per
+ * workgroup and tests per round, 0 meaning the 4-test kernel; the kernel it was tuned for:
+ * candidates 0 as points, 1 along lines, and 2 more in the tempered outer loop.  An entry that
+ * names no kernel holds for any or, with "planned" 1, for points).  ns_tune_save writes the cache
  * to path; ns_tune_load merges a file in the format ns_tune_save writes (its entries replace
  * cached ones of the same shape); ns_tune_clear empties the cache; contexts created
  * afterwards with NS_FLAG_AUTOTUNE start with the cached value.  *n (may be NULL) receives the

@@ -814,7 +814,26 @@ static std::vector<long long> tune_key(const ns_ctx *ctx, const Group &G)
 {
     long long chains = 0;
     for (int r : G.runs) chains += ctx->runs[r].k;
-    return {G.D, G.lik, G.mode, G.upwT, G.rw, chains, G.plan_ok ? 1 : 0};
+    return {G.D, G.lik, G.mode, G.upwT, G.rw, chains, G.plan_ok ? 1 : 0,
+            (G.line ? 1 : 0) + (ctx->smc ? 2 : 0)};
+}
+
+// The kernel of an entry that names none (a file from before the candidates were evaluated along
+// lines): any, or for the 16-bit mixture chains that of points, for whose planned tests it was
+// tuned (held to 4 or 8 tests the same chains take three to eight times as long as on their line).
+constexpr long long kAnyKernel = -1;
+static long long unnamed_kernel(long long planned) { return planned ? 0 : kAnyKernel; }
+
+// The cached shape of group G (C = 0: none); g_tune_mu held.
+static Shape tuned_shape(const ns_ctx *ctx, const Group &G)
+{
+    std::vector<long long> key = tune_key(ctx, G);
+    auto it = g_tuned.find(key);
+    if (it == g_tuned.end() && !G.plan_ok) {
+        key.back() = kAnyKernel;
+        it = g_tuned.find(key);
+    }
+    return it == g_tuned.end() ? Shape{0, 0} : it->second;
 }
 
 // Launch shape of group g's runs, on the host and in the device descriptors (slot n mirrors
@@ -1353,8 +1372,7 @@ extern "C" ns_status ns_init_batch(int32_t n_runs, const ns_prior *priors,
         Shape cached{0, 0};
         {
             std::lock_guard<std::mutex> lk(g_tune_mu);
-            auto it = g_tuned.find(tune_key(ctx, G));
-            if (it != g_tuned.end()) cached = it->second;
+            cached = tuned_shape(ctx, G);
         }
         if (cached.C > 0) {
             for (int r : G.runs) ctx->runs[r].R.C = cached.C;
@@ -1536,8 +1554,9 @@ extern "C" ns_status ns_run(ns_ctx *ctx, int32_t max_iter, int32_t *iters)
 }
 
 // The tuning cache as JSON: {"nss_tune": 2, "entries": [{"D": .., "lik": .., "mode": ..,
-// "upw": .., "rw": .., "chains": .., "planned": .., "C": .., "plan": ..}, ...]}, one entry per
-// line ("planned": whether the group may use the hypothesis-plan kernel).
+// "upw": .., "rw": .., "chains": .., "planned": .., "C": .., "plan": ..[, "kernel": ..]}, ...]},
+// one entry per line ("planned": whether the group may use the hypothesis-plan kernel; "kernel":
+// 1 along lines, 0 points, 2 more in the tempered outer loop).
 extern "C" ns_status ns_tune_save(const char *path, int32_t *n)
 {
     if (!path) return NS_EINVAL;
@@ -1549,9 +1568,11 @@ extern "C" ns_status ns_tune_save(const char *path, int32_t *n)
     for (const auto &kv : g_tuned) {
         const std::vector<long long> &k = kv.first;
         fprintf(f, "%s\n  {\"D\": %lld, \"lik\": %lld, \"mode\": %lld, \"upw\": %lld, "
-                   "\"rw\": %lld, \"chains\": %lld, \"planned\": %lld, \"C\": %d, \"plan\": %d}",
+                   "\"rw\": %lld, \"chains\": %lld, \"planned\": %lld, \"C\": %d, \"plan\": %d",
                 i++ ? "," : "", k[0], k[1], k[2], k[3], k[4], k[5], k[6], kv.second.C,
                 kv.second.plan);
+        if (k[7] != unnamed_kernel(k[6])) fprintf(f, ", \"kernel\": %lld", k[7]);
+        fprintf(f, "}");
     }
     fprintf(f, "\n]}\n");
     const bool ok = fclose(f) == 0;
@@ -1576,11 +1597,11 @@ extern "C" ns_status ns_tune_load(const char *path, int32_t *n)
     if (pos == std::string::npos)
         return fail(nullptr, NS_EINVAL, std::string(path) + ": not a tuning cache");
     for (; (pos = txt.find('{', pos)) != std::string::npos; ++pos) {
-        long long D, lik, mode, upw, rw, chains, planned;
-        int C, plan, end = -1;
+        long long D, lik, mode, upw, rw, chains, planned, kernel;
+        int C, plan, end = -1, close = -1;
         if (sscanf(txt.c_str() + pos,
                    "{\"D\": %lld, \"lik\": %lld, \"mode\": %lld, \"upw\": %lld, \"rw\": %lld, "
-                   "\"chains\": %lld, \"planned\": %lld, \"C\": %d, \"plan\": %d}%n",
+                   "\"chains\": %lld, \"planned\": %lld, \"C\": %d, \"plan\": %d%n",
                    &D, &lik, &mode, &upw, &rw, &chains, &planned, &C, &plan, &end) != 9 ||
             end < 0 || C < 1 || C > kMaxChainsPerWG || chains < 1 || (rw != 0 && rw != 1) ||
             (D != 32 && D != 64 && D != 128 && D != 320) || lik < LIK_MIXTURE || lik > LIK_RG ||
@@ -1590,7 +1611,16 @@ extern "C" ns_status ns_tune_load(const char *path, int32_t *n)
             (planned != 0 && planned != 1) || (plan != 0 && plan != 8 && plan != 16) ||
             (plan != 0 && !planned))
             return fail(nullptr, NS_EINVAL, std::string(path) + ": malformed entry");
-        add[{D, lik, mode, upw, rw, chains, planned}] = Shape{C, plan};
+        pos += end;
+        if (sscanf(txt.c_str() + pos, ", \"kernel\": %lld}%n", &kernel, &close) == 1) {
+            if (close < 0 || kernel < 0 || kernel > (planned ? 1 : 3))
+                return fail(nullptr, NS_EINVAL, std::string(path) + ": malformed entry");
+        } else if (txt[pos] == '}') {
+            kernel = unnamed_kernel(planned);
+        } else {
+            return fail(nullptr, NS_EINVAL, std::string(path) + ": malformed entry");
+        }
+        add[{D, lik, mode, upw, rw, chains, planned, kernel}] = Shape{C, plan};
     }
     std::lock_guard<std::mutex> lk(g_tune_mu);
     for (const auto &kv : add) g_tuned[kv.first] = kv.second;
