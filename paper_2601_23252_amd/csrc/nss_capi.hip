@@ -1311,7 +1311,7 @@ extern "C" ns_status ns_init_batch(int32_t n_runs, const ns_prior *priors,
         }
         rh.upw = (rh.mode == NS_FP64 || rh.lik == LIK_GP) ? 1 : upw_template(rh.D, upw_for(rh.P));
         rh.P = problem_for_mode(rh, rh.mode);
-        rh.P.gp_spin_max = (rh.cfg.flags & NS_FLAG_GP_NO_WAIT) ? -1 : (1 << 22);
+        rh.P.gp_give_up = (rh.cfg.flags & NS_FLAG_GP_NO_WAIT) ? 1 : 0;
         if ((st = alloc_run(ctx, r)) != NS_OK) return bail(st);
         // group by compiled HRSS kernel; the 16-bit mixture chains may plan 8 or 16 tests per
         // round unless NS_FLAG_SHALLOW_PLAN keeps them on the 4-test kernel

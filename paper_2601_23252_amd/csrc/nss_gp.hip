@@ -140,8 +140,7 @@ __device__ __forceinline__ T dot16(const T (&a)[16], const T (&b)[16])
 // -|z|^2 / 2 - sum_i log L_ii of N(y; 0, K_theta + sigma_n^2 I) at u = log theta with the
 // factorisation in T.  Called by every thread of the workgroup with the same u (the result is
 // uniform); the inputs and targets must be staged at kOffXs / kOffYs.  failed = a pivot was not
-// positive.  A negative spin_max makes the evaluation fail as timed out at once (a host-set test
-// mode of the failure path).
+// positive.
 //
 // A function of its own rather than inlined in the chain's loop: there, the loop's state and what
 // the compiler hoists out of it (addresses, the math functions' constants) took registers that
@@ -152,12 +151,12 @@ struct GpPoint {
 };
 struct GpResult {
     double L;
-    int failed, timed_out;
+    int failed;
 };
 template <typename T>
-__device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_ptr lds,
-                                                         int spin_max)
+__device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_ptr lds)
 {
+    n = uniform_i(n);   // (an argument arrives in a vector register)
     unsigned char *smem = (unsigned char *)lds;
     const double *u = pt.u;
     typedef Mf<T> M;
@@ -176,14 +175,12 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
     // FP32 refinement: alpha = L^{-T} z, the partial products of one block step
     float *alpha = (float *)(zb + kGpMaxObs);
     float *part = alpha + kGpMaxObs;
-    if (spin_max < 0) return GpResult{-INFINITY, 1, 1};
     // the thread index, opaque to the compiler in each evaluation and each block column: keeps
     // the many lane-derived masks and LDS addresses of the unrolled code below from being hoisted
     // out of the loops around it, where they would hold registers across all of it
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane0 = tid & 63, w = uniform_i(tid >> 6);
-    n = uniform_i(n);   // (an argument arrives in a vector register)
     const int NT = (n + 15) >> 4, NTT = NT * (NT + 1) / 2;
     const GpTheta h = gp_theta(u);
 
@@ -436,7 +433,7 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
         q = qv;
     }
     __syncthreads();   // the LDS slots are reused by the next evaluation
-    return GpResult{fma(q, -0.5, -ld), failed, 0};
+    return GpResult{fma(q, -0.5, -ld), failed};
 }
 
 // n/2 log(2 pi), rounded: log L of a chain's point is the evaluator's value less this
@@ -448,15 +445,13 @@ __device__ __forceinline__ double gp_norm(int n)
 }
 
 template <typename T>
-__device__ __forceinline__ double gp_eval(const double *u, int n, unsigned char *smem, bool &failed,
-                                          bool &timed_out, int spin_max = 0)
+__device__ __forceinline__ double gp_eval(const double *u, int n, unsigned char *smem, bool &failed)
 {
     GpPoint pt;
 #pragma unroll
     for (int a = 0; a < kGpD; ++a) pt.u[a] = u[a];
-    const GpResult r = gp_eval_at<T>(pt, n, (lds_ptr)smem, spin_max);
+    const GpResult r = gp_eval_at<T>(pt, n, (lds_ptr)smem);
     failed = uniform_i(r.failed) != 0;
-    timed_out = uniform_i(r.timed_out) != 0;
     return r.L;
 }
 
@@ -514,12 +509,11 @@ __global__ __launch_bounds__(kGpThreads) void k_eval_gp(Launch Lc, const double 
 #pragma unroll
     for (int a = 0; a < kGpD; ++a) u[a] = X[(size_t)a * ld + i];
     __syncthreads();
-    bool failed = false, timed_out = false;
+    bool failed = false;
     double L;
-    if constexpr (MODE == MODE_FP64) L = gp_eval<double>(u, P.gp_n, smem, failed, timed_out);
-    else L = gp_eval<float>(u, P.gp_n, smem, failed, timed_out);
+    if constexpr (MODE == MODE_FP64) L = gp_eval<double>(u, P.gp_n, smem, failed);
+    else L = gp_eval<float>(u, P.gp_n, smem, failed);
     L = fma(-0.5 * (double)P.gp_n, LOG_2PI, L);
-    if (timed_out && from_run && threadIdx.x == 0) atomicAdd(&R.ctr[10], 1ull);
     if (threadIdx.x == 0) {
         unsigned long long nf = 0;
         out[i] = failed ? -INFINITY : sanitize(L, nf);
@@ -562,7 +556,6 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
     // vector ones.  Thread 0 publishes the counters.
     unsigned long long c_evals = 0, c_tests = 0, c_prej = 0, c_outcap = 0, c_shcap = 0,
                        c_nonfin = 0, c_rc = 0, c_viol = 0, c_wait = 0;
-    const int spin_max = P.gp_spin_max;
     const double norm = gp_norm(n);
     __syncthreads();
 
@@ -664,25 +657,23 @@ __global__ __launch_bounds__(kGpThreads) void k_hrss_gp(Launch Lc)
             ++c_prej;
         } else {
             // the single evaluation site
-            bool failed = false, tout = false;
-            if constexpr (MODE == MODE_FP64) {
-                L = gp_eval<double>(y, n, smem, failed, tout, spin_max) - norm;
-                c_wait += uniform_i(tout);
+            bool failed = false;
+            if (P.gp_give_up) {
+                failed = true;
+                ++c_wait;
+            } else if constexpr (MODE == MODE_FP64) {
+                L = gp_eval<double>(y, n, smem, failed) - norm;
             } else {
                 int need64 = (phase == PH_FINAL);
                 if (!need64 && uniform_i(gp_illcond(P, y))) {   // FP64 only, no FP32 attempt
                     need64 = 1;
                     ++c_rc;
                 } else if (!need64) {
-                    L = gp_eval<float>(y, n, smem, failed, tout, spin_max) - norm;
-                    c_wait += uniform_i(tout);
-                    need64 = uniform_i((failed && !tout) || !(L == L) || gp_near(L, Lstar, P, y));
+                    L = gp_eval<float>(y, n, smem, failed) - norm;
+                    need64 = uniform_i(failed || !(L == L) || gp_near(L, Lstar, P, y));
                     if (need64) ++c_rc; else exact = 0;
                 }
-                if (need64) {
-                    L = gp_eval<double>(y, n, smem, failed, tout, spin_max) - norm;
-                    c_wait += uniform_i(tout);
-                }
+                if (need64) L = gp_eval<double>(y, n, smem, failed) - norm;
             }
             if (failed) L = -INFINITY;
             if (phase == PH_FINAL) {

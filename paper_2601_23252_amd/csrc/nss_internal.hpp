@@ -45,8 +45,7 @@ struct DevProblem {
     float guard_abs;       //   (GP: rel |L| + abs + kappa_coef kappa n / 256)
     float guard_kappa;
     int gp_n;              // GP: observations
-    int gp_spin_max;       // GP: < 0 makes every chain evaluation give up at once (a test
-                           //     mode of the failure path)
+    int gp_give_up;        // GP: every chain evaluation fails (a test mode of the failure path)
     const double *gp_x;    // GP: [n][2] inputs
     const double *gp_y;    // GP: [n] targets
     double rg_la, rg_l1a;  // Gaussian-Rastrigin: log alpha, log(1 - alpha) (-inf at 0 / 1)
