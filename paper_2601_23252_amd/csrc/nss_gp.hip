@@ -24,14 +24,14 @@
 // choose: the prior reaches sigma_f^2 / sigma_n^2 = 1e8, where another rounding of an entry, a
 // root or a product moves log L by 1e-9 of itself, and results are to stay what they are.
 //
-// What bounds it at n = 256 (about 255,000 cycles an evaluation): the chain of 16 block columns,
+// What bounds it at n = 256 (about 250,000 cycles an evaluation): the chain of 16 block columns,
 // each about 3,000 cycles to bring the diagonal tile up to date and into rows, 4,000 for its 16
 // dependent pivots and 1,800 for the panel, then the entries' exponentials (50,000) and what the
-// updates leave uncovered.  500 chains of 30 steps: 26.2 ms a pass with one wave factoring, then
+// updates leave uncovered.  500 chains of 30 steps: 25.9 ms a pass with one wave factoring, then
 // inverting, each diagonal tile and the tiles in a layout that had to be turned for every product,
-// 16.7 here; at n = 100 in the FP32 mode 5.5 and 3.8 ms.  (n and the tile indices have to be
-// wave-uniform to the compiler: as vector values they came back from scratch memory for every
-// tile, 25.3 ms.)
+// 16.4 here; at n = 100 in the FP32 mode 5.3 and 3.7 ms.  (n, the tile indices and the LDS address
+// have to be wave-uniform values to the compiler: as vector values the indices came back from
+// scratch memory for every tile, 25.3 ms.)
 //
 //  k_hrss_gp   one HRSS chain per workgroup (App. A.6), candidates evaluated one at a time
 //  k_eval_gp   one point per workgroup (initial live set, tests)
@@ -156,7 +156,9 @@ struct GpResult {
 template <typename T>
 __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_ptr lds)
 {
-    n = uniform_i(n);   // (an argument arrives in a vector register)
+    // (arguments arrive in vector registers)
+    lds = (lds_ptr)(uintptr_t)(unsigned)uniform_i((int)(unsigned)(uintptr_t)lds);
+    n = uniform_i(n);
     unsigned char *smem = (unsigned char *)lds;
     const double *u = pt.u;
     typedef Mf<T> M;
@@ -450,7 +452,11 @@ __device__ __forceinline__ double gp_eval(const double *u, int n, unsigned char 
     GpPoint pt;
 #pragma unroll
     for (int a = 0; a < kGpD; ++a) pt.u[a] = u[a];
-    const GpResult r = gp_eval_at<T>(pt, n, (lds_ptr)smem);
+    // (opaque: known to be the kernel's dynamic LDS in every call, its address would be looked up in
+    // a table in memory wherever the evaluator uses it)
+    lds_ptr lds = (lds_ptr)smem;
+    asm volatile("" : "+v"(lds));
+    const GpResult r = gp_eval_at<T>(pt, n, lds);
     failed = uniform_i(r.failed) != 0;
     return r.L;
 }
