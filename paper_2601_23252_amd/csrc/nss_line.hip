@@ -37,10 +37,11 @@
 // eight polynomials side by side for their latency (two: 8.6 ms).
 //
 // The funnel's radius is a parabola too, but exp(-v) weighs it by up to e^20 in the neck, where it
-// is far smaller than at a point in the mouth: there a parabola's rounding, relative to the larger
-// one, decided (1e-6 of log L at v = -18).  It is summed from each candidate's coordinates in the
-// same way, which costs what the products with the directions did (32 funnels of d <= 128 beside 32
-// Gaussians, 55.9 ms a pass with the parabola and 55.2 so).
+// is far smaller than at a point in the mouth, and a parabola's rounding is relative to the larger
+// one (1e-6 of log L at v = -18).  A candidate whose log L lies within 1e-13 of the terms so weighed
+// (their rounding over a block is below 1e-14) of L* has its radius summed from its coordinates, in
+// the way of the Rastrigin sums; the tempered slices, which go on from the value itself, and the
+// random walk, whose products such sums cost no more than, always.
 //
 // The random walk's proposals x + u_n are the same products at t = 1: a block's fifteen are tested
 // at once from the current point, and again after each acceptance, their moves in registers for
@@ -83,7 +84,7 @@ struct LineLayout {
 };
 __host__ __device__ inline LineLayout line_layout(int D, int K, int lik, bool box, bool rw)
 {
-    const int forms = (lik == LIK_MIXTURE ? K : 0) + (box ? 0 : 1);
+    const int forms = (lik == LIK_MIXTURE ? K : lik == LIK_FUNNEL && !rw ? 1 : 0) + (box ? 0 : 1);
     LineLayout o;
     int off = 0;
     o.gram = off; off += al16(forms * 16 * kLineLd * 8);
@@ -192,10 +193,11 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
     constexpr int NJB = D / 16, NKS = D / 4, LDV = D + 1;   // LDV: row stride of the walk's proposals
     constexpr bool MIX = LIK == LIK_MIXTURE, RG = LIK == LIK_RG;
     constexpr bool TEMP = KIND == LINE_TEMPERED, RW = KIND == LINE_WALK;
+    constexpr bool FORM = MIX || (LIK == LIK_FUNNEL && KIND == LINE_SLICE);   // parabolas
     const LineLayout lay = line_layout(D, P.K, LIK, BOX, RW);
     const int tid = threadIdx.x, w = uniform_i(tid >> 6), l = tid & 63;
     const int col = l & 15, row = l >> 4;
-    const int d = P.d, K = MIX ? P.K : 0, C = R.C, p = R.p;
+    const int d = P.d, K = MIX ? P.K : FORM ? 1 : 0, C = R.C, p = R.p;
     const double Lstar = R.scal[0], beta = Lstar;   // tempered: the inverse temperature
     const int t0 = R.iscal[1], nsurv = R.iscal[2];
     const uint32_t it = (uint32_t)R.iscal[3] + 1u;
@@ -437,18 +439,24 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                     }
                     put(gpri, Gp);
                 }
-            } else if (!BOX) {   // the Gaussian prior's form alone
+            } else if (FORM || !BOX) {
+                // the funnel's form: the coordinates after the first (and the Gaussian prior's)
                 const bool dcol = col < nb;
                 const auto vrow = dirs + (size_t)(s0 + (dcol ? col : 0)) * D;
-                d4v Gp = (d4v){0.0, 0.0, 0.0, 0.0};
+                d4v G = (d4v){0.0, 0.0, 0.0, 0.0}, Gp = (d4v){0.0, 0.0, 0.0, 0.0};
 #pragma unroll 16
                 for (int ks = 0; ks < NKS; ++ks) {
                     const int kk = 4 * ks + row;
                     const double bv = dcol ? vrow[kk] : (xcol ? xs[kk] : 0.0);
-                    const double bp = kk < d ? (xcol ? bv - spa[kk] : bv) * sipb[kk] : 0.0;
-                    Gp = __builtin_amdgcn_mfma_f64_16x16x4f64(bp, bp, Gp, 0, 0, 0);
+                    const double bb = kk > 0 ? bv : 0.0;
+                    if (FORM) G = __builtin_amdgcn_mfma_f64_16x16x4f64(bb, bb, G, 0, 0, 0);
+                    if (!BOX) {
+                        const double bp = kk < d ? (xcol ? bv - spa[kk] : bv) * sipb[kk] : 0.0;
+                        Gp = __builtin_amdgcn_mfma_f64_16x16x4f64(bp, bp, Gp, 0, 0, 0);
+                    }
                 }
-                put(gpri, Gp);
+                if (FORM) put(gram, G);
+                if (!BOX) put(gpri, Gp);
             }
             wave_sync();
             // the point's products with the directions (row 15; column 0 is the current step's),
@@ -458,8 +466,8 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             for (int q = 0; q < NR; ++q) {
                 const int c = 4 * q + row;
                 const double *g15 = gram + ((c < K ? c : 0) * 16 + 15) * kLineLd;
-                h[q] = MIX ? g15[col] : 0.0;
-                aa[q] = MIX ? g15[15] : 0.0;
+                h[q] = FORM ? g15[col] : 0.0;
+                aa[q] = FORM ? g15[15] : 0.0;
             }
             if (!BOX) hp = gpri[15 * kLineLd + col];
             if (s0 + kLineB < p) fetch_block(s0 + kLineB);
@@ -591,10 +599,11 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             }
 
             // ---- the block's steps ----
+            double size = aa[0];   // what the forms' rounding is relative to (funnel)
             double tn = tt[col], grn[NR], gpn = 0.0;   // the next step's, read ahead
 #pragma unroll
             for (int q = 0; q < NR; ++q)
-                grn[q] = MIX ? gram[((4 * q + row < K ? 4 * q + row : 0) * 16) * kLineLd + col] : 0.0;
+                grn[q] = FORM ? gram[((4 * q + row < K ? 4 * q + row : 0) * 16) * kLineLd + col] : 0.0;
             if (!BOX) gpn = gpri[col];
             for (int sb = 0; sb < nb; ++sb) {
                 const int st = s0 + sb;
@@ -628,7 +637,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
 #pragma unroll
                     for (int q = 0; q < NR; ++q) {
                         const int c = 4 * q + row < K ? 4 * q + row : 0;
-                        if (MIX) grn[q] = gram[(c * 16 + sn) * kLineLd + min(sn + col, 15)];
+                        if (FORM) grn[q] = gram[(c * 16 + sn) * kLineLd + min(sn + col, 15)];
                     }
                     if (!BOX) gpn = gpri[sn * kLineLd + min(sn + col, 15)];
                 }
@@ -637,7 +646,8 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                     v0 = lane_value(vr[0], 0);
                     x00 = lane_value(x0r[0], 0);
                 }
-                if constexpr (!MIX) {   // the point and the direction, for the coordinate sums
+                // the point and the direction, for the coordinate sums
+                auto spread = [&]() {
                     const bool sum0 = RG || l > 0;   // (not the funnel's v)
 #pragma unroll
                     for (int i = 0; i < NA; ++i)
@@ -646,7 +656,8 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                             vs[l + 64 * i] = i > 0 || sum0 ? vr[i] : 0.0;
                         }
                     wave_sync();
-                }
+                };
+                if constexpr (!FORM) spread();
                 // box prior: t inside [tin0, tin1] keeps every coordinate in the box whatever
                 // the rounding of x + t v, t outside [tou0, tou1] puts one out; the margins
                 // cover the FP32 quotients and, away from the faces, the rounding of y.  The
@@ -670,13 +681,14 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                         m1 = fminf(m1, (float)(pos ? hi : lo) * rv);
                         m0 = fminf(m0, (float)(pos ? lo : hi) * rv);
                     }
+                    face = face || fminf(m0, m1) < 1e-30f;
                     m1 = wave_min_pos(m1);
                     m0 = wave_min_pos(m0);
                     tin1 = m1 * (1.f - 2e-5f);
                     tin0 = -m0 * (1.f - 2e-5f);
                     tou1 = m1 * (1.f + 2e-5f);
                     tou0 = -m0 * (1.f + 2e-5f);
-                    if (__any(face) || fminf(m0, m1) < 1e-30f) {   // coordinate by coordinate
+                    if (__any(face)) {   // decided coordinate by coordinate
                         tin0 = INFINITY; tin1 = -INFINITY;
                         tou0 = -INFINITY; tou1 = INFINITY;
                     }
@@ -789,23 +801,41 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                                       doubt;
                         }
                     } else {
-                        // the lane's coordinates 8 i + 2 row, + 1
-                        double q0 = 0.0, q1 = 0.0;
+                        const double vv = fma(t, v0, x00), ew = 0.5 * exp(-vv);
+                        const double rest = -vv * vv / 18.0 - 0.5 * (LOG_2PI + log(9.0)) -
+                                            (double)(d - 1) * 0.5 * (vv + LOG_2PI);
+                        auto radius2 = [&]() -> double {   // the lane's coordinates 8 i + 2 row, + 1
+                            double q0 = 0.0, q1 = 0.0;
 #pragma unroll 4
-                        for (int a = 2 * row; a < d; a += 8) {   // (zero from d up)
-                            const double2 x2 = *(const double2 *)(xs + a);
-                            const double2 v2 = *(const double2 *)(vs + a);
-                            const double y0 = fma(t, v2.x, x2.x), y1 = fma(t, v2.y, x2.y);
-                            q0 = fma(y0, y0, q0);
-                            q1 = fma(y1, y1, q1);
+                            for (int a = 2 * row; a < d; a += 8) {   // (zero from d up)
+                                const double2 x2 = *(const double2 *)(xs + a);
+                                const double2 v2 = *(const double2 *)(vs + a);
+                                const double y0 = fma(t, v2.x, x2.x), y1 = fma(t, v2.y, x2.y);
+                                q0 = fma(y0, y0, q0);
+                                q1 = fma(y1, y1, q1);
+                            }
+                            double s2 = q0 + q1;
+                            s2 += __shfl_xor(s2, 16, 64);
+                            s2 += __shfl_xor(s2, 32, 64);
+                            return s2;
+                        };
+                        if constexpr (FORM) {
+                            const double tb = t * b2[0], tg = t * t * g[0];
+                            Lv = rest - ew * (aa[0] + tb + tg);
+                            in = (unsigned)__ballot(Lv > Lstar);
+                            const double slack = 1e-13 * ew * (size + fabs(tb) + tg);
+                            const unsigned doubt =
+                                (unsigned)__ballot(!(fabs(Lv - Lstar) > slack)) & okm;
+                            if (doubt) {
+                                spread();
+                                Lv = rest - ew * radius2();
+                                in = (in & ~doubt) | ((unsigned)__ballot(Lv > Lstar) & doubt);
+                                wave_sync();
+                            }
+                        } else {
+                            Lv = rest - ew * radius2();
+                            in = (unsigned)__ballot(Lv > Lstar);
                         }
-                        double s2 = q0 + q1;
-                        s2 += __shfl_xor(s2, 16, 64);
-                        s2 += __shfl_xor(s2, 32, 64);
-                        const double vv = fma(t, v0, x00);
-                        Lv = -vv * vv / 18.0 - 0.5 * (LOG_2PI + log(9.0)) - 0.5 * exp(-vv) * s2
-                             - (double)(d - 1) * 0.5 * (vv + LOG_2PI);
-                        if constexpr (!TEMP) in = (unsigned)__ballot(Lv > Lstar);
                     }
                     if constexpr (TEMP)
                         in = (unsigned)__ballot((BOX ? 0.0 : lp) + beta * (Lv - logL0) > lu);
@@ -924,6 +954,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                     moved = true;
 #pragma unroll
                     for (int i = 0; i < NA; ++i) x0r[i] = fma(ta, vr[i], x0r[i]);
+                    if (LIK == LIK_FUNNEL) size += fabs(ta * b2[0]) + ta * ta * g[0];
 #pragma unroll
                     for (int q = 0; q < NR; ++q) {
                         aa[q] = fma(ta, fma(ta, g[q], b2[q]), aa[q]);
