@@ -599,7 +599,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
             }
 
             // ---- the block's steps ----
-            double size = aa[0];   // what the forms' rounding is relative to (funnel)
+            float size = (float)aa[0];   // what the form's rounding is relative to (funnel)
             double tn = tt[col], grn[NR], gpn = 0.0;   // the next step's, read ahead
 #pragma unroll
             for (int q = 0; q < NR; ++q)
@@ -806,7 +806,9 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                                             (double)(d - 1) * 0.5 * (vv + LOG_2PI);
                         auto radius2 = [&]() -> double {   // the lane's coordinates 8 i + 2 row, + 1
                             double q0 = 0.0, q1 = 0.0;
-#pragma unroll 4
+                            // (rarely run beside the parabola: registers before speed)
+                            constexpr int kUnroll = FORM ? 1 : 4;
+#pragma unroll kUnroll
                             for (int a = 2 * row; a < d; a += 8) {   // (zero from d up)
                                 const double2 x2 = *(const double2 *)(xs + a);
                                 const double2 v2 = *(const double2 *)(vs + a);
@@ -823,9 +825,10 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                             const double tb = t * b2[0], tg = t * t * g[0];
                             Lv = rest - ew * (aa[0] + tb + tg);
                             in = (unsigned)__ballot(Lv > Lstar);
-                            const double slack = 1e-13 * ew * (size + fabs(tb) + tg);
+                            // (in FP32: too large a term makes it infinite, and everything doubtful)
+                            const float slack = (float)ew * (size + (float)(fabs(tb) + tg)) * 1e-13f;
                             const unsigned doubt =
-                                (unsigned)__ballot(!(fabs(Lv - Lstar) > slack)) & okm;
+                                (unsigned)__ballot(!(fabs(Lv - Lstar) > (double)slack)) & okm;
                             if (doubt) {
                                 spread();
                                 Lv = rest - ew * radius2();
@@ -954,7 +957,7 @@ __global__ __launch_bounds__(256, OCC) void k_hrss_line(Launch Lc, int fp64)
                     moved = true;
 #pragma unroll
                     for (int i = 0; i < NA; ++i) x0r[i] = fma(ta, vr[i], x0r[i]);
-                    if (LIK == LIK_FUNNEL) size += fabs(ta * b2[0]) + ta * ta * g[0];
+                    if (LIK == LIK_FUNNEL) size += (float)(fabs(ta * b2[0]) + ta * ta * g[0]);
 #pragma unroll
                     for (int q = 0; q < NR; ++q) {
                         aa[q] = fma(ta, fma(ta, g[q], b2[q]), aa[q]);
