@@ -40,15 +40,15 @@ sys.path.insert(0, ROOT)
 # (precision, chain length, chains per workgroup, planned tests per round), recorded for the
 # kernel sources with this sha256 prefix; reported as null once the sources differ or for a
 # shape the counters were not taken on.
-TRAFFIC = {("fp16x3", 320, 4, 8): 188.7e6}
-TRAFFIC_SOURCE_SHA = "c5036605d8601153"
+TRAFFIC = {("fp16x3", 320, 4, 8): 188.6e6}
+TRAFFIC_SOURCE_SHA = "c3815f5d586d0ca0"
 
 
 # VALU lane-instructions per evaluation issued by the chain kernel (SQ_INSTS_VALU x 64 /
 # evaluations of the profiled launches), keyed like TRAFFIC, for the kernel sources with this
 # prefix: the instruction view of the same kernel (its chain logic runs on the vector ALU).
-HRSS_VALU_PER_EVAL = {("fp16x3", 320, 4, 8): 24544.0}
-HRSS_VALU_SOURCE_SHA = "c5036605d8601153"
+HRSS_VALU_PER_EVAL = {("fp16x3", 320, 4, 8): 24401.0}
+HRSS_VALU_SOURCE_SHA = "c3815f5d586d0ca0"
 
 KERNEL_SOURCES = ("nss_kernels.hip", "nss_hrss_plan.hip", "nss_tiles.hpp", "nss_internal.hpp")
 
@@ -525,8 +525,8 @@ def lnz_rastrigin_gauss(d, alpha, r=5.14, amp=10.0):
 # VALU lane-instructions per likelihood evaluation of the Gaussian-Rastrigin k_hrss_line at d=100
 # (SQ_INSTS_VALU x 64 / evaluations of the profiled launches), for the kernel source with this
 # sha256 prefix.
-RG_VALU_PER_EVAL = 35622.0
-RG_SOURCE_SHA = "d2f5037ac61b1803"
+RG_VALU_PER_EVAL = 35121.0
+RG_SOURCE_SHA = "c60e054be72a9dc1"
 
 
 def _rastrigin_table(args):

@@ -208,9 +208,10 @@ typedef enum {
                                  * Gaussian-Rastrigin likelihood that read their directions from the buffer
                                  * evaluate up to sixteen candidates at a time along each
                                  * step's line: quadratic forms are parabolas in t, held in
-                                 * FP64 in every precision (no re-checks), and each chain's
-                                 * final point is evaluated as a point.  Decisions and
-                                 * trajectories are identical. */
+                                 * FP64 in every precision (no re-checks; forms so much larger
+                                 * elsewhere that their rounding could decide are evaluated as
+                                 * points or sums), and each chain's final point is evaluated
+                                 * as a point.  Decisions and trajectories are identical. */
 #define NS_FLAG_PLAN8 128  /* mixture chains in a 16-bit mode plan 8 tests per round (the
                            * next two stepping-out tests of each open end and the shrink
                            * proposals of the three likeliest expansion outcomes), each
