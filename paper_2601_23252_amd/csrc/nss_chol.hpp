@@ -80,15 +80,16 @@ __device__ __forceinline__ float rsq_newton(float x) { return rsq_refined(x); }
 // Eliminates a block column with one row per lane: a[c] is the lane's row, lane i < 16
 // row i of the diagonal tile.  On return lane i < 16 holds row i of the factor (its entries above
 // the diagonal are not meaningful), the other lanes their row times the transposed inverse
-// factor (of a row of the identity: a column of the inverse).  roots: the product of the pivots'
-// roots; bad: a pivot was not positive (the results are then not meaningful).  ROUNDED: the roots
-// and quotients are rounded to nearest, as sqrt and / are (about 60 cycles more on a pivot's
+// factor (of a row of the identity: a column of the inverse).  p0: the product of the pivots'
+// roots; in FP32, whose roots are rounded, p0 and p1: of the first and the last eight pivots
+// themselves.  bad: a pivot was not positive (the results are then not meaningful).  ROUNDED: the
+// roots and quotients are rounded to nearest, as sqrt and / are (about 60 cycles more on a pivot's
 // chain), for a matrix whose last pivots are its rounding error: there another rounding is another
 // factor.
 template <typename T, bool ROUNDED = false>
-__device__ __forceinline__ void eliminate(T (&a)[16], double &roots, int &bad)
+__device__ __forceinline__ void eliminate(T (&a)[16], double &p0, double &p1, int &bad)
 {
-    roots = 1.0;
+    p0 = p1 = 1.0;
     bad = 0;
 #pragma unroll
     for (int jj = 0; jj < 16; ++jj) {
@@ -104,7 +105,9 @@ __device__ __forceinline__ void eliminate(T (&a)[16], double &roots, int &bad)
             a[jj] = (threadIdx.x & 63) == jj ? root : fma(fma(-q, root, a[jj]), inv, q);
         } else {
             const T r = rsq_newton(piv);
-            roots *= (double)(piv * r);
+            if (sizeof(T) == 8) p0 *= (double)(piv * r);
+            else if (jj < 8) p0 *= (double)piv;
+            else p1 *= (double)piv;
             a[jj] *= r;
         }
 #pragma unroll

@@ -165,7 +165,7 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
     typedef typename M::v4 v4;
     const double *xs = (const double *)(smem + kOffXs);
     const double *ys = (const double *)(smem + kOffYs);
-    double *red = (double *)(smem + kOffMisc);   // log det / 2, |z|^2, partial sums, root products
+    double *red = (double *)(smem + kOffMisc);   // log det / 2, |z|^2, partial sums, pivots' products
     int *flag = (int *)(red + 16);
     double *sc = (double *)(smem + kOffSc);
     T *pan = (T *)(smem + kOffT);    // [2][16] panel tiles
@@ -290,16 +290,17 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
                 const T v = dg[(l & 15) * kTileLd + c];
                 a[c] = !(l & 16) ? v : (l & 15) == c ? T(1) : T(0);
             }
-            double roots;
+            double p0, p1;
             int bad;
-            eliminate<T>(a, roots, bad);
+            eliminate<T>(a, p0, p1, bad);
             if ((l >> 4) == 1) {   // lane 16 + c: column c of the inverse
                 T *lj = li + (J & (kGpInv<T> - 1)) * kTile + (l & 15);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) lj[r * kTileLd] = a[r];
             }
             if (l == 0) {
-                red[10 + (J & 1)] = roots;
+                red[10 + (J & 1)] = p0;
+                red[12 + (J & 1)] = p1;
                 if (bad) *flag = 1;
             }
         }
@@ -320,7 +321,8 @@ __device__ __attribute__((noinline)) GpResult gp_eval_at(GpPoint pt, int n, lds_
                 double q2 = fma((double)b[0], (double)b[0], (double)b[1] * (double)b[1]);
 #pragma unroll
                 for (int c = 2; c < 16; ++c) q2 = fma((double)b[c], (double)b[c], q2);
-                const double ld = log(red[10 + ((J - 1) & 1)]);
+                double ld = log(red[10 + ((J - 1) & 1)]);
+                if (refine) ld = 0.5 * (ld + log(red[12 + ((J - 1) & 1)]));
                 if (l == 0) {
                     red[0] += ld;
                     red[1] += q2;

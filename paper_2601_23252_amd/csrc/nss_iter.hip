@@ -493,11 +493,11 @@ __global__ __launch_bounds__(kCholThreads) void k_chol(Launch Lc)
             const bool prow = l >= 16 && below < rows;
             const int a0 = 16 * J + (l < 16 ? l : (prow ? 16 + below : 0));
             double *rp = cur + (a0 >> 4) * kTile + (a0 & 15) * kTileLd;
-            double a[16], roots;
+            double a[16], p0, p1;
             int bad;
 #pragma unroll
             for (int c = 0; c < 16; ++c) a[c] = rp[c];
-            eliminate<double, true>(a, roots, bad);
+            eliminate<double, true>(a, p0, p1, bad);
             if (w == 0 && l == 0 && bad) *fail = 1;
             if (prow || (w == 0 && l < 16)) {
                 const int ro = a0 * (a0 + 1) / 2;
